@@ -67,9 +67,11 @@ std::once_flag g_fft_once;
 // code must not pass the array's name to a kernel (it is a host-side stand-in, not a
 // device address): its address on each device comes from hipGetSymbolAddress, taken
 // once per device with that device current.
+// The ring starts follow in as much space again, in bands of m where they need more.
 constexpr size_t kScratchBytes = (size_t)64 << 20;
+constexpr size_t kStartScratchBytes = (size_t)64 << 20;
 constexpr int kMaxDevices = 64;
-__device__ __align__(256) unsigned char scratch[kScratchBytes];
+__device__ __align__(256) unsigned char scratch[kScratchBytes + kStartScratchBytes];
 std::mutex g_scratch_mu;
 void *g_scratch_ptr[kMaxDevices] = {};
 // host copies of the start data most recently sent to each device's scratch (kept
@@ -402,48 +404,117 @@ void choose_sizes(gsht_plan *p)
     p->npairs = (p->ntheta + 1) / 2;
 }
 
+// Places the three arrays of the ring starts of `band` values of m in one buffer.
+void place_starts(gsht_plan *p, void *buf, int band)
+{
+    const size_t n = (size_t)band * p->leg.np;
+    p->leg.band = band;
+    p->leg.sta = (double2 *)buf;
+    p->leg.stb = p->leg.sta + n;
+    p->leg.stk = (int32_t *)(p->leg.sta + n * (p->spin ? 2 : 1));
+}
+
+void set_leg_shapes(gsht_plan *p, int syn_r, int adj_r, int adj_b)
+{
+    p->syn_r = syn_r;
+    p->adj_r = adj_r;
+    p->adj_b = adj_b;
+    p->syn_nchunk = (p->npairs + 64 * syn_r - 1) / (64 * syn_r);
+    p->adj_nchunk = (p->npairs + 64 * adj_r - 1) / (64 * adj_r);
+}
+
+// Bytes of ring starts that the stage entry points take at most (more rings than any
+// plan has: bands of m).
+constexpr size_t kStageStartLimit = (size_t)2 << 30;
+
+// Ring starts: all m at once within start_limit bytes (0: no limit) and the device's
+// memory, otherwise the largest band that fits, down to one m.
+int alloc_starts(gsht_plan *p)
+{
+    p->leg.np = (p->npairs + 63) / 64 * 64;
+    const size_t per = leg_start_bytes(*p);
+    int band = p->mmax + 1;
+    if (p->start_limit)
+        band = (int)std::max<size_t>(1, std::min<size_t>((size_t)band, p->start_limit / per));
+    for (;;) {
+        void *buf = nullptr;
+        const int rc = dev_alloc(p, &buf, per * (size_t)band);
+        if (rc == GSHT_OK) {
+            place_starts(p, buf, band);
+            return GSHT_OK;
+        }
+        if (band == 1)
+            return rc;
+        band = (band + 1) / 2;
+    }
+}
+
+// Launch shapes of the Legendre kernels: slices of 64 ring pairs per wave, and degrees
+// per reduction block of the adjoint.  More slices per wave share the coefficient loads
+// (and the adjoint's lane reduction) between more rings, but make fewer, longer waves,
+// so the shape grows with the number of waves (of m values times chunks) it leaves.
+// Measured (FP64, ms, one launch; lmax = mmax, spin 2 / spin 0):
+//   synthesis  lmax  512: R = 1 0.041 / 0.022, R = 2 0.045 / 0.025, R = 4 0.075 / 0.033
+//              lmax 1400:       0.290 / 0.118,       0.296 / 0.113,       0.370 / 0.134
+//              lmax 2048:       0.716 / 0.274,       0.701 / 0.244,       0.728 / 0.270
+//              lmax 4096:       5.11  / 1.90,        4.64  / 1.64,        4.60  / 1.64
+//   adjoint    lmax  256: R = 1 0.038 / 0.027, R = 2 0.043 / 0.030, R = 4 0.049 / 0.033
+//              lmax 1024:       0.270 / 0.138,       0.260 / 0.122,       0.278 / 0.130
+//              lmax 2048:       1.51  / 0.72,        1.14  / 0.52,        1.02  / 0.43,
+//                         R = 5 1.29  / 0.51
+//              lmax 4096:       10.9  / 5.0,         8.2   / 3.4,         6.9   / 2.6,
+//                         R = 5 6.7   / 2.5
+// GSHT_SYN_R, GSHT_ADJ_R and GSHT_ADJ_B override (synthesis R in {1, 2, 4}; adjoint
+// (R, B) in {(1,8), (2,8), (2,4), (4,4), (3,8), (3,4), (4,8), (5,8)}).
+int choose_leg_shapes(gsht_plan *p)
+{
+    const int64_t nm = p->mmax + 1, nslice = (p->npairs + 63) / 64;
+    auto waves = [&](int r) { return nm * ((nslice + r - 1) / r); };
+    int r1 = waves(2) >= 8192 ? 2 : 1;
+    if (p->spin && waves(4) >= 16384)
+        r1 = 4;
+    int r2 = 1, b = 8;
+    for (int r : {2, 4})
+        if (waves(r) >= 4096)
+            r2 = r;
+    if (waves(5) >= 16384)
+        r2 = 5;
+    const char *sr = getenv("GSHT_SYN_R"), *ar = getenv("GSHT_ADJ_R"), *ab = getenv("GSHT_ADJ_B");
+    if (sr)
+        r1 = atoi(sr);
+    if (ar)
+        r2 = atoi(ar);
+    if (ab)
+        b = atoi(ab);
+    const int key = 100 * r2 + b;
+    if ((r1 != 1 && r1 != 2 && r1 != 4) ||
+        (key != 108 && key != 208 && key != 204 && key != 404 && key != 308 && key != 408 &&
+         key != 304 && key != 508))
+        return fail(GSHT_EINVAL, "unsupported Legendre launch shape syn_r=%d adj_r=%d adj_b=%d",
+                    r1, r2, b);
+    set_leg_shapes(p, r1, r2, b);
+    return GSHT_OK;
+}
+
 // Allocate the Legendre tables and upload the start data and deconvolution tables.
 int setup_legendre(gsht_plan *p, hipStream_t s, bool with_deconv)
 {
     int rc;
-    if ((rc = dev_alloc(p, &p->leg.ab, sizeof(double2) * (size_t)p->nalm)) != GSHT_OK) return rc;
+    if ((rc = dev_alloc(p, &p->leg.ab, sizeof(double) * (p->spin ? 2 : 1) * (size_t)p->nalm)) != GSHT_OK) return rc;
     if ((rc = dev_alloc(p, &p->leg.norm, sizeof(double) * (size_t)p->nalm)) != GSHT_OK) return rc;
     if ((rc = dev_alloc(p, &p->leg.start, sizeof(StartInfo) * (size_t)(p->mmax + 1))) != GSHT_OK)
         return rc;
     if ((rc = dev_alloc(p, &p->uprep, sizeof(double) * 2 * p->ncomp * (size_t)p->nalm)) != GSHT_OK)
         return rc;
-    if ((rc = dev_alloc(p, &p->acc, sizeof(double) * 2 * p->ncomp * (size_t)p->nalm)) != GSHT_OK)
-        return rc;
-    // Launch shapes of the Legendre kernels; GSHT_SYN_R, GSHT_ADJ_R and GSHT_ADJ_B
-    // override the defaults for tuning (synthesis R in {1, 2, 4}; adjoint (R, B) in
-    // {(1,8), (2,8), (2,4), (4,4), (3,8), (3,4), (4,8)}).
-    {
-        const char *sr = getenv("GSHT_SYN_R"), *ar = getenv("GSHT_ADJ_R"), *ab = getenv("GSHT_ADJ_B");
-        const int r1 = sr ? atoi(sr) : p->syn_r;
-        const int r2 = ar ? atoi(ar) : p->adj_r, b = ab ? atoi(ab) : p->adj_b;
-        const int key = 100 * r2 + b;
-        if ((r1 != 1 && r1 != 2 && r1 != 4) ||
-            (key != 108 && key != 208 && key != 204 && key != 404 && key != 308 && key != 408 &&
-             key != 304))
-            return fail(GSHT_EINVAL, "unsupported Legendre launch shape syn_r=%d adj_r=%d adj_b=%d",
-                        r1, r2, b);
-        p->syn_r = r1;
-        p->adj_r = r2;
-        p->adj_b = b;
-    }
-    p->syn_nchunk = (p->npairs + 64 * p->syn_r - 1) / (64 * p->syn_r);
-    p->adj_nchunk = (p->npairs + 64 * p->adj_r - 1) / (64 * p->adj_r);
-    if ((rc = dev_alloc(p, &p->leg.lfirst_syn,
-                        sizeof(int32_t) * (size_t)(p->mmax + 1) * p->syn_nchunk)) != GSHT_OK)
-        return rc;
-    if ((rc = dev_alloc(p, &p->leg.lfirst_adj,
-                        sizeof(int32_t) * (size_t)(p->mmax + 1) * p->adj_nchunk)) != GSHT_OK)
-        return rc;
+    p->acc = p->uprep;  // a call is a synthesis or an adjoint: one buffer serves both
+    if ((rc = choose_leg_shapes(p)) != GSHT_OK) return rc;
+    if ((rc = alloc_starts(p)) != GSHT_OK) return rc;
     std::vector<StartInfo> si = make_start_info(p->lmax, p->mmax, p->spin);
     HIP_TRY(hipMemcpyAsync(p->leg.start, si.data(), sizeof(StartInfo) * si.size(),
                            hipMemcpyHostToDevice, s));
     HIP_TRY(launch_leg_tables(*p, s));
-    HIP_TRY(launch_leg_live(*p, s));
+    if (p->leg.band > p->mmax)
+        HIP_TRY(launch_leg_starts(*p, 0, p->mmax + 1, s));
     if (with_deconv) {
         std::vector<double> k1 = deconv_table(p->lmax, p->n1, p->w, p->beta, 1.0 / p->nd);
         std::vector<double> k2 = deconv_table(p->mmax, p->n2, p->w, p->beta, 1.0);
@@ -737,19 +808,24 @@ int plan_create_impl(gsht_plan **out, int lmax, int mmax, int spin, const double
     const size_t gcols = spin ? (size_t)p->n2 : (size_t)p->n2 / 2 + 1;
     // workspace estimate (before allocating anything large)
     int64_t ws = 0;
-    ws += (int64_t)p->nalm * (16 + 8 + 2 * 16 * p->ncomp);   // ab, norm, uprep, acc
+    ws += (int64_t)p->nalm * (16 + 8 + 16 * p->ncomp);   // ab, norm, uprep = acc
     ws += (int64_t)p->ncol * p->nd * cs + (int64_t)p->ncol * p->n1 * cs;
     ws += (int64_t)p->nrows * gcols * cs + (spin ? 0 : (int64_t)p->nrows * p->n2 * rs);
     ws += npts * (16 + 4) + (p->ntiles + 1) * 4;
-    p->workspace_bytes = ws;
-    if (ws > workspace_cap()) {
+    // the ring starts take what the cap leaves, at least 16 ncomp nalm bytes (the cap is
+    // checked with as much for them); under a tighter cap they are kept in bands of m
+    const int64_t least = (int64_t)p->nalm * 16 * p->ncomp;
+    if (ws + least > workspace_cap()) {
+        const int64_t want = ws + least;
         delete p;
         return fail(GSHT_ENOMEM, "workspace of %lld bytes exceeds GSHT_MAX_WORKSPACE_BYTES",
-                    (long long)ws);
+                    (long long)want);
     }
+    p->start_limit = (size_t)std::max<int64_t>(workspace_cap() - ws, 1);
     std::call_once(g_fft_once, []() { rocfft_setup(); });
     tr.mark("sizes");
     if ((rc = setup_legendre(p, s, true)) != GSHT_OK) { free_plan(p); return rc; }
+    p->workspace_bytes = ws + (int64_t)(leg_start_bytes(*p) * (size_t)p->leg.band);
     tr.mark("legendre tables");
     if ((rc = dev_alloc(p, &p->D, (size_t)p->ncol * p->nd * cs)) != GSHT_OK) { free_plan(p); return rc; }
     if ((rc = dev_alloc(p, &p->E, (size_t)p->ncol * p->n1 * cs)) != GSHT_OK) { free_plan(p); return rc; }
@@ -1202,13 +1278,6 @@ int gsht_plan_autotune(gsht_plan *p, void *hip_stream)
     if (!p->D || !p->uprep)
         return fail(GSHT_EINVAL, "plan has no Legendre buffers");
     hipStream_t s = (hipStream_t)hip_stream;
-    const int nck1 = (p->npairs + 63) / 64;  // chunks at one slice per wave (the most)
-    int32_t *ls = nullptr, *la = nullptr;
-    int rc;
-    if ((rc = dev_alloc(p, &ls, sizeof(int32_t) * (size_t)(p->mmax + 1) * nck1)) != GSHT_OK)
-        return rc;
-    if ((rc = dev_alloc(p, &la, sizeof(int32_t) * (size_t)(p->mmax + 1) * nck1)) != GSHT_OK)
-        return rc;
     HIP_TRY(launch_zero(p->uprep, sizeof(double) * 2 * p->ncomp * (size_t)p->nalm, s));
     HIP_TRY(launch_zero(p->D, (size_t)p->ncol * p->nd * csize(p->prec), s));
     hipEvent_t e0, e1;
@@ -1217,16 +1286,7 @@ int gsht_plan_autotune(gsht_plan *p, void *hip_stream)
         (void)hipEventDestroy(e0);
         return fail(GSHT_EHIP, "hipEventCreate failed");
     }
-    auto set_shape = [&](int sr, int ar, int ab) {
-        p->syn_r = sr;
-        p->adj_r = ar;
-        p->adj_b = ab;
-        p->syn_nchunk = (p->npairs + 64 * sr - 1) / (64 * sr);
-        p->adj_nchunk = (p->npairs + 64 * ar - 1) / (64 * ar);
-        p->leg.lfirst_syn = ls;
-        p->leg.lfirst_adj = la;
-        return launch_leg_live(*p, s);
-    };
+    auto set_shape = [&](int sr, int ar, int ab) { set_leg_shapes(p, sr, ar, ab); };
     // best of two runs of one launch, in ms (negative on a launch error)
     auto time_ms = [&](auto launch) {
         float best = -1.0f;
@@ -1245,8 +1305,7 @@ int gsht_plan_autotune(gsht_plan *p, void *hip_stream)
     int best_sr = p->syn_r;
     float best_t = -1.0f;
     for (int sr : {1, 2, 4}) {
-        if (set_shape(sr, ar0, ab0) != hipSuccess)
-            break;
+        set_shape(sr, ar0, ab0);
         const float t = time_ms([&] { return launch_leg_synth(*p, p->D, false, s); });
         if (t >= 0 && (best_t < 0 || t < best_t)) {
             best_t = t;
@@ -1255,10 +1314,9 @@ int gsht_plan_autotune(gsht_plan *p, void *hip_stream)
     }
     int best_ar = ar0, best_ab = ab0;
     best_t = -1.0f;
-    const int shapes[7][2] = {{1, 8}, {2, 8}, {2, 4}, {4, 4}, {3, 8}, {3, 4}, {4, 8}};
+    const int shapes[8][2] = {{1, 8}, {2, 8}, {2, 4}, {4, 4}, {3, 8}, {3, 4}, {4, 8}, {5, 8}};
     for (const auto &sh : shapes) {
-        if (set_shape(best_sr, sh[0], sh[1]) != hipSuccess)
-            break;
+        set_shape(best_sr, sh[0], sh[1]);
         const float t = time_ms([&] { return launch_leg_adjoint(*p, p->D, false, s); });
         if (t >= 0 && (best_t < 0 || t < best_t)) {
             best_t = t;
@@ -1266,8 +1324,8 @@ int gsht_plan_autotune(gsht_plan *p, void *hip_stream)
             best_ab = sh[1];
         }
     }
-    const hipError_t e = set_shape(best_sr, best_ar, best_ab);
-    (void)hipStreamSynchronize(s);
+    set_shape(best_sr, best_ar, best_ab);
+    const hipError_t e = hipStreamSynchronize(s);
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (e != hipSuccess)
@@ -1287,7 +1345,7 @@ static bool use_mfma(const gsht_plan *p)
 }
 
 // Buffers of the matrix-core step, sized for 16 maps: tile offsets per m (16 degrees
-// per block from l0 = max(m, s)), tiles, scales, doubled columns, dead-chunk table.
+// per block from l0 = max(m, s)), tiles, scales, doubled columns.
 static int setup_mfma(gsht_plan *p, hipStream_t s)
 {
     if (p->mfma_tiles)
@@ -1304,11 +1362,8 @@ static int setup_mfma(gsht_plan *p, hipStream_t s)
     const size_t nt = p->spin ? 2 : 1;
     const size_t tile_bytes = (size_t)nblk * nt * 2 /* column blocks */ * 2 /* hi, lo */ * 64 * 16;
     const size_t dstride = (size_t)p->ncol * p->nd;
-    const int nchunk = (p->npairs + 63) / 64;
     if ((rc = dev_alloc(p, &p->mfma_boff, sizeof(int64_t) * boff.size())) != GSHT_OK) return rc;
     if ((rc = dev_alloc(p, &p->mfma_scale, sizeof(float) * 16 * boff.size())) != GSHT_OK) return rc;
-    if ((rc = dev_alloc(p, &p->mfma_live, sizeof(int32_t) * (size_t)nchunk * boff.size())) != GSHT_OK)
-        return rc;
     if ((rc = dev_alloc(p, &p->Dmfma, 16 * dstride * csize(p->prec))) != GSHT_OK) return rc;
     if ((rc = dev_alloc(p, &p->mfma_tiles, tile_bytes)) != GSHT_OK) {
         p->mfma_tiles = nullptr;
@@ -1316,14 +1371,12 @@ static int setup_mfma(gsht_plan *p, hipStream_t s)
     }
     HIP_TRY(hipMemcpyAsync(p->mfma_boff, boff.data(), sizeof(int64_t) * boff.size(),
                            hipMemcpyHostToDevice, s));
-    HIP_TRY(launch_leg_live_r1(*p, p->mfma_live, s));
     HIP_TRY(hipStreamSynchronize(s));
     return GSHT_OK;
 }
 
 // Buffers of the matrix-core adjoint (16 maps): ring-input tiles per (m, slice, 32-ring
-// step), scales, sums; the doubled columns and the dead-chunk table are shared with
-// the matrix-core synthesis.
+// step), scales, sums; the doubled columns are shared with the matrix-core synthesis.
 static int setup_mfma_adj(gsht_plan *p, hipStream_t s)
 {
     int rc;
@@ -1389,7 +1442,7 @@ int gsht_plan_adjoint_many(gsht_plan *p, int nmaps, const void *map, void *alm, 
             RUN(ST_PREP, launch_prep_adj_mfma(*p, nm, p->Dmfma, dstride, p->mfma_atiles,
                                               p->mfma_ascale, s));
             RUN(ST_LEG_ADJ, launch_leg_adjoint_mfma(*p, nm, p->mfma_atiles, p->mfma_ascale,
-                                                    p->mfma_live, p->mfma_rstate, p->mfma_acc, s));
+                                                    p->mfma_rstate, p->mfma_acc, s));
             for (int j = 0; j < nm; ++j) {
                 double *asave = p->acc;
                 p->acc = p->mfma_acc + j * (size_t)p->nalm * nr;
@@ -1434,7 +1487,7 @@ int gsht_plan_synth_many(gsht_plan *p, int nmaps, const void *alm, void *map, vo
             char *mk = (char *)map + (map ? k * mstride : 0);
             RUN(ST_PREP, launch_prep_mfma(*p, ak, nm, p->mfma_boff, p->mfma_tiles, p->mfma_scale, s));
             RUN(ST_LEG_SYNTH, launch_leg_synth_mfma(*p, nm, p->mfma_tiles, p->mfma_scale,
-                                                    p->mfma_boff, p->mfma_live, p->Dmfma, dstride, s));
+                                                    p->mfma_boff, p->Dmfma, dstride, s));
             for (int j = 0; j < nm; ++j) {
                 void *dsave = p->D;
                 p->D = (char *)p->Dmfma + j * dstride * cs;
@@ -1447,9 +1500,7 @@ int gsht_plan_synth_many(gsht_plan *p, int nmaps, const void *alm, void *map, vo
             k += nm;
             continue;
         }
-        int nm = nmaps - k >= 4 ? 4 : (nmaps - k >= 2 ? 2 : 1);
-        if (p->syn_r > 2)
-            nm = 1;
+        const int nm = nmaps - k >= 4 ? 4 : (nmaps - k >= 2 ? 2 : 1);
         const char *ak = (const char *)alm + k * astride;
         char *mk = (char *)map + (map ? k * mstride : 0);
         if (nm == 1) {
@@ -1919,6 +1970,7 @@ int gsht_legendre_rings(const void *alm, int lmax, int mmax, int spin, int nthet
     p->nd = 2 * ntheta - 2;
     p->ncol = spin ? 2 * mmax + 1 : mmax + 1;
     p->npairs = (ntheta + 1) / 2;
+    p->start_limit = kStageStartLimit;
     if ((rc = setup_legendre(p, s, false)) != GSHT_OK) { free_plan(p); return rc; }
     int rc2 = check_launch(launch_prep_alm(*p, alm, 1.0, false, s), "prep_alm");
     if (rc2 == GSHT_OK)
@@ -2019,6 +2071,7 @@ int gsht_analysis_minimal(const void *map, int lmax, int mmax, int spin, int nph
     p->nd = nd;
     p->ncol = ncol;
     p->npairs = (ntheta + 1) / 2;
+    p->start_limit = kStageStartLimit;
     if ((rc = setup_legendre(p, s, false)) != GSHT_OK) {
         free_plan(p);
         cleanup();
@@ -2057,6 +2110,7 @@ int gsht_legendre_rings_adjoint(const void *F, int lmax, int mmax, int spin, int
     p->nd = 2 * ntheta - 2;
     p->ncol = spin ? 2 * mmax + 1 : mmax + 1;
     p->npairs = (ntheta + 1) / 2;
+    p->start_limit = kStageStartLimit;
     if ((rc = setup_legendre(p, s, false)) != GSHT_OK) { free_plan(p); return rc; }
     int rc2 = check_launch(launch_leg_adjoint(*p, F, false, s), "legendre_adjoint");
     if (rc2 == GSHT_OK)
@@ -2089,19 +2143,21 @@ int gsht_legendre_rings_adjoint_noalloc(const void *F, int lmax, int mmax, int s
     p.nd = 2 * ntheta - 2;
     p.ncol = spin ? 2 * mmax + 1 : mmax + 1;
     p.npairs = (ntheta + 1) / 2;
-    p.adj_nchunk = (p.npairs + 64 * p.adj_r - 1) / (64 * p.adj_r);
-    p.syn_nchunk = (p.npairs + 64 * p.syn_r - 1) / (64 * p.syn_r);
     auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
+    // (the limit counts both recurrence coefficients for spin 0 too, and a table per 192
+    // ring pairs that earlier forms of the kernel took)
     const size_t b_ab = up(sizeof(double2) * (size_t)p.nalm);
     const size_t b_norm = up(sizeof(double) * (size_t)p.nalm);
     const size_t b_acc = up(sizeof(double) * 2 * p.ncomp * (size_t)p.nalm);
     const size_t b_start = up(sizeof(StartInfo) * (size_t)(mmax + 1));
-    const size_t b_live = up(sizeof(int32_t) * (size_t)(mmax + 1) * p.adj_nchunk);
-    const size_t need = b_ab + b_norm + b_acc + b_start + b_live;
+    const size_t reserve = up(sizeof(int32_t) * (size_t)(mmax + 1) * ((p.npairs + 191) / 192));
+    const size_t need = b_ab + b_norm + b_acc + b_start + reserve;
     if (need > kScratchBytes)
         return fail(GSHT_EINVAL, "lmax %d, mmax %d, spin %d, ntheta %d need %zu bytes of device "
                                  "scratch; the allocation-free entry point holds %zu",
                     lmax, mmax, spin, ntheta, need, kScratchBytes);
+    if ((rc = choose_leg_shapes(&p)) != GSHT_OK)
+        return rc;
     hipStream_t s = (hipStream_t)hip_stream;
     int dev = 0;
     HIP_TRY(hipGetDevice(&dev));
@@ -2110,22 +2166,24 @@ int gsht_legendre_rings_adjoint_noalloc(const void *F, int lmax, int mmax, int s
     if ((rc = scratch_address(dev, &base)) != GSHT_OK)
         return rc;
     char *q = (char *)base;
-    p.leg.ab = (double2 *)q;
+    p.leg.ab = (double *)q;
     q += b_ab;
     p.leg.norm = (double *)q;
     q += b_norm;
     p.acc = (double *)q;
     q += b_acc;
     p.leg.start = (StartInfo *)q;
-    q += b_start;
-    p.leg.lfirst_adj = (int32_t *)q;
+    p.leg.np = (p.npairs + 63) / 64 * 64;
+    place_starts(&p, (char *)base + kScratchBytes,
+                 (int)std::min<size_t>((size_t)mmax + 1, kStartScratchBytes / leg_start_bytes(p)));
     // start data: computed on the host, sent from a host copy kept until the next call
     g_scratch_start[dev] = make_start_info(lmax, mmax, spin);
     HIP_TRY(hipMemcpyAsync(p.leg.start, g_scratch_start[dev].data(),
                            sizeof(StartInfo) * (size_t)(mmax + 1), hipMemcpyHostToDevice, s));
     rc = check_launch(launch_leg_tables(p, s), "legendre tables");
     if (rc == GSHT_OK)
-        rc = check_launch(launch_leg_live_adj(p, s), "live-chunk table");
+        rc = check_launch(p.leg.band > mmax ? launch_leg_starts(p, 0, mmax + 1, s) : hipSuccess,
+                          "ring starts");
     if (rc == GSHT_OK)
         rc = check_launch(launch_leg_adjoint(p, F, false, s), "legendre_adjoint");
     if (rc == GSHT_OK)

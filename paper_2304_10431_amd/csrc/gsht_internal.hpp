@@ -28,11 +28,27 @@ struct StartInfo {
 // Device tables of the normalised recurrence p_{l+1} = (a_l x + sigma b_l) p_l - p_{l-1},
 // p_l = sY_lm / N_l (identical a_l, b_l, N_l for both channels).
 struct LegendreTables {
-    double2 *ab = nullptr;     // [nalm]  (a_l, b_l) at idx(l, m), valid for l0 <= l < lmax
+    double *ab = nullptr;      // [nalm] (a_l, b_l) at idx(l, m), valid for l0 <= l < lmax;
+                               // spin 0: [nalm] a_l (b_l = 0)
     double *norm = nullptr;    // [nalm]  N_l
     StartInfo *start = nullptr;  // [mmax + 1]
-    int32_t *lfirst_syn = nullptr;  // [(mmax + 1) * syn_nchunk] first degree a chunk can matter at
-    int32_t *lfirst_adj = nullptr;  // [(mmax + 1) * adj_nchunk] same for the adjoint's chunks
+    // recurrence starts of every ring pair for a band of m (leg_starts_kernel): all m
+    // when they fit, otherwise rebuilt band by band within each Legendre launch
+    double2 *sta = nullptr;    // [band][np] (p_{l-1}, p_l) of channel +s at its entry degree
+    double2 *stb = nullptr;    // [band][np] channel -s (spin > 0)
+    int32_t *stk = nullptr;    // [band][np] entry blocks, channel +s low half, -s high half
+    int np = 0;                // ring pairs, rounded up to whole waves
+    int band = 0;              // values of m the buffers hold
+};
+
+// Entry block of a channel that stays below the threshold up to lmax.
+constexpr int START_NEVER = 0x7fff;
+
+// The starts of m0 <= m < m0 + band, as the kernels take them.
+struct RingStarts {
+    const double2 *a, *b;
+    const int32_t *k;
+    int m0, np;
 };
 
 // One in-LDS FFT of length n (per-column stage): decimation-in-frequency passes of
@@ -127,12 +143,13 @@ struct gsht_plan {
     int tile_req = 0;      // requested tile edge (0: the default 32)
     int64_t ntiles = 0, nchunks = 0;
     int ncol = 0, npairs = 0;
-    int syn_r = 2;       // ring pairs per lane, Legendre synthesis (slices of 64)
-    int adj_r = 3;       // ring pairs per lane, Legendre adjoint
+    int syn_r = 1;       // ring pairs per lane, Legendre synthesis (slices of 64)
+    int adj_r = 1;       // ring pairs per lane, Legendre adjoint
     int adj_b = 8;       // degrees per reduction block of the adjoint
     int syn_nchunk = 0;  // chunks of 64 * syn_r ring pairs
     int adj_nchunk = 0;  // chunks of 64 * adj_r ring pairs
     int64_t workspace_bytes = 0;
+    size_t start_limit = 0;  // bytes the ring starts may take (0: no limit)
     // device tables
     gsht::LegendreTables leg;
     double *uprep = nullptr;   // prepared coefficients [nalm][2 or 4]
@@ -152,7 +169,7 @@ struct gsht_plan {
     void *E = nullptr;     // [ncol][n1] complex
     void *G = nullptr;     // complex grid [nrows][n2] (spin > 0) or half spectrum [nrows][n2/2+1]
     void *g = nullptr;     // real grid [nrows][n2] (spin 0 only)
-    double *acc = nullptr; // adjoint accumulators [nalm][2 * ncomp]
+    double *acc = nullptr; // adjoint accumulators [nalm][2 * ncomp] (the uprep buffer)
     double *umulti = nullptr;  // several-map coefficients [nalm][4][2 or 4] (on first use)
     void *Dmulti = nullptr;    // several-map doubled columns [4][ncol][nd] (on first use)
     // matrix-core synthesis of up to 16 maps (FP32 plans, on first use)
@@ -160,7 +177,6 @@ struct gsht_plan {
     void *mfma_tiles = nullptr;    // FP16 coefficient tiles (16 maps)
     int64_t *mfma_boff = nullptr;  // [mmax + 1] first tile block of each m
     float *mfma_scale = nullptr;   // [mmax + 1][16] output scales
-    int32_t *mfma_live = nullptr;  // dead-chunk table for slices of 64 ring pairs
     void *mfma_atiles = nullptr;   // FP16 ring-input tiles of the matrix-core adjoint
     float *mfma_ascale = nullptr;  // [mmax + 1][16] their output scales
     double *mfma_acc = nullptr;    // [16][nalm][2 ncomp] adjoint sums of the group
@@ -191,8 +207,13 @@ namespace gsht {
 
 // ---- Legendre step (legendre.hip) ------------------------------------------
 hipError_t launch_leg_tables(const gsht_plan &p, hipStream_t s);
-hipError_t launch_leg_live(const gsht_plan &p, hipStream_t s);
-hipError_t launch_leg_live_adj(const gsht_plan &p, hipStream_t s);  // adjoint's table only
+// ring starts of the m values m0 .. m0 + nm - 1 into the plan's buffers
+hipError_t launch_leg_starts(const gsht_plan &p, int m0, int nm, hipStream_t s);
+size_t leg_start_bytes(const gsht_plan &p);  // bytes of the starts of one m
+// Runs f(starts, nm) over the plan's bands of m, rebuilding the starts of each band
+// first where the buffers do not hold all of them.
+template <typename F>
+hipError_t leg_bands(const gsht_plan &p, hipStream_t s, F f);
 // mscale multiplies the coefficients (prep) or results (finalize) of every m > 0:
 // 1 for the transforms, 1/2 or 2 for the weights w_m of their derivatives.
 // grad: gradient-only spin s (C = 0 on input; only G on output).
@@ -203,15 +224,13 @@ hipError_t launch_leg_synth(const gsht_plan &p, void *Dout, bool grad, hipStream
 hipError_t launch_prep_multi(const gsht_plan &p, const void *alm, int nm, double *u, hipStream_t s);
 hipError_t launch_leg_synth_multi(const gsht_plan &p, int nm, const double *u, void *Dout,
                                   size_t dstride, hipStream_t s);
-// matrix-core synthesis of nm <= 16 maps (FP32 plans): coefficient tiles and scales,
-// the dead-chunk table of its 64-pair chunks, and the Legendre step itself
+// matrix-core synthesis of nm <= 16 maps (FP32 plans): coefficient tiles and scales
+// and the Legendre step itself
 hipError_t launch_prep_mfma(const gsht_plan &p, const void *alm, int nm, const int64_t *boff,
                             void *tiles, float *oscale, hipStream_t s);
-hipError_t launch_leg_live_r1(const gsht_plan &p, int32_t *lfirst1, hipStream_t s);
 hipError_t launch_leg_synth_mfma(const gsht_plan &p, int nm, const void *tiles,
-                                 const float *oscale, const int64_t *boff,
-                                 const int32_t *lfirst1, void *Dout, size_t dstride,
-                                 hipStream_t s);
+                                 const float *oscale, const int64_t *boff, void *Dout,
+                                 size_t dstride, hipStream_t s);
 // matrix-core adjoint of nm <= 16 maps (FP32 plans) from their doubled columns
 // (map k at Din + k dstride): ring-input tiles, then the sums into accm [nm][nalm][NR]
 void adj_mfma_shape(const gsht_plan &p, int &S, int &W);  // W = 0: not possible
@@ -219,8 +238,8 @@ size_t adj_mfma_state_bytes(const gsht_plan &p);          // recurrence state bu
 hipError_t launch_prep_adj_mfma(const gsht_plan &p, int nm, const void *Din, size_t dstride,
                                 void *tiles, float *oscale, hipStream_t s);
 hipError_t launch_leg_adjoint_mfma(const gsht_plan &p, int nm, const void *tiles,
-                                   const float *oscale, const int32_t *lfirst1, void *rstate,
-                                   double *accm, hipStream_t s);
+                                   const float *oscale, void *rstate, double *accm,
+                                   hipStream_t s);
 hipError_t launch_leg_adjoint(const gsht_plan &p, const void *Din, bool grad, hipStream_t s);
 hipError_t launch_leg_finalize(const gsht_plan &p, void *alm, double mscale, bool grad,
                                hipStream_t s);
@@ -283,5 +302,20 @@ hipError_t launch_magnification(const void *alpha, const void *kappa, const void
 hipError_t launch_interp_deriv(const gsht_plan &p, void *out_map, void *dth, void *dph,
                               const void *gin, double *gth, double *gph, hipStream_t s);
 hipError_t launch_spread(const gsht_plan &p, const void *map, hipStream_t s);
+
+template <typename F>
+hipError_t leg_bands(const gsht_plan &p, hipStream_t s, F f)
+{
+    for (int m0 = 0; m0 <= p.mmax; m0 += p.leg.band) {
+        const int nm = p.mmax + 1 - m0 < p.leg.band ? p.mmax + 1 - m0 : p.leg.band;
+        if (p.leg.band <= p.mmax) {
+            const hipError_t e = launch_leg_starts(p, m0, nm, s);
+            if (e != hipSuccess)
+                return e;
+        }
+        f(RingStarts{p.leg.sta, p.leg.stb, p.leg.stk, m0, p.leg.np}, nm);
+    }
+    return hipGetLastError();
+}
 
 }  // namespace gsht

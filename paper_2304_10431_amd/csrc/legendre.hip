@@ -10,9 +10,8 @@
 // column -m of a spin-s field through sY_{l,-m} = (-1)^(s+m) (-s)Y_lm.
 //
 // The start value at l0 = max(m, s) is a single half-angle power term that can
-// be far below the double range; each channel carries a binary exponent offset
-// (a non-positive multiple of 512) until its value has grown into range, and
-// contributes nothing before that (such terms are below 2^-256 relative).
+// be far below the double range; a channel enters the sums at the degree where its value
+// has grown to 2^-100 (legendre_kernels.hip).
 #include "gsht_internal.hpp"
 
 #include <cmath>
@@ -118,7 +117,7 @@ std::vector<StartInfo> make_start_info(int lmax, int mmax, int spin)
 // ---- device: recurrence tables ---------------------------------------------
 
 // One thread per m: a_l, b_l and N_l for l0 <= l <= lmax (zeros below l0).
-__global__ void leg_tables_kernel(int lmax, int mmax, int s, double2 *__restrict__ ab,
+__global__ void leg_tables_kernel(int lmax, int mmax, int s, double *__restrict__ ab,
                                   double *__restrict__ norm)
 {
     const int m = blockIdx.x * blockDim.x + threadIdx.x;
@@ -126,8 +125,14 @@ __global__ void leg_tables_kernel(int lmax, int mmax, int s, double2 *__restrict
         return;
     const int64_t base = (int64_t)m * (2 * lmax + 1 - m) / 2;
     const int l0 = m > s ? m : s;
+    auto put = [&](int l, double a, double b) {
+        if (s)
+            reinterpret_cast<double2 *>(ab)[base + l] = make_double2(a, b);
+        else
+            ab[base + l] = a;
+    };
     for (int l = m; l < l0 && l <= lmax; ++l) {
-        ab[base + l] = make_double2(0.0, 0.0);
+        put(l, 0.0, 0.0);
         norm[base + l] = 0.0;
     }
     if (l0 > lmax)
@@ -150,12 +155,12 @@ __global__ void leg_tables_kernel(int lmax, int mmax, int s, double2 *__restrict
         }
         const double a = ap * ncur / nnext;
         const double b = (l == 0) ? 0.0 : a * (double)m * (double)s / (L * (L + 1));
-        ab[base + l] = make_double2(a, b);
+        put(l, a, b);
         norm[base + l + 1] = nnext;
         nprev = ncur;
         ncur = nnext;
     }
-    ab[base + lmax] = make_double2(0.0, 0.0);
+    put(lmax, 0.0, 0.0);
 }
 
 hipError_t launch_leg_tables(const gsht_plan &p, hipStream_t s)
@@ -403,8 +408,15 @@ __global__ void leg_finalize_kernel(const double *__restrict__ acc, const double
     if (l > lmax)
         return;
     const int64_t i = (int64_t)m * (2 * lmax + 1 - m) / 2 + l;
-    const double n = (l < s) ? 0.0 : (m > 0 ? mscale : 1.0) * norm[i];
     TC o;
+    if (l < s) {  // no such harmonic: the sums of these entries may never have been written
+        o.x = o.y = 0;
+        alm[i] = o;
+        if (!grad)
+            alm[nalm + i] = o;
+        return;
+    }
+    const double n = (m > 0 ? mscale : 1.0) * norm[i];
     if (grad) {  // gradient-only: acc holds S+ + (-1)^s S-, G = -(that) / 2
         o.x = -0.5 * n * acc[2 * i];
         o.y = (m == 0) ? 0.0 : -0.5 * n * acc[2 * i + 1];

@@ -66,32 +66,6 @@ __device__ inline XD start_value(double mant, int ex0, int a, int b, double sh, 
     return v;
 }
 
-constexpr double TWO_P256 = 0x1p256;
-constexpr double TWO_M512 = 0x1p-512;
-// In-range thresholds 2^INX: values from there up are held unscaled (normal
-// doubles; in the decaying region the recurrence only grows them).  The synthesis
-// takes 2^-900, which ends its masked phase early; the adjoint takes 2^-256, which
-// spares it the lane reductions of blocks that hold only negligible terms.
-constexpr int SYN_IN_EXP = -900;
-constexpr int ADJ_IN_EXP = -256;
-
-// true value = p 2^ex, ex a non-positive multiple of 512, ex == 0 <=> in range.
-template <int INX>
-__device__ inline void to_scaled(const XD &v, double &p, int &ex)
-{
-    if (v.m == 0.0) {
-        p = 0.0;
-        ex = 0;
-    } else if (v.e >= INX + 1) {
-        p = ldexp(v.m, v.e);
-        ex = 0;
-    } else {
-        const int t = v.e + 256;              // < 0
-        ex = 512 * (-((-t + 511) / 512));     // 512 floor(t / 512)
-        p = ldexp(v.m, v.e - ex);
-    }
-}
-
 __device__ inline void ring_geom(int q, int ntheta, double &x, double &sh, double &ch)
 {
     const double t = (double)q / (double)(ntheta - 1);
@@ -108,52 +82,145 @@ __device__ inline void ring_geom(int q, int ntheta, double &x, double &sh, doubl
 // and the m values are dealt to the XCDs round-robin, largest work first on each.
 constexpr int NXCD = 8;
 
-__device__ inline void xcd_map(int nchunk, int &m, int &chunk)
+__device__ inline void xcd_map(int m0, int nchunk, int &m, int &chunk)
 {
     const int x = blockIdx.x % NXCD, k = blockIdx.x / NXCD;
     const int g = k / nchunk;
     chunk = k - g * nchunk;
-    m = x + NXCD * g;
+    m = m0 + x + NXCD * g;
 }
 
-inline unsigned xcd_grid(int mmax, int nchunk)
+// Workgroups for a band of nm values of m.
+inline unsigned xcd_grid(int nm, int nchunk)
 {
-    return (unsigned)(NXCD * ((mmax + NXCD) / NXCD) * nchunk);
+    return (unsigned)(NXCD * ((nm + NXCD - 1) / NXCD) * nchunk);
 }
 
 // ---- per-ring recurrence state ------------------------------------------------------
 
+// Ring pairs are counted from the equator: position e is the pair q = npairs - 1 - e.
+// A wave's chunk of 64 R consecutive positions then holds rings that enter the sums at
+// similar degrees, and the one partly filled chunk of an m lies at the pole, where the
+// sums are shortest (counted from the pole it lay at the equator and ran all degrees).
 struct Ring {
     double x;
     double a0, a1, b0, b1;  // p_{l-1}, p_l of channels +s and -s
-    int ea, eb;             // exponent offsets
 };
 
-template <int INX>
-__device__ inline Ring ring_init(const StartInfo &si, int q, int ntheta, bool active, bool spin)
+// Start of one ring pair's recurrences (see leg_starts_kernel): k is the 8-degree block,
+// counted from l0, at which a channel enters; before it the channel's values are 0.
+constexpr int START_DEG = 8;  // degrees per entry block
+
+struct RingStart {
+    int ka, kb;
+};
+
+__device__ inline RingStart ring_start(const RingStarts &t, int m, int e, bool spin)
 {
-    Ring r;
-    double sh, ch;
-    ring_geom(active ? q : 0, ntheta, r.x, sh, ch);
-    r.a0 = r.b0 = 0.0;
-    to_scaled<INX>(start_value(si.mant_p, si.ex_p, si.a_p, si.b_p, sh, ch), r.a1, r.ea);
-    if (spin)
-        to_scaled<INX>(start_value(si.mant_m, si.ex_m, si.a_m, si.b_m, sh, ch), r.b1, r.eb);
-    else {
-        r.b1 = 0.0;
-        r.eb = 0;
+    const unsigned k = (unsigned)t.k[(size_t)(m - t.m0) * t.np + e];
+    return RingStart{(int)(k & 0xffffu), spin ? (int)(k >> 16) : START_NEVER};
+}
+
+// first[r]: the smallest entry block among a wave's slices r, r + 1, ... (slices nearer
+// the pole enter later, so normally that of slice r); kmax: the largest entry block below
+// START_NEVER (-1: none).
+template <int R>
+__device__ inline void wave_start_range(const RingStart (&rs)[R], int (&first)[R], int &kmax)
+{
+    int hi = -1;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        first[r] = min(rs[r].ka, rs[r].kb);
+        hi = max(hi, rs[r].ka < START_NEVER ? rs[r].ka : -1);
+        hi = max(hi, rs[r].kb < START_NEVER ? rs[r].kb : -1);
     }
-    if (!active) {
-        r.a1 = r.b1 = 0.0;
-        r.ea = r.eb = 0;
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            first[r] = min(first[r], __shfl_xor(first[r], d, 64));
+        hi = max(hi, __shfl_xor(hi, d, 64));
     }
-    return r;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        first[r] = __builtin_amdgcn_readfirstlane(first[r]);
+#pragma unroll
+    for (int r = R - 2; r >= 0; --r)
+        first[r] = min(first[r], first[r + 1]);
+    kmax = __builtin_amdgcn_readfirstlane(hi);
+}
+
+__device__ inline double ring_x(int q, int ntheta)
+{
+    return cospi((double)q / (double)(ntheta - 1));
+}
+
+// Enter the channels whose block is k.
+template <bool SPIN>
+__device__ inline void ring_enter(Ring &r, const RingStart &rs, int k, const double2 &va,
+                                  const double2 &vb)
+{
+    if (rs.ka == k) {
+        r.a0 = va.x;
+        r.a1 = va.y;
+    }
+    if (SPIN && rs.kb == k) {
+        r.b0 = vb.x;
+        r.b1 = vb.y;
+    }
+}
+
+// Recurrence coefficients (a_l, b_l) at coefficient index i: interleaved for spin > 0;
+// spin 0 has b_l = 0 and keeps a_l alone, which halves that scalar stream.
+template <bool SPIN>
+__device__ inline double2 rec_coef(const double *__restrict__ ab, int64_t i)
+{
+    if constexpr (SPIN)
+        return *reinterpret_cast<const double2 *>(ab + 2 * i);
+    else
+        return make_double2(ab[i], 0.0);
+}
+
+// Sets the recurrence state of a wave's rings to "not entered" and loads their entry
+// blocks; the entry values wait in LDS (each lane reads back its own).
+template <bool SPIN, int R>
+__device__ inline void rings_init(Ring (&rg)[R], RingStart (&rs)[R], double2 (&ent)[R][SPIN ? 2 : 1][64],
+                                  const RingStarts &tab, int m, int e0, int ntheta, int npairs,
+                                  bool live, int (&first)[R], int &kmax)
+{
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int e = e0 + 64 * r + lane;
+        const bool in = live && e < npairs;
+        rs[r] = in ? ring_start(tab, m, e, SPIN) : RingStart{START_NEVER, START_NEVER};
+        rg[r].x = ring_x(in ? npairs - 1 - e : 0, ntheta);
+        rg[r].a0 = rg[r].a1 = rg[r].b0 = rg[r].b1 = 0.0;
+        const size_t idx = (size_t)(m - tab.m0) * tab.np + e;
+        if (rs[r].ka < START_NEVER)
+            ent[r][0][lane] = tab.a[idx];
+        if (SPIN && rs[r].kb < START_NEVER)
+            ent[r][1][lane] = tab.b[idx];
+    }
+    wave_start_range(rs, first, kmax);
+}
+
+// Enters the channels whose block is k (a wave-uniform test first: most blocks have none).
+template <bool SPIN, int NR, int R>
+__device__ inline void rings_enter(Ring (&rg)[R], const RingStart (&rs)[R],
+                                   const double2 (&ent)[R][SPIN ? 2 : 1][64], int k)
+{
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+        if (__any(rs[r].ka == k || (SPIN && rs[r].kb == k)))
+            ring_enter<SPIN>(rg[r], rs[r], k, ent[r][0][lane], ent[r][SPIN ? 1 : 0][lane]);
 }
 
 template <bool SPIN>
 __device__ inline void ring_advance(Ring &r, double a, double b)
 {
-    const double ta = fma(a, r.x, b);
+    const double ta = SPIN ? fma(a, r.x, b) : a * r.x;
     const double na = fma(ta, r.a1, -r.a0);
     r.a0 = r.a1;
     r.a1 = na;
@@ -165,71 +232,31 @@ __device__ inline void ring_advance(Ring &r, double a, double b)
     }
 }
 
-// A scaled channel whose true value p 2^e has reached 2^INX is folded to e = 0;
-// otherwise it is rescaled by 2^-512 once |p| reaches 2^256.  Selects only, no
-// lane-divergent branch (the matrix-core kernels schedule their products among the
-// recurrence steps; the vector kernels run the same code, at equal speed and bits).
-// A fold happens only at e = -512 or -1024 (values reach at most 2^288 before the
-// next check), where 2^e is still a double, so the product by it is exact like ldexp.
-template <int INX>
-__device__ inline void rescale_channel(double &p0, double &p1, int &e)
+// Pulls the coefficient stream of one m into the XCD's L2 ahead of the scalar loads,
+// which otherwise wait for HBM about once per pair of degrees (all chunks of an m run
+// close together, so none of them finds the line already there).  One lane per touched
+// line; W doubles per degree, PF_DEG degrees per call.  The value is dropped: the empty
+// asm only keeps the load, and names it as an input one call later.
+constexpr int PF_DEG = 256;
+
+template <int W>
+__device__ inline float stream_touch(const double *p, int64_t base, int l, int lmax)
 {
-    const bool neg = e < 0;
-    const bool fold = neg && fabs(p1) >= ldexp(1.0, INX - e);
-    const bool down = neg && !fold && fabs(p1) >= TWO_P256;
-    const double f = fold ? ldexp(1.0, e) : (down ? TWO_M512 : 1.0);
-    p0 *= f;
-    p1 *= f;
-    e = fold ? 0 : (down ? e + 512 : e);
+    const int lane = threadIdx.x & 63;
+    const int ll = min(l + lane * (PF_DEG / 64), lmax);
+    return *reinterpret_cast<const float *>(p + W * (base + ll));
 }
 
-template <bool SPIN, int INX>
-__device__ inline void ring_rescale(Ring &r)
-{
-    rescale_channel<INX>(r.a0, r.a1, r.ea);
-    if (SPIN)
-        rescale_channel<INX>(r.b0, r.b1, r.eb);
-}
+template <int N>
+using count = std::integral_constant<int, N>;
 
-// Wave-uniform slice state: 0 = no lane in range, 1 = some, 2 = all.
-template <bool SPIN>
-__device__ inline int slice_phase(const Ring &r)
+// f(count<1>()), ..., f(count<N>()) in order.
+template <int N, typename F>
+__device__ inline void for_counts(F &&f)
 {
-    const bool in = (r.ea == 0) && (!SPIN || r.eb == 0);
-    const bool some = (r.ea == 0 && r.a1 != 0.0) || (SPIN && r.eb == 0 && r.b1 != 0.0);
-    if (__all(in))
-        return 2;
-    return __any(some) ? 1 : 0;
-}
-
-// Silent blocks: while no lane of the wave holds a channel in range every term would
-// get the weight 0, so only the recurrence runs (no sums, no reductions), with the
-// rescaling and the slice phases after every 8 degrees (the longest interval between
-// checks the growth bound of the rescaling allows).  ab_m points at the
-// degree-indexed coefficients of the wave's m; lb advances.
-template <bool SPIN, int INX, int R>
-__device__ inline void silent_blocks(Ring (&rg)[R], const double2 *ab_m, int &lb, int lmax,
-                                     bool &all_in, bool &some_in)
-{
-    for (; lb + 7 <= lmax && !some_in; lb += 8) {
-        const double2 *abl = ab_m + lb;
-#pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            const double2 cc = abl[b];
-#pragma unroll
-            for (int r = 0; r < R; ++r)
-                ring_advance<SPIN>(rg[r], cc.x, cc.y);
-        }
-        all_in = true;
-        some_in = false;
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            ring_rescale<SPIN, INX>(rg[r]);
-            const int p = slice_phase<SPIN>(rg[r]);
-            all_in = all_in && p == 2;
-            some_in = some_in || p != 0;
-        }
-    }
+    if constexpr (N > 1)
+        for_counts<N - 1>(f);
+    f(count<N>());
 }
 
 template <bool B>

@@ -10,129 +10,153 @@
 // north recurrence through sY_lm(pi - theta) = (-1)^(l+m) (-s)Y_lm(theta), and the
 // column -m of a spin-s field through sY_{l,-m} = (-1)^(s+m) (-s)Y_lm.
 //
-// Start values at l0 = max(m, s) can lie far below the double range: each channel
-// carries an exponent offset e (a non-positive multiple of 512), the true value
-// being p 2^e, and contributes only while e = 0.  A channel reaches e = 0 once its
-// true value passes 2^-900 (synthesis) or 2^-256 (adjoint), checked at block ends,
-// so terms smaller than that, relative to the O(1) values of the oscillating
-// region, are dropped.
+// Start values at l0 = max(m, s) can lie far below the double range, and on each ring
+// the values stay negligible until l sin(theta) comes near m.  A table holds, for every
+// (m, ring pair), the 8-degree block at which each channel first reaches 2^-100 and its
+// two recurrence values there; the kernels start each wave at the first such block of
+// its rings, keep a lane's values at 0 until its own block, and then simply set them.
+// Terms below 2^-100, against values of order 1 in the oscillating region, are thus
+// dropped, 47 bits below the rounding of the sums they would enter.
 //
-// Work decomposition: one wave per (m, chunk); a chunk is R slices of 64
-// consecutive ring pairs, lane L of slice r owning pair 64 (R chunk + r) + L.
-// Degrees advance in blocks of 8; offsets change only at block ends.  A block runs
-// "masked" (out-of-range channels excluded for the whole block, rescaling and
-// phase update at its end) until every lane of the wave is in range; from then on
-// blocks run without masks or checks, and only a final partial block checks the
-// degree bound.  Chunks whose most equatorial ring stays below 2^-900 up to lmax
-// are skipped outright.
+// Work decomposition: one wave per (m, chunk); a chunk is R slices of 64 consecutive
+// ring pairs counted from the equator, lane L of slice r owning position 64 (R chunk +
+// r) + L.  Degrees advance in blocks of 8 without masks or scaling, and only a final
+// partial block checks the degree bound.
 #include "legendre_device.hpp"
 
 namespace gsht {
 
-// ---- live-chunk table -------------------------------------------------------------
+// ---- recurrence starts ----------------------------------------------------------------
 
-// For each (m, chunk): the first degree at which the chunk's most equatorial ring
-// reaches 2^THR in either channel (lmax + 1 if never).  The other rings of the
-// chunk are smaller there, so a chunk whose entry exceeds lmax has nothing at or
-// above 2^THR and is skipped.  THR is the kernel's in-range threshold: the synthesis
-// takes 2^-900 and the adjoint 2^-256, below which it adds nothing (a channel
-// contributes only once its value has reached that threshold), so skipping such a
-// chunk leaves the results unchanged.
-template <bool SPIN>
-__global__ void leg_live_kernel(const double2 *__restrict__ ab, const StartInfo *__restrict__ st,
-                                int lmax, int mmax, int ntheta, int npairs, int chunk_pairs,
-                                int nchunk, int thr, int32_t *__restrict__ lfirst)
+// A channel enters at the first multiple of START_DEG degrees above l0 at which its
+// value has reached 2^START_EXP.  At lmax 4096 (spin 2) 77 % of the (m, l, ring) volume
+// in waves of 128 rings lies past the entry; a threshold of 2^-256 would make it 81 %,
+// 2^-900 90 %, 2^-64 76 %.
+constexpr int START_EXP = -100;
+
+// true value = p 2^ex; ex == 0 <=> at least 2^START_EXP, otherwise ex <= -512 is a
+// multiple of 512.
+__device__ inline void to_scaled(const XD &v, double &p, int &ex)
 {
-    const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= (int64_t)(mmax + 1) * nchunk)
+    if (v.m == 0.0) {
+        p = 0.0;
+        ex = -512;
+    } else if (v.e >= START_EXP + 1) {
+        p = ldexp(v.m, v.e);
+        ex = 0;
+    } else {
+        const int t = v.e + 256;
+        ex = t < 0 ? 512 * (-((-t + 511) / 512)) : -512;
+        p = ldexp(v.m, v.e - ex);
+    }
+}
+
+// Fold to ex = 0 once |p| 2^ex >= 2^START_EXP; step the offset when |p| has grown past
+// 2^256 (START_DEG degrees multiply it by less than 2^32, so |p| stays below 2^444).
+__device__ inline void rescale_channel(double &p0, double &p1, int &ex)
+{
+    if (ex == 0)
         return;
-    const int m = (int)(id / nchunk), c = (int)(id - (int64_t)(id / nchunk) * nchunk);
+    if (fabs(p1) >= ldexp(1.0, ex < -1024 ? 1023 : START_EXP - ex)) {
+        p0 = ldexp(p0, ex);
+        p1 = ldexp(p1, ex);
+        ex = 0;
+    } else if (ex < -512 && fabs(p1) >= 0x1p256) {
+        p0 *= 0x1p-512;
+        p1 *= 0x1p-512;
+        ex += 512;
+    }
+}
+
+// One lane per (m, ring pair), the pair's position counted from the equator.  Runs the
+// recurrence with exponent offsets through the degrees where the values are negligible;
+// done once per plan (or per band of m), 2 ms at lmax 4096.
+template <bool SPIN>
+__global__ __launch_bounds__(64) void leg_starts_kernel(
+    const double *__restrict__ ab, const StartInfo *__restrict__ st, int lmax, int m0, int ntheta,
+    int npairs, int np, double2 *__restrict__ sta, double2 *__restrict__ stb,
+    int32_t *__restrict__ stk)
+{
+    const int m = m0 + blockIdx.y, e = blockIdx.x * 64 + threadIdx.x;
     const StartInfo si = st[m];
     const int l0 = si.l0;
-    if (l0 > lmax) {
-        lfirst[id] = lmax + 1;
-        return;
-    }
-    int q = c * chunk_pairs + chunk_pairs - 1;
-    if (q > npairs - 1)
-        q = npairs - 1;
+    const bool valid = e < npairs && l0 <= lmax;
     double x, sh, ch;
-    ring_geom(q, ntheta, x, sh, ch);
-    const XD va = start_value(si.mant_p, si.ex_p, si.a_p, si.b_p, sh, ch);
-    const XD vb = SPIN ? start_value(si.mant_m, si.ex_m, si.a_m, si.b_m, sh, ch) : XD{0.0, 0};
-    double a0 = 0, a1 = va.m, b0 = 0, b1 = vb.m;
-    int ea = va.e, eb = vb.e;
+    ring_geom(valid ? npairs - 1 - e : 0, ntheta, x, sh, ch);
+    double a0 = 0.0, a1 = 0.0, b0 = 0.0, b1 = 0.0;
+    int ea = -512, eb = -512;
+    if (valid) {
+        to_scaled(start_value(si.mant_p, si.ex_p, si.a_p, si.b_p, sh, ch), a1, ea);
+        if (SPIN)
+            to_scaled(start_value(si.mant_m, si.ex_m, si.a_m, si.b_m, sh, ch), b1, eb);
+    }
+    const size_t idx = (size_t)blockIdx.y * np + e;
+    int ka = START_NEVER, kb = START_NEVER;
+    double2 va = make_double2(0.0, 0.0), vb = va;
+    bool wa = valid && a1 != 0.0, wb = SPIN && valid && b1 != 0.0;  // still waiting
     const int64_t base = (int64_t)m * (2 * lmax + 1 - m) / 2;
-    int res = lmax + 1;
-    for (int l = l0; l <= lmax; ++l) {
-        int k;
-        const bool ha = a1 != 0.0 && (frexp(a1, &k), k + ea >= thr);
-        const bool hb = SPIN && b1 != 0.0 && (frexp(b1, &k), k + eb >= thr);
-        if (ha || hb) {
-            res = l;
-            break;
+    for (int lb = l0, k = 0; lb <= lmax; lb += START_DEG, ++k) {
+        if (wa && ea == 0) {
+            va = make_double2(a0, a1);
+            ka = k;
+            wa = false;
         }
-        if (l == lmax)
-            break;
-        const double2 cf = ab[base + l];
-        const double na = fma(fma(cf.x, x, cf.y), a1, -a0);
-        a0 = a1;
-        a1 = na;
-        if (fabs(a1) > 0x1p64 || (a1 != 0.0 && fabs(a1) < 0x1p-64)) {
-            frexp(a1, &k);
-            a0 = ldexp(a0, -k);
-            a1 = ldexp(a1, -k);
-            ea += k;
+        if (SPIN && wb && eb == 0) {
+            vb = make_double2(b0, b1);
+            kb = k;
+            wb = false;
         }
-        if (SPIN) {
-            const double nb = fma(fma(cf.x, x, -cf.y), b1, -b0);
-            b0 = b1;
-            b1 = nb;
-            if (fabs(b1) > 0x1p64 || (b1 != 0.0 && fabs(b1) < 0x1p-64)) {
-                frexp(b1, &k);
-                b0 = ldexp(b0, -k);
-                b1 = ldexp(b1, -k);
-                eb += k;
+        if (!__any(wa || wb) || lb + START_DEG > lmax)
+            break;
+#pragma unroll
+        for (int d = 0; d < START_DEG; ++d) {
+            const double2 c = rec_coef<SPIN>(ab, base + lb + d);
+            const double na = fma(fma(c.x, x, c.y), a1, -a0);
+            a0 = a1;
+            a1 = na;
+            if (SPIN) {
+                const double nb = fma(fma(c.x, x, -c.y), b1, -b0);
+                b0 = b1;
+                b1 = nb;
             }
         }
+        if (wa)
+            rescale_channel(a0, a1, ea);
+        if (SPIN && wb)
+            rescale_channel(b0, b1, eb);
     }
-    lfirst[id] = res;
+    sta[idx] = va;
+    if (SPIN)
+        stb[idx] = vb;
+    stk[idx] = (int32_t)((unsigned)ka | ((unsigned)kb << 16));
 }
 
-static void live_launch(const gsht_plan &p, int r, int nchunk, int thr, int32_t *lfirst,
-                        hipStream_t s)
+size_t leg_start_bytes(const gsht_plan &p)
 {
-    const int64_t n = (int64_t)(p.mmax + 1) * nchunk;
-    dim3 blk(64), grd((unsigned)((n + 63) / 64));
+    return (size_t)p.leg.np * ((p.spin ? 2 : 1) * sizeof(double2) + sizeof(int32_t));
+}
+
+hipError_t launch_leg_starts(const gsht_plan &p, int m0, int nm, hipStream_t s)
+{
+    dim3 blk(64), grd(p.leg.np / 64, nm);
     if (p.spin)
-        hipLaunchKernelGGL(leg_live_kernel<true>, grd, blk, 0, s, p.leg.ab, p.leg.start, p.lmax,
-                           p.mmax, p.ntheta, p.npairs, 64 * r, nchunk, thr, lfirst);
+        hipLaunchKernelGGL(leg_starts_kernel<true>, grd, blk, 0, s, p.leg.ab, p.leg.start, p.lmax,
+                           m0, p.ntheta, p.npairs, p.leg.np, p.leg.sta, p.leg.stb, p.leg.stk);
     else
-        hipLaunchKernelGGL(leg_live_kernel<false>, grd, blk, 0, s, p.leg.ab, p.leg.start, p.lmax,
-                           p.mmax, p.ntheta, p.npairs, 64 * r, nchunk, thr, lfirst);
-}
-
-hipError_t launch_leg_live(const gsht_plan &p, hipStream_t s)
-{
-    live_launch(p, p.syn_r, p.syn_nchunk, SYN_IN_EXP, p.leg.lfirst_syn, s);
-    live_launch(p, p.adj_r, p.adj_nchunk, ADJ_IN_EXP, p.leg.lfirst_adj, s);
-    return hipGetLastError();
-}
-
-hipError_t launch_leg_live_adj(const gsht_plan &p, hipStream_t s)
-{
-    live_launch(p, p.adj_r, p.adj_nchunk, ADJ_IN_EXP, p.leg.lfirst_adj, s);
+        hipLaunchKernelGGL(leg_starts_kernel<false>, grd, blk, 0, s, p.leg.ab, p.leg.start, p.lmax,
+                           m0, p.ntheta, p.npairs, p.leg.np, p.leg.sta, p.leg.stb, p.leg.stk);
     return hipGetLastError();
 }
 
 // Accumulators of one ring pair: spin s -> N+ (0,1), S+ (2,3), N- (4,5), S- (6,7);
-// spin 0 -> N (0,1), S (2,3).  SG = (-1)^(l - l0).
+// spin 0 -> the sums E (0,1) over even and O (2,3) over odd l - l0, N = E + O and
+// S = E - O.  SG = (-1)^(l - l0).
 template <bool SPIN, int SG>
 __device__ inline void synth_acc(double (&c)[8], double va, double vb, const double *u)
 {
-    c[0] = fma(u[0], va, c[0]);
-    c[1] = fma(u[1], va, c[1]);
     if (SPIN) {
+        c[0] = fma(u[0], va, c[0]);
+        c[1] = fma(u[1], va, c[1]);
         c[2] = fma(SG * u[0], vb, c[2]);
         c[3] = fma(SG * u[1], vb, c[3]);
         c[4] = fma(u[2], vb, c[4]);
@@ -140,9 +164,20 @@ __device__ inline void synth_acc(double (&c)[8], double va, double vb, const dou
         c[6] = fma(SG * u[2], va, c[6]);
         c[7] = fma(SG * u[3], va, c[7]);
     } else {
-        c[2] = fma(SG * u[0], va, c[2]);
-        c[3] = fma(SG * u[1], va, c[3]);
+        constexpr int o = SG > 0 ? 0 : 2;
+        c[o] = fma(u[0], va, c[o]);
+        c[o + 1] = fma(u[1], va, c[o + 1]);
     }
+}
+
+// Spin 0: parity sums E, O -> ring values N, S.
+__device__ inline void parity_rings(double (&c)[8])
+{
+    const double e0 = c[0], e1 = c[1], o0 = c[2], o1 = c[3];
+    c[0] = e0 + o0;
+    c[1] = e1 + o1;
+    c[2] = e0 - o0;
+    c[3] = e1 - o1;
 }
 
 // Gradient-only spin s (C = 0): u- = (-1)^s conj(u+), so the four ring sums follow
@@ -170,163 +205,132 @@ __device__ inline void synth_acc_any(double (&c)[8], double va, double vb, const
         synth_acc<SPIN, SG>(c, va, vb, u);
 }
 
-// Add a masked block's sums t to c for the channels in range (the offsets are
-// those the block ran with: rescaling happens after the fold).  Channel +s feeds
-// c[0,1,6,7], channel -s c[2..5]; spin 0 has channel +s only.  Gradient-only:
-// channel +s feeds c[0,1,4,5], channel -s c[2,3,6,7].
-template <bool SPIN, bool GRAD = false>
-__device__ inline void synth_fold(double (&c)[8], const double (&t)[8], const Ring &r)
-{
-    const bool ia = r.ea == 0, ib = SPIN && r.eb == 0;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const bool chan_a = GRAD ? ((k & 2) == 0) : (!SPIN || k < 2 || k > 5);
-        const bool in = chan_a ? ia : ib;
-        c[k] += in ? t[k] : 0.0;
-    }
-}
+constexpr int LB = START_DEG;  // degrees per block
 
-constexpr int LB = 8;  // degrees per block
-
-// Waves per SIMD each synthesis shape is compiled for: R = 2 fits 96 registers, five
-// waves (about 1 % faster than four at 124 registers; a few values spill around the
-// loops, none inside them).
-template <int R>
-constexpr int syn_waves()
-{
-    return R == 2 ? 5 : 1;
-}
-
+// One wave per (m, chunk), R slices per lane: 12 FMA per ring pair and degree for spin s
+// (4 of them the two channels' recurrences), 4 for spin 0, the coefficients through
+// scalar loads.  Bound by the FP64 vector rate: 4.6 ms at lmax 4096, spin 2 (6.9 ms when
+// every wave ran all degrees from l0 with masks and exponent offsets and waited for the
+// coefficients), 1.64 ms for spin 0.  The offsets and masks gone, R = 2 takes 71 and
+// R = 4 124 registers.
 template <typename T, bool SPIN, int R, bool GRAD = false>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(syn_waves<R>())))
-void leg_synth_kernel(
-    const double2 *__restrict__ ab, const double *__restrict__ u, const StartInfo *__restrict__ st,
-    const int32_t *__restrict__ lfirst, int lmax, int mmax, int s, int ntheta, int nd, int npairs,
-    int nchunk, typename cplxk<T>::type *__restrict__ D)
+__global__ __launch_bounds__(64) void leg_synth_kernel(
+    const double *__restrict__ ab, const double *__restrict__ u, const StartInfo *__restrict__ st,
+    RingStarts tab, int lmax, int mend, int mmax, int s, int ntheta, int nd, int npairs, int nchunk,
+    typename cplxk<T>::type *__restrict__ D)
 {
     static_assert(SPIN || !GRAD, "gradient-only needs spin > 0");
     constexpr int US = (SPIN && !GRAD) ? 4 : 2;
+    __shared__ double2 ent[R][SPIN ? 2 : 1][64];
     int m, chunk;
-    xcd_map(nchunk, m, chunk);
-    if (m > mmax)
+    xcd_map(tab.m0, nchunk, m, chunk);
+    if (m >= mend)
         return;
     const int lane = threadIdx.x;
-    const StartInfo si = st[m];
-    const int l0 = si.l0;
-    const bool live = (l0 <= lmax) && (lfirst[m * nchunk + chunk] <= lmax);
+    const int l0 = st[m].l0;
     const int64_t base = (int64_t)m * (2 * lmax + 1 - m) / 2;
 
     Ring rg[R];
+    RingStart rs[R];
     double c[R][8];
-    bool all_in = true, some_in = false;
+    int first[R], kmax;
+    rings_init<SPIN>(rg, rs, ent, tab, m, chunk * 64 * R, ntheta, npairs, l0 <= lmax, first, kmax);
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int q = chunk * 64 * R + 64 * r + lane;
-        rg[r] = ring_init<SYN_IN_EXP>(si, q, ntheta, live && q < npairs, SPIN);
+    for (int r = 0; r < R; ++r)
 #pragma unroll
         for (int k = 0; k < 8; ++k)
             c[r][k] = 0.0;
-        const int ph = slice_phase<SPIN>(rg[r]);
-        all_in = all_in && ph == 2;
-        some_in = some_in || ph != 0;
-    }
-    // Masked block: the block's terms are summed separately and added only for
-    // channels in range (offset 0, constant inside a block); then rescaling and the
-    // slice phases.  Only the final partial block (TAIL) checks the degree bound.
-    auto masked_block = [&](int lb, auto tail) {
-        constexpr bool TAIL = decltype(tail)::value;
-        const double2 *abl = ab + base + lb;
-        const double *ul = u + US * (base + lb);
-        double t[R][8];
+    if (kmax >= 0) {
+        // Degrees in groups of G, their coefficients loaded one group ahead so that the
+        // scalar loads overlap the previous group's arithmetic (as many as two groups'
+        // worth of scalar registers hold).
+        constexpr int G = US == 4 ? 2 : 4;
+        struct Group {
+            double2 c[G];
+            double u[G * US];
+        };
+        auto load_group = [&](int l) {
+            Group q;
 #pragma unroll
-        for (int r = 0; r < R; ++r)
+            for (int g = 0; g < G; ++g) {
+                q.c[g] = rec_coef<SPIN>(ab, base + l + g);
 #pragma unroll
-            for (int k = 0; k < 8; ++k)
-                t[r][k] = 0.0;
-        // two rolled halves: a fully unrolled block would load all its scalar
-        // coefficients at once and run out of scalar registers
-#pragma unroll 1
-        for (int h = 0; h < LB; h += LB / 2)
-#pragma unroll
-        for (int b = h; b < h + LB / 2; b += 2) {
-            const int l = lb + b;
-            if (TAIL && l > lmax)
-                break;
-            const double2 c0 = abl[b];
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                synth_acc_any<SPIN, GRAD, 1>(t[r], rg[r].a1, rg[r].b1, ul + US * b);
-                ring_advance<SPIN>(rg[r], c0.x, c0.y);
+                for (int k = 0; k < US; ++k)
+                    q.u[g * US + k] = u[US * (base + l + g) + k];
             }
-            if (TAIL && l + 1 > lmax)
-                break;
-            const double2 c1 = abl[b + 1];
+            return q;
+        };
+        // Slice r joins at the first entry block of its rings: spans with 1, 2, .., R
+        // slices follow one another.
+        int kb = first[0], lb = l0 + LB * kb;
+        const int kfull = (lmax + 1 - l0) / LB;  // full blocks
+        float ta = stream_touch<SPIN ? 2 : 1>(ab, base, lb, lmax);
+        float tu = stream_touch<US>(u, base, lb, lmax);
+        int lpf = lb;  // at degree lpf the stretch from lpf + PF_DEG is fetched
+        if (kb < kfull) {  // at least one full block, so lb + LB - 1 <= lmax
+            const int lsafe = lmax + 1 - G;  // last degree a whole group can be read at
+            Group cur = load_group(lb);
+            for_counts<R>([&](auto nr) {
+                constexpr int NR = decltype(nr)::value;
+                const int kend = NR < R ? min(first[NR < R ? NR : 0], kfull) : kfull;
+                for (; kb < kend; lb += LB, ++kb) {
+                    if (kb <= kmax)
+                        rings_enter<SPIN, NR>(rg, rs, ent, kb);
+                    if (lb >= lpf) {
+                        asm volatile("" ::"v"(ta), "v"(tu));
+                        lpf += PF_DEG;
+                        ta = stream_touch<SPIN ? 2 : 1>(ab, base, lpf, lmax);
+                        tu = stream_touch<US>(u, base, lpf, lmax);
+                    }
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                synth_acc_any<SPIN, GRAD, -1>(t[r], rg[r].a1, rg[r].b1, ul + US * (b + 1));
-                ring_advance<SPIN>(rg[r], c1.x, c1.y);
-            }
+                    for (int b = 0; b < LB; b += G) {
+                        const Group nxt = load_group(min(lb + b + G, lsafe));
+#pragma unroll
+                        for (int r = 0; r < NR; ++r)
+#pragma unroll
+                            for (int g = 0; g < G; g += 2) {
+                                const double *ug = cur.u + g * US;
+                                synth_acc_any<SPIN, GRAD, 1>(c[r], rg[r].a1, rg[r].b1, ug);
+                                ring_advance<SPIN>(rg[r], cur.c[g].x, cur.c[g].y);
+                                synth_acc_any<SPIN, GRAD, -1>(c[r], rg[r].a1, rg[r].b1, ug + US);
+                                ring_advance<SPIN>(rg[r], cur.c[g + 1].x, cur.c[g + 1].y);
+                            }
+                        cur = nxt;
+                    }
+                }
+            });
         }
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-            synth_fold<SPIN, GRAD>(c[r], t[r], rg[r]);
-        all_in = true;
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            ring_rescale<SPIN, SYN_IN_EXP>(rg[r]);
-            all_in = all_in && (slice_phase<SPIN>(rg[r]) == 2);
-        }
-    };
-    if (live) {
-        // Sequential loops (no loop-carried value crosses a branch merge): silent
-        // blocks until some lane is in range, masked full blocks until every lane is,
-        // full plain blocks, and a masked partial tail.
-        int lb = l0;
-        silent_blocks<SPIN, SYN_IN_EXP>(rg, ab + base, lb, lmax, all_in, some_in);
-        for (; lb + LB - 1 <= lmax && !all_in; lb += LB)
-            masked_block(lb, flag<false>());
-        // Full plain blocks, run as degree pairs whose coefficients are loaded one
-        // pair ahead, so that the scalar loads overlap the previous pair's arithmetic.
-        if (lb + LB - 1 <= lmax) {
-            const int lend = lb + ((lmax - lb + 1) / LB) * LB;
-            struct Pair {
-                double2 c0, c1;
-                double u[2 * US];
-            };
-            auto load_pair = [&](int l) {
-                Pair q;
-                q.c0 = ab[base + l];
-                q.c1 = ab[base + l + 1];
-#pragma unroll
-                for (int k = 0; k < 2 * US; ++k)
-                    q.u[k] = u[US * (base + l) + k];
-                return q;
-            };
-            Pair cur = load_pair(lb);
-#pragma unroll 4
-            for (; lb < lend; lb += 2) {
-                const Pair nxt = load_pair(lb + 2 < lend ? lb + 2 : lb);
+        if (lb <= lmax) {
+            if (kb <= kmax)
+                rings_enter<SPIN, R>(rg, rs, ent, kb);
+            auto degree = [&](int l, auto sign) {
+                constexpr int SG = decltype(sign)::value;
+                const double2 cf = rec_coef<SPIN>(ab, base + l);
+                const double *ul = u + US * (base + l);
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
-                    synth_acc_any<SPIN, GRAD, 1>(c[r], rg[r].a1, rg[r].b1, cur.u);
-                    ring_advance<SPIN>(rg[r], cur.c0.x, cur.c0.y);
-                    synth_acc_any<SPIN, GRAD, -1>(c[r], rg[r].a1, rg[r].b1, cur.u + US);
-                    ring_advance<SPIN>(rg[r], cur.c1.x, cur.c1.y);
+                    synth_acc_any<SPIN, GRAD, SG>(c[r], rg[r].a1, rg[r].b1, ul);
+                    ring_advance<SPIN>(rg[r], cf.x, cf.y);
                 }
-                cur = nxt;
+            };
+#pragma unroll 1
+            for (; lb <= lmax; lb += 2) {
+                degree(lb, count<1>());
+                if (lb + 1 <= lmax)
+                    degree(lb + 1, count<-1>());
             }
         }
-        if (lb <= lmax)
-            masked_block(lb, flag<true>());
     }
     // south values carry (-1)^(l+m) = (-1)^(l0+m) (-1)^(l-l0)
     const double sfix = ((l0 + m) & 1) ? -1.0 : 1.0;
     const double ms = ((s + m) & 1) ? -1.0 : 1.0;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        const int q = chunk * 64 * R + 64 * r + lane;
-        if (q >= npairs)
+        const int q = npairs - 1 - (chunk * 64 * R + 64 * r + lane);
+        if (q < 0)
             continue;
+        if constexpr (!SPIN)
+            parity_rings(c[r]);
         if constexpr (GRAD) {  // parity sums -> N+, S+, N-, S- (see synth_acc_grad)
             const double sg = (s & 1) ? -1.0 : 1.0;
             double (&v)[8] = c[r];
@@ -356,12 +360,13 @@ void leg_synth_kernel(
 }
 
 template <int R>
-static void synth_launch(const gsht_plan &p, void *Dout, bool grad, hipStream_t s)
+static void synth_launch(const gsht_plan &p, const RingStarts &tab, int nm, void *Dout, bool grad,
+                         hipStream_t s)
 {
-    dim3 blk(64), grd(xcd_grid(p.mmax, p.syn_nchunk));
+    dim3 blk(64), grd(xcd_grid(nm, p.syn_nchunk));
 #define GSHT_LEG_SYNTH(T, SP, G, C)                                                              \
     hipLaunchKernelGGL((leg_synth_kernel<T, SP, R, G>), grd, blk, 0, s, p.leg.ab, p.uprep,       \
-                       p.leg.start, p.leg.lfirst_syn, p.lmax, p.mmax, p.spin, p.ntheta, p.nd,     \
+                       p.leg.start, tab, p.lmax, tab.m0 + nm, p.mmax, p.spin, p.ntheta, p.nd,     \
                        p.npairs, p.syn_nchunk, (C *)Dout)
     if (p.prec == GSHT_F64) {
         if (p.spin && grad) GSHT_LEG_SYNTH(double, true, true, double2);
@@ -377,132 +382,88 @@ static void synth_launch(const gsht_plan &p, void *Dout, bool grad, hipStream_t 
 
 hipError_t launch_leg_synth(const gsht_plan &p, void *Dout, bool grad, hipStream_t s)
 {
-    switch (p.syn_r) {
-    case 1: synth_launch<1>(p, Dout, grad, s); break;
-    case 2: synth_launch<2>(p, Dout, grad, s); break;
-    case 4: synth_launch<4>(p, Dout, grad, s); break;
-    default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+    if (p.syn_r != 1 && p.syn_r != 2 && p.syn_r != 4)
+        return hipErrorInvalidValue;
+    return leg_bands(p, s, [&](const RingStarts &tab, int nm) {
+        switch (p.syn_r) {
+        case 1: synth_launch<1>(p, tab, nm, Dout, grad, s); break;
+        case 2: synth_launch<2>(p, tab, nm, Dout, grad, s); break;
+        default: synth_launch<4>(p, tab, nm, Dout, grad, s); break;
+        }
+    });
 }
 
 // ---- synthesis of several maps sharing one geometry --------------------------------
 
 // NM maps at once: the recurrence (both channels) runs once per ring pair and
 // degree and feeds the sums of every map; coefficients are interleaved per degree
-// as u[idx][map][US].  Masked blocks weight the Legendre values by 0/1 per channel
-// (offset 0 or not, constant inside a block) instead of keeping block sums.  The
-// chunking (R slices of 64 ring pairs) is the single-map kernel's, so the dead-chunk
-// table is shared.  Map k's doubled columns start at D + k dstride.
+// as u[idx][map][US].  Chunks, starts and blocks are the single-map kernel's.  Map k's
+// doubled columns start at D + k dstride.
 template <typename T, bool SPIN, int R, int NM>
 __global__ __launch_bounds__(64) void leg_synth_multi_kernel(
-    const double2 *__restrict__ ab, const double *__restrict__ u, const StartInfo *__restrict__ st,
-    const int32_t *__restrict__ lfirst, int lmax, int mmax, int s, int ntheta, int nd, int npairs,
-    int nchunk, size_t dstride, typename cplxk<T>::type *__restrict__ D)
+    const double *__restrict__ ab, const double *__restrict__ u, const StartInfo *__restrict__ st,
+    RingStarts tab, int lmax, int mend, int mmax, int s, int ntheta, int nd, int npairs, int nchunk,
+    size_t dstride, typename cplxk<T>::type *__restrict__ D)
 {
     constexpr int US = SPIN ? 4 : 2;
     constexpr int UD = NM * US;  // doubles per degree
+    __shared__ double2 ent[R][SPIN ? 2 : 1][64];
     int m, chunk;
-    xcd_map(nchunk, m, chunk);
-    if (m > mmax)
+    xcd_map(tab.m0, nchunk, m, chunk);
+    if (m >= mend)
         return;
     const int lane = threadIdx.x;
-    const StartInfo si = st[m];
-    const int l0 = si.l0;
-    const bool live = (l0 <= lmax) && (lfirst[m * nchunk + chunk] <= lmax);
+    const int l0 = st[m].l0;
     const int64_t base = (int64_t)m * (2 * lmax + 1 - m) / 2;
 
     Ring rg[R];
+    RingStart rs[R];
     double c[R][NM][8];
-    bool all_in = true;
+    int first[R], kmax;
+    rings_init<SPIN>(rg, rs, ent, tab, m, chunk * 64 * R, ntheta, npairs, l0 <= lmax, first, kmax);
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int q = chunk * 64 * R + 64 * r + lane;
-        rg[r] = ring_init<SYN_IN_EXP>(si, q, ntheta, live && q < npairs, SPIN);
+    for (int r = 0; r < R; ++r)
 #pragma unroll
         for (int k = 0; k < NM; ++k)
 #pragma unroll
             for (int j = 0; j < 8; ++j)
                 c[r][k][j] = 0.0;
-        all_in = all_in && (slice_phase<SPIN>(rg[r]) == 2);
-    }
-    auto masked_block = [&](int lb, auto tail) {
-        constexpr bool TAIL = decltype(tail)::value;
-        double wa[R], wb[R];
+    auto degree = [&](int l, auto sign) {
+        constexpr int SG = decltype(sign)::value;
+        const double2 cf = rec_coef<SPIN>(ab, base + l);
+        const double *ul = u + UD * (base + l);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            wa[r] = rg[r].ea == 0 ? 1.0 : 0.0;
-            wb[r] = (SPIN && rg[r].eb == 0) ? 1.0 : 0.0;
-        }
-#pragma unroll 1
-        for (int b = 0; b < LB; b += 2) {
-            const int l = lb + b;
-            if (TAIL && l > lmax)
-                break;
-            const double2 c0 = ab[base + l];
-            const double *u0 = u + UD * (base + l);
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const double va = rg[r].a1 * wa[r], vb = rg[r].b1 * wb[r];
-#pragma unroll
-                for (int k = 0; k < NM; ++k)
-                    synth_acc<SPIN, 1>(c[r][k], va, vb, u0 + US * k);
-                ring_advance<SPIN>(rg[r], c0.x, c0.y);
-            }
-            if (TAIL && l + 1 > lmax)
-                break;
-            const double2 c1 = ab[base + l + 1];
-            const double *u1 = u0 + UD;
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const double va = rg[r].a1 * wa[r], vb = rg[r].b1 * wb[r];
-#pragma unroll
-                for (int k = 0; k < NM; ++k)
-                    synth_acc<SPIN, -1>(c[r][k], va, vb, u1 + US * k);
-                ring_advance<SPIN>(rg[r], c1.x, c1.y);
-            }
-        }
-        all_in = true;
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            ring_rescale<SPIN, SYN_IN_EXP>(rg[r]);
-            all_in = all_in && (slice_phase<SPIN>(rg[r]) == 2);
+            for (int k = 0; k < NM; ++k)
+                synth_acc<SPIN, SG>(c[r][k], rg[r].a1, rg[r].b1, ul + US * k);
+            ring_advance<SPIN>(rg[r], cf.x, cf.y);
         }
     };
-    if (live) {
-        int lb = l0;
-        for (; lb + LB - 1 <= lmax && !all_in; lb += LB)
-            masked_block(lb, flag<false>());
-        const int lend = lb + ((lmax - lb + 1) / LB) * LB;
+    if (kmax >= 0) {
+        int lb = l0 + LB * first[0];
 #pragma unroll 1
-        for (; lb < lend; lb += 2) {
-            const double2 c0 = ab[base + lb], c1 = ab[base + lb + 1];
-            const double *u0 = u + UD * (base + lb);
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-#pragma unroll
-                for (int k = 0; k < NM; ++k)
-                    synth_acc<SPIN, 1>(c[r][k], rg[r].a1, rg[r].b1, u0 + US * k);
-                ring_advance<SPIN>(rg[r], c0.x, c0.y);
-#pragma unroll
-                for (int k = 0; k < NM; ++k)
-                    synth_acc<SPIN, -1>(c[r][k], rg[r].a1, rg[r].b1, u0 + UD + US * k);
-                ring_advance<SPIN>(rg[r], c1.x, c1.y);
-            }
+        for (; lb <= lmax; lb += 2) {
+            const int d = lb - l0;
+            if ((d & (LB - 1)) == 0 && d / LB <= kmax)
+                rings_enter<SPIN, R>(rg, rs, ent, d / LB);
+            degree(lb, count<1>());
+            if (lb + 1 <= lmax)
+                degree(lb + 1, count<-1>());
         }
-        if (lb <= lmax)
-            masked_block(lb, flag<true>());
     }
     const double sfix = ((l0 + m) & 1) ? -1.0 : 1.0;
     const double ms = ((s + m) & 1) ? -1.0 : 1.0;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        const int q = chunk * 64 * R + 64 * r + lane;
-        if (q >= npairs)
+        const int q = npairs - 1 - (chunk * 64 * R + 64 * r + lane);
+        if (q < 0)
             continue;
         const int jn = q, js = ntheta - 1 - q;
 #pragma unroll
         for (int k = 0; k < NM; ++k) {
+            if constexpr (!SPIN)
+                parity_rings(c[r][k]);
             typename cplxk<T>::type *Dk = D + k * dstride;
             typename cplxk<T>::type *colp = Dk + (size_t)(SPIN ? m + mmax : m) * nd;
             put_ring<T>(colp, jn, ntheta, nd, ms, c[r][k][0], c[r][k][1]);
@@ -519,14 +480,15 @@ __global__ __launch_bounds__(64) void leg_synth_multi_kernel(
 }
 
 template <int R, int NM>
-static void synth_multi_launch(const gsht_plan &p, const double *u, void *Dout, size_t dstride,
-                               hipStream_t s)
+static void synth_multi_launch(const gsht_plan &p, const RingStarts &tab, int nm, const double *u,
+                               void *Dout, size_t dstride, hipStream_t s)
 {
-    dim3 blk(64), grd(xcd_grid(p.mmax, p.syn_nchunk));
+    const int nchunk = (p.npairs + 64 * R - 1) / (64 * R);
+    dim3 blk(64), grd(xcd_grid(nm, nchunk));
 #define GSHT_LEG_SYNTH_M(T, SP, C)                                                               \
     hipLaunchKernelGGL((leg_synth_multi_kernel<T, SP, R, NM>), grd, blk, 0, s, p.leg.ab, u,      \
-                       p.leg.start, p.leg.lfirst_syn, p.lmax, p.mmax, p.spin, p.ntheta, p.nd,     \
-                       p.npairs, p.syn_nchunk, dstride, (C *)Dout)
+                       p.leg.start, tab, p.lmax, tab.m0 + nm, p.mmax, p.spin, p.ntheta, p.nd,     \
+                       p.npairs, nchunk, dstride, (C *)Dout)
     if (p.prec == GSHT_F64) {
         if (p.spin) GSHT_LEG_SYNTH_M(double, true, double2);
         else GSHT_LEG_SYNTH_M(double, false, double2);
@@ -537,19 +499,21 @@ static void synth_multi_launch(const gsht_plan &p, const double *u, void *Dout, 
 #undef GSHT_LEG_SYNTH_M
 }
 
-// nm maps (2 or 4) at once; slices per lane as the plan's synthesis (1 or 2).
+// nm maps (2 or 4) at once; slices per lane as the plan's synthesis, at most 2.
 hipError_t launch_leg_synth_multi(const gsht_plan &p, int nm, const double *u, void *Dout,
                                   size_t dstride, hipStream_t s)
 {
-    const int key = 10 * p.syn_r + nm;
-    switch (key) {
-    case 12: synth_multi_launch<1, 2>(p, u, Dout, dstride, s); break;
-    case 14: synth_multi_launch<1, 4>(p, u, Dout, dstride, s); break;
-    case 22: synth_multi_launch<2, 2>(p, u, Dout, dstride, s); break;
-    case 24: synth_multi_launch<2, 4>(p, u, Dout, dstride, s); break;
-    default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+    const int key = 10 * (p.syn_r < 2 ? p.syn_r : 2) + nm;
+    if (key != 12 && key != 14 && key != 22 && key != 24)
+        return hipErrorInvalidValue;
+    return leg_bands(p, s, [&](const RingStarts &tab, int n) {
+        switch (key) {
+        case 12: synth_multi_launch<1, 2>(p, tab, n, u, Dout, dstride, s); break;
+        case 14: synth_multi_launch<1, 4>(p, tab, n, u, Dout, dstride, s); break;
+        case 22: synth_multi_launch<2, 2>(p, tab, n, u, Dout, dstride, s); break;
+        default: synth_multi_launch<2, 4>(p, tab, n, u, Dout, dstride, s); break;
+        }
+    });
 }
 
 // ---- adjoint -----------------------------------------------------------------------
@@ -633,11 +597,27 @@ __device__ inline double swap_add16(double a, double b)
     return a2 + b2;
 }
 
-// Degrees per masked block of the adjoint (blocks before every lane is in range): the
-// masked blocks set the kernel's register count, and at 4 degrees the R = 3 shapes fit
-// 168 registers, three waves per SIMD (9.43 ms at the benchmark against 9.55 for
-// 8-degree masked blocks at two waves, and 10.18 for 4-degree ones at two waves).
-constexpr int ADJ_MASKED_B = 4;
+// The value of the lane whose number within the quad differs in bit 1 (0: bit 0).
+template <int CTRL>
+__device__ inline double quad_perm(double x)
+{
+    const unsigned long long u = (unsigned long long)__double_as_longlong(x);
+    const unsigned lo = __builtin_amdgcn_mov_dpp((unsigned)u, CTRL, 0xf, 0xf, true);
+    const unsigned hi = __builtin_amdgcn_mov_dpp((unsigned)(u >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+__device__ inline double quad_xor2(double x) { return quad_perm<0x4e>(x); }
+
+// Even lanes: a summed over the lane pair, odd lanes: b.
+__device__ inline double quad_swap_add(double a, double b)
+{
+    const bool odd = threadIdx.x & 1;
+    const double send = odd ? a : b, keep = odd ? b : a;
+    return keep + quad_perm<0xb1>(send);
+}
+
+// Degrees per partial block at the end of the adjoint's range.
+constexpr int ADJ_TAIL_B = 4;
 
 // Waves per SIMD each adjoint shape is compiled for.
 template <int R, int B>
@@ -646,48 +626,53 @@ constexpr int adj_waves()
     return R == 3 ? 3 : 1;
 }
 
-// One wave per (m, chunk).  Per block of B degrees the V = B NC per-lane sums are
+// One wave per (m, chunk).  Per block of B degrees the V = B NR per-lane sums are
 // reduced over the 64 lanes: two swap-add stages in registers leave V/4 values per
-// lane, each value spread over the 16 lanes of one row; these go through LDS
-// (rotated slots, conflict free) and are summed by V groups of 64/V lanes.  The
-// results are added to acc[idx][0..NC-1] with one coalesced FP64 atomic per
-// (degree, component).
+// lane, each value spread over the 16 lanes of one row; these go through LDS in pairs
+// and are joined there and across a few lanes.  The results are added to
+// acc[idx][0..NR-1] with one FP64 atomic per (degree, component).
+// Bound by the FP64 vector rate and, at few slices per wave, by the reduction (a fixed
+// cost per block: at lmax 4096, spin 2, the launch takes 5.7 ms + 5 ms / R).  R = 5: 6.7 ms
+// against 9.2 ms of R = 3 with masked blocks, exponent offsets and all degrees from l0.
+// Reducing through LDS alone (whole rows of 16 values per lane, no swaps) took 8.1
+// instead of 7.4 ms at R = 3: LDS bandwidth then binds.
 template <typename T, bool SPIN, int R, int B, bool GRAD = false>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(adj_waves<R, B>())))
 void leg_adjoint_kernel(
-    const double2 *__restrict__ ab, const StartInfo *__restrict__ st,
-    const int32_t *__restrict__ lfirst, const typename cplxk<T>::type *__restrict__ D, int lmax,
-    int mmax, int s, int ntheta, int nd, int npairs, int nchunk, double *__restrict__ acc)
+    const double *__restrict__ ab, const StartInfo *__restrict__ st, RingStarts tab,
+    const typename cplxk<T>::type *__restrict__ D, int lmax, int mend, int mmax, int s, int ntheta,
+    int nd, int npairs, int nchunk, double *__restrict__ acc)
 {
     static_assert(SPIN || !GRAD, "gradient-only needs spin > 0");
     constexpr int NC = SPIN ? 4 : 2;         // per-lane sums per degree
     constexpr int NR = GRAD ? 2 : NC;        // reduced values per degree
     constexpr int V = B * NR;
-    constexpr int BM = ADJ_MASKED_B < B ? ADJ_MASKED_B : B;  // degrees per masked block
+    constexpr int BM = ADJ_TAIL_B < B ? ADJ_TAIL_B : B;  // degrees per partial block
     static_assert(64 % V == 0 && V >= 8, "block values must divide the wave");
-    __shared__ double red[V * 16];
+    static_assert(LB % B == 0, "entry blocks start with reduction blocks");
+    __shared__ double2 red[V * 8];
+    __shared__ double2 ent[R][SPIN ? 2 : 1][64];
     int m, chunk;
-    xcd_map(nchunk, m, chunk);
-    if (m > mmax)
+    xcd_map(tab.m0, nchunk, m, chunk);
+    if (m >= mend)
         return;
     const int lane = threadIdx.x;
-    const StartInfo si = st[m];
-    const int l0 = si.l0;
-    if (l0 > lmax || lfirst[m * nchunk + chunk] > lmax)
+    const int l0 = st[m].l0;
+    Ring rg[R];
+    RingStart rs[R];
+    int first[R], kmax;
+    rings_init<SPIN>(rg, rs, ent, tab, m, chunk * 64 * R, ntheta, npairs, l0 <= lmax, first, kmax);
+    if (kmax < 0)
         return;
     const int64_t base = (int64_t)m * (2 * lmax + 1 - m) / 2;
     const double ms = ((s + m) & 1) ? -1.0 : 1.0;
     const double sfix = ((l0 + m) & 1) ? -1.0 : 1.0;
 
-    Ring rg[R];
     RingIn in[R];
-    int ph[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        const int q = chunk * 64 * R + 64 * r + lane;
-        const bool active = q < npairs;
-        rg[r] = ring_init<ADJ_IN_EXP>(si, q, ntheta, active, SPIN);
-        ph[r] = slice_phase<SPIN>(rg[r]);
+        const int q = npairs - 1 - (chunk * 64 * R + 64 * r + lane);
+        const bool active = q >= 0;
         double2 fpn = make_double2(0, 0), fps = fpn, fmn = fpn, fms = fpn;
         if (active) {
             const int jn = q, js = ntheta - 1 - q;
@@ -725,13 +710,6 @@ void leg_adjoint_kernel(
             in[r].v[4] = in[r].v[5] = in[r].v[6] = in[r].v[7] = 0.0;
         }
     }
-    bool all_in = true, some_in = false;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        all_in = all_in && ph[r] == 2;
-        some_in = some_in || ph[r] != 0;
-    }
-
     // Reduce the block sums cb (VB values: VB / NR degrees) over the wave and add them
     // to acc (degrees lb..).
     auto reduce_add = [&](auto &cb, int lb) {
@@ -748,26 +726,42 @@ void leg_adjoint_kernel(
 #pragma unroll
         for (int k = 0; k < VB / 4; ++k)
             c2[k] = swap_add16(c1[k], c1[k + VB / 4]);
-        const int g = lane >> 4, li = lane & 15;
+        // stage 3: pairs of slots go through LDS ([pair][lane]); SUB lanes of a group sum
+        // the 16 lanes of one (pair, row), first each its 16 / SUB entries (read in an
+        // order that keeps the groups on different banks), then across the group
+        constexpr int NP = VB / 8;          // pairs per row
+        constexpr int SUB = 64 / (4 * NP);  // lanes per group: lane bits 0, 1, then 5, 4
+        static_assert(SUB == 4 || SUB == 8 || SUB == 16, "8, 16 or 32 values");
+        double2 *const buf = red;
         __syncthreads();
 #pragma unroll
-        for (int k = 0; k < VB / 4; ++k) {
-            const int vv = k + (g & 1) * (VB / 4) + (g >> 1) * (VB / 2);
-            red[vv * 16 + ((li + vv) & 15)] = c2[k];
+        for (int k = 0; k < NP; ++k)
+            buf[k * 64 + lane] = make_double2(c2[2 * k], c2[2 * k + 1]);
+        __syncthreads();
+        const int G = SUB == 4 ? lane >> 2 : SUB == 8 ? (lane >> 2) & 7 : (lane >> 2) & 3;
+        const int sub = SUB == 4   ? lane & 3
+                        : SUB == 8 ? (lane & 3) | ((lane >> 5) << 2)
+                                   : (lane & 3) | ((lane >> 4) << 2);
+        const int g = G & 3, pr = G >> 2;
+        constexpr int NE = 16 / SUB;
+        const double2 *src = buf + pr * 64 + 16 * g + NE * sub;
+        double2 t = make_double2(0.0, 0.0);
+#pragma unroll
+        for (int i = 0; i < NE; ++i) {
+            const double2 v = src[(i + G) & (NE - 1)];
+            t.x += v.x;
+            t.y += v.y;
         }
-        __syncthreads();
-        constexpr int H = 64 / VB;      // lanes per value
-        constexpr int SPAN = 16 / H;    // row partials summed per lane
-        const int v = lane % VB, h = lane / VB;
-        double sum = 0.0;
-#pragma unroll
-        for (int i = 0; i < SPAN; ++i)
-            sum += red[v * 16 + ((h * SPAN + i + v) & 15)];
-#pragma unroll
-        for (int d = VB; d < 64; d <<= 1)
-            sum += __shfl_xor(sum, d, 64);
-        if (lane < VB && lb + lane / NR <= lmax)
-            unsafeAtomicAdd(acc + (base + lb) * NR + lane, sum);
+        double sum = quad_swap_add(t.x, t.y);  // even lanes .x, odd lanes .y
+        sum += quad_xor2(sum);
+        if constexpr (SUB >= 8)
+            sum = swap_add32(sum, sum);
+        if constexpr (SUB == 16)
+            sum = swap_add16(sum, sum);
+        const int v = 2 * pr + (lane & 1) + (g & 1) * (VB / 4) + (g >> 1) * (VB / 2);
+        constexpr int idle = 2 | (SUB >= 8 ? 32 : 0) | (SUB == 16 ? 16 : 0);
+        if ((lane & idle) == 0 && lb + v / NR <= lmax)
+            unsafeAtomicAdd(acc + (base + lb) * NR + v, sum);
     };
     // per-lane sums of a block of BB = size / NC degrees -> the values reduced over
     // the wave
@@ -785,104 +779,91 @@ void leg_adjoint_kernel(
             reduce_add(cf, lb);
         }
     };
-    // Masked block of BM degrees: channels out of range (offset < 0, constant inside a
-    // block) get the weight 0 for the block; rescaling and phase update at its end.
-    // Only partial blocks at the end (TAIL) check the degree bound.
-    auto masked_block = [&](int lb, auto tail) {
-        constexpr bool TAIL = decltype(tail)::value;
+    // Full blocks, in spans with 1, 2, .., R slices (slice r joins at the first entry
+    // block of its rings); the coefficients of each degree pair are loaded one pair ahead
+    // (across block ends too), so the scalar loads overlap the current pair's work.
+    int lb = l0 + LB * first[0];
+    if (lb + B - 1 <= lmax) {
+        const int lfull = l0 + (lmax + 1 - l0) / B * B;
+        float ta = stream_touch<SPIN ? 2 : 1>(ab, base, lb, lmax);
+        int lpf = lb;  // at degree lpf the stretch from lpf + PF_DEG is fetched
+        double2 q0 = rec_coef<SPIN>(ab, base + lb), q1 = rec_coef<SPIN>(ab, base + lb + 1);
+        for_counts<R>([&](auto nr) {
+            constexpr int N = decltype(nr)::value;
+            const int lend = N < R ? min(l0 + LB * first[N < R ? N : 0], lfull) : lfull;
+            for (; lb < lend; lb += B) {
+                const int d = lb - l0;
+                if ((B == LB || (d & (LB - 1)) == 0) && d / LB <= kmax)
+                    rings_enter<SPIN, N>(rg, rs, ent, d / LB);
+                if (lb >= lpf) {
+                    asm volatile("" ::"v"(ta));
+                    lpf += PF_DEG;
+                    ta = stream_touch<SPIN ? 2 : 1>(ab, base, lpf, lmax);
+                }
+                double cb[B * NC];
+#pragma unroll
+                for (int k = 0; k < B * NC; ++k)
+                    cb[k] = 0.0;
+#pragma unroll
+                for (int b = 0; b < B; b += 2) {
+                    const int ln = lb + b + 2;                    // next pair
+                    const int lc = ln + 1 <= lmax ? ln : lb + b;  // stays inside this m's table
+                    const double2 n0 = rec_coef<SPIN>(ab, base + lc), n1 = rec_coef<SPIN>(ab, base + lc + 1);
+#pragma unroll
+                    for (int r = 0; r < N; ++r) {
+                        adj_acc_any<SPIN, GRAD, 1>(cb + b * NC, in[r], rg[r].a1, rg[r].b1);
+                        ring_advance<SPIN>(rg[r], q0.x, q0.y);
+                        adj_acc_any<SPIN, GRAD, -1>(cb + (b + 1) * NC, in[r], rg[r].a1, rg[r].b1);
+                        ring_advance<SPIN>(rg[r], q1.x, q1.y);
+                    }
+                    q0 = n0;
+                    q1 = n1;
+                }
+                reduce_block(cb, lb);
+            }
+        });
+    }
+    // partial blocks at the end
+    for (; lb <= lmax; lb += BM) {
+        const int d = lb - l0;
+        if ((d & (LB - 1)) == 0 && d / LB <= kmax)
+            rings_enter<SPIN, R>(rg, rs, ent, d / LB);
         double cb[BM * NC];
 #pragma unroll
         for (int k = 0; k < BM * NC; ++k)
             cb[k] = 0.0;
-        const double2 *abl = ab + base + lb;
-        const bool had_some = some_in;
-        double wa[R], wb[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            wa[r] = rg[r].ea == 0 ? 1.0 : 0.0;
-            wb[r] = (SPIN && rg[r].eb == 0) ? 1.0 : 0.0;
-        }
 #pragma unroll
         for (int b = 0; b < BM; b += 2) {
             const int l = lb + b;
-            if (TAIL && l > lmax)
+            if (l > lmax)
                 break;
-            const double2 c0 = abl[b];
+            const double2 c0 = rec_coef<SPIN>(ab, base + l);
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                adj_acc_any<SPIN, GRAD, 1>(cb + b * NC, in[r], rg[r].a1 * wa[r], rg[r].b1 * wb[r]);
+                adj_acc_any<SPIN, GRAD, 1>(cb + b * NC, in[r], rg[r].a1, rg[r].b1);
                 ring_advance<SPIN>(rg[r], c0.x, c0.y);
             }
-            if (TAIL && l + 1 > lmax)
+            if (l + 1 > lmax)
                 break;
-            const double2 c1 = abl[b + 1];
+            const double2 c1 = rec_coef<SPIN>(ab, base + l + 1);
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                adj_acc_any<SPIN, GRAD, -1>(cb + (b + 1) * NC, in[r], rg[r].a1 * wa[r],
-                                            rg[r].b1 * wb[r]);
+                adj_acc_any<SPIN, GRAD, -1>(cb + (b + 1) * NC, in[r], rg[r].a1, rg[r].b1);
                 ring_advance<SPIN>(rg[r], c1.x, c1.y);
             }
-            // one degree pair per scheduling region: hoisting later degrees'
-            // recurrence steps ahead of this pair's sums costs registers
-            __builtin_amdgcn_sched_barrier(0);
         }
-        all_in = true;
-        some_in = false;
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            ring_rescale<SPIN, ADJ_IN_EXP>(rg[r]);
-            const int p = slice_phase<SPIN>(rg[r]);
-            all_in = all_in && p == 2;
-            some_in = some_in || p != 0;
-        }
-        if (had_some)  // otherwise every lane was out of range for the whole block
-            reduce_block(cb, lb);
-    };
-    // Sequential loops (no loop-carried value crosses a branch merge): silent blocks
-    // until some lane is in range, masked full blocks until every lane is, full plain
-    // blocks, and masked partial blocks at the end.
-    int lb = l0;
-    silent_blocks<SPIN, ADJ_IN_EXP>(rg, ab + base, lb, lmax, all_in, some_in);
-    for (; lb + BM - 1 <= lmax && !all_in; lb += BM)
-        masked_block(lb, flag<false>());
-    // Plain blocks; the coefficients of each degree pair are loaded one pair ahead
-    // (across block ends too), so the scalar loads overlap the current pair's work.
-    if (lb + B - 1 <= lmax) {
-        double2 q0 = ab[base + lb], q1 = ab[base + lb + 1];
-        for (; lb + B - 1 <= lmax; lb += B) {
-            double cb[B * NC];
-#pragma unroll
-            for (int k = 0; k < B * NC; ++k)
-                cb[k] = 0.0;
-#pragma unroll
-            for (int b = 0; b < B; b += 2) {
-                const int ln = lb + b + 2;                    // next pair
-                const int lc = ln + 1 <= lmax ? ln : lb + b;  // stays inside this m's table
-                const double2 n0 = ab[base + lc], n1 = ab[base + lc + 1];
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    adj_acc_any<SPIN, GRAD, 1>(cb + b * NC, in[r], rg[r].a1, rg[r].b1);
-                    ring_advance<SPIN>(rg[r], q0.x, q0.y);
-                    adj_acc_any<SPIN, GRAD, -1>(cb + (b + 1) * NC, in[r], rg[r].a1, rg[r].b1);
-                    ring_advance<SPIN>(rg[r], q1.x, q1.y);
-                }
-                q0 = n0;
-                q1 = n1;
-            }
-            reduce_block(cb, lb);
-        }
+        reduce_block(cb, lb);
     }
-    for (; lb <= lmax; lb += BM)
-        masked_block(lb, flag<true>());
 }
 
 template <int R, int B>
-static void adj_launch(const gsht_plan &p, const void *Din, bool grad, hipStream_t s)
+static void adj_launch(const gsht_plan &p, const RingStarts &tab, int nm, const void *Din, bool grad,
+                       hipStream_t s)
 {
-    dim3 blk(64), grd(xcd_grid(p.mmax, p.adj_nchunk));
+    dim3 blk(64), grd(xcd_grid(nm, p.adj_nchunk));
 #define GSHT_LEG_ADJ(T, SP, G, C)                                                                \
     hipLaunchKernelGGL((leg_adjoint_kernel<T, SP, R, B, G>), grd, blk, 0, s, p.leg.ab,           \
-                       p.leg.start, p.leg.lfirst_adj, (const C *)Din, p.lmax, p.mmax, p.spin,     \
+                       p.leg.start, tab, (const C *)Din, p.lmax, tab.m0 + nm, p.mmax, p.spin,     \
                        p.ntheta, p.nd, p.npairs, p.adj_nchunk, p.acc)
     if (p.prec == GSHT_F64) {
         if (p.spin && grad) GSHT_LEG_ADJ(double, true, true, double2);
@@ -896,13 +877,6 @@ static void adj_launch(const gsht_plan &p, const void *Din, bool grad, hipStream
 #undef GSHT_LEG_ADJ
 }
 
-
-hipError_t launch_leg_live_r1(const gsht_plan &p, int32_t *lfirst1, hipStream_t s)
-{
-    live_launch(p, 1, (p.npairs + 63) / 64, SYN_IN_EXP, lfirst1, s);
-    return hipGetLastError();
-}
-
 hipError_t launch_zero(void *ptr, size_t bytes, hipStream_t s);
 
 hipError_t launch_leg_adjoint(const gsht_plan &p, const void *Din, bool grad, hipStream_t s)
@@ -911,17 +885,21 @@ hipError_t launch_leg_adjoint(const gsht_plan &p, const void *Din, bool grad, hi
     if (e != hipSuccess)
         return e;
     const int key = p.adj_r * 100 + p.adj_b;
-    switch (key) {
-    case 108: adj_launch<1, 8>(p, Din, grad, s); break;
-    case 208: adj_launch<2, 8>(p, Din, grad, s); break;
-    case 204: adj_launch<2, 4>(p, Din, grad, s); break;
-    case 404: adj_launch<4, 4>(p, Din, grad, s); break;
-    case 308: adj_launch<3, 8>(p, Din, grad, s); break;
-    case 304: adj_launch<3, 4>(p, Din, grad, s); break;
-    case 408: adj_launch<4, 8>(p, Din, grad, s); break;
-    default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+    if (key != 108 && key != 208 && key != 204 && key != 404 && key != 308 && key != 304 &&
+        key != 408 && key != 508)
+        return hipErrorInvalidValue;
+    return leg_bands(p, s, [&](const RingStarts &tab, int nm) {
+        switch (key) {
+        case 108: adj_launch<1, 8>(p, tab, nm, Din, grad, s); break;
+        case 208: adj_launch<2, 8>(p, tab, nm, Din, grad, s); break;
+        case 204: adj_launch<2, 4>(p, tab, nm, Din, grad, s); break;
+        case 404: adj_launch<4, 4>(p, tab, nm, Din, grad, s); break;
+        case 508: adj_launch<5, 8>(p, tab, nm, Din, grad, s); break;
+        case 308: adj_launch<3, 8>(p, tab, nm, Din, grad, s); break;
+        case 304: adj_launch<3, 4>(p, tab, nm, Din, grad, s); break;
+        default: adj_launch<4, 8>(p, tab, nm, Din, grad, s); break;
+        }
+    });
 }
 
 }  // namespace gsht

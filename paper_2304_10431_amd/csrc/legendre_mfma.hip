@@ -19,8 +19,7 @@ namespace gsht {
 // into FP16 pairs hi + lo (hi the value rounded towards zero, lo the remainder,
 // likewise) and multiplied on the matrix cores (v_mfma_f32_32x32x16_f16) with FP32
 // accumulation as hi hi + hi lo + lo hi; the dropped lo lo term and the split are
-// below 2^-21 relative.  Values of a channel still carrying an exponent offset enter
-// as 0.  Columns 4k..4k+3 of map k: channel +s ("a"): Re, Im of u+ (N+) and SG Re, Im
+// below 2^-21 relative.  Values before a channel's entry block are 0.  Columns 4k..4k+3 of map k: channel +s ("a"): Re, Im of u+ (N+) and SG Re, Im
 // u- (S-); channel -s ("b"): Re, Im u- (N-) and SG Re, Im u+ (S+); spin 0: u (N) and
 // SG u (S), SG = (-1)^(l - l0).  Operand layouts of the 32x32x16 product: A row =
 // lane % 32, B column = lane % 32, degree 8 (lane / 32) + j in element j of both;
@@ -63,24 +62,24 @@ struct AOps {
 };
 
 // Values of degrees lb .. lb + 15 of both channels as operands, advancing the
-// recurrence by 16 degrees (coefficients past lmax read the zero entry at lmax).
-template <bool SPIN>
-__device__ inline void make_a(Ring &rg, const double2 *__restrict__ abm, int lb, int lmax,
-                              AOps &A, AOps &B)
+// recurrence by 16 degrees (coefficients past lmax read the zero entry at lmax).  With
+// ENTER the channels whose entry block is k0 or k0 + 1 enter at degrees lb and lb + 8.
+template <bool SPIN, bool ENTER>
+__device__ inline void make_a(Ring &rg, const RingStart &rs, const double2 (&ent)[SPIN ? 2 : 1][64], int k0,
+                              const double *__restrict__ abm, int lb, int lmax, AOps &A, AOps &B)
 {
-    const bool ia = rg.ea == 0, ib = SPIN && rg.eb == 0;
+    const int lane = threadIdx.x & 63;
     float fa[MK], fb[MK];
 #pragma unroll
     for (int j = 0; j < MK; ++j) {
-        fa[j] = ia ? (float)rg.a1 : 0.f;
-        fb[j] = ib ? (float)rg.b1 : 0.f;
+        if (ENTER && j % START_DEG == 0)
+            ring_enter<SPIN>(rg, rs, k0 + j / START_DEG, ent[0][lane], ent[SPIN ? 1 : 0][lane]);
+        fa[j] = (float)rg.a1;
+        fb[j] = (float)rg.b1;
         const int l = lb + j;
-        const double2 c = abm[l < lmax ? l : lmax];
+        const double2 c = rec_coef<SPIN>(abm, l < lmax ? l : lmax);
         ring_advance<SPIN>(rg, c.x, c.y);
     }
-    rescale_channel<SYN_IN_EXP>(rg.a0, rg.a1, rg.ea);
-    if (SPIN)
-        rescale_channel<SYN_IN_EXP>(rg.b0, rg.b1, rg.eb);
 #pragma unroll
     for (int d = 0; d < 8; ++d) {
         unsigned hi, lo;
@@ -112,27 +111,31 @@ __device__ inline f32x16_t mma(const u32x4_t &a, const u32x4_t &b, const f32x16_
 // l0 + 16 kb + 8 (lane / 32) + j.  oscale[m][map] undoes the coefficient scaling.
 template <bool SPIN, int NCB>
 __global__ __launch_bounds__(64, 2) void leg_synth_mfma_kernel(
-    const double2 *__restrict__ ab, const StartInfo *__restrict__ st,
-    const int32_t *__restrict__ lfirst, const int64_t *__restrict__ boff,
-    const u32x4_t *__restrict__ Bt, const float *__restrict__ oscale, int nm, int lmax, int mmax,
-    int s, int ntheta, int nd, int npairs, int nchunk, size_t dstride, float2 *__restrict__ D)
+    const double *__restrict__ ab, const StartInfo *__restrict__ st, RingStarts tab,
+    const int64_t *__restrict__ boff, const u32x4_t *__restrict__ Bt,
+    const float *__restrict__ oscale, int nm, int lmax, int mend, int mmax, int s, int ntheta,
+    int nd, int npairs, int nchunk, size_t dstride, float2 *__restrict__ D)
 {
     constexpr int NT = SPIN ? 2 : 1;
     constexpr int NMX = 8 * NCB;
     constexpr int BLK = NT * NCB * 2 * 64;  // 16-byte entries per block
     __shared__ float tile[64][33];
+    __shared__ double2 ent[1][SPIN ? 2 : 1][64];
     int m, chunk;
-    xcd_map(nchunk, m, chunk);
-    if (m > mmax)
+    xcd_map(tab.m0, nchunk, m, chunk);
+    if (m >= mend)
         return;
     const int lane = threadIdx.x;
-    const StartInfo si = st[m];
-    const int l0 = si.l0;
-    const bool live = (l0 <= lmax) && (lfirst[m * nchunk + chunk] <= lmax);
+    const int l0 = st[m].l0;
     const int64_t base = (int64_t)m * (2 * lmax + 1 - m) / 2;
-    const double2 *abm = ab + base;
-    const int q = chunk * 64 + lane;
-    Ring rg = ring_init<SYN_IN_EXP>(si, q, ntheta, live && q < npairs, SPIN);
+    const double *abm = ab + (SPIN ? 2 : 1) * base;
+    const int q = npairs - 1 - (chunk * 64 + lane);
+    Ring rgs[1];
+    RingStart rss[1];
+    int first[1], kmax;
+    rings_init<SPIN>(rgs, rss, ent, tab, m, chunk * 64, ntheta, npairs, l0 <= lmax, first, kmax);
+    Ring &rg = rgs[0];
+    const RingStart &rs = rss[0];
     f32x16_t acc[2][NT][NCB];
 #pragma unroll
     for (int h = 0; h < 2; ++h)
@@ -143,60 +146,61 @@ __global__ __launch_bounds__(64, 2) void leg_synth_mfma_kernel(
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
                     acc[h][t][c][r] = 0.f;
-    if (live) {
+    if (kmax >= 0) {
         const u32x4_t *bm = Bt + boff[m] * BLK + lane;
         const int nkb = (lmax - l0 + MK) / MK;
-        int kb = 0;
-        // blocks before any lane is in range: recurrence only
-        while (kb < nkb && slice_phase<SPIN>(rg) == 0) {
-#pragma unroll 4
-            for (int j = 0; j < MK; ++j) {
-                const int l = l0 + MK * kb + j;
-                const double2 c = abm[l < lmax ? l : lmax];
-                ring_advance<SPIN>(rg, c.x, c.y);
-            }
-            ring_rescale<SPIN, SYN_IN_EXP>(rg);
-            ++kb;
+        constexpr int KB = MK / START_DEG;  // entry blocks per matrix step
+        int kb = first[0] / KB;
+        AOps A[NT], An[NT];
+        u32x4_t Bc[NT][NCB][2], Bn[NT][NCB][2];
+        auto load_b = [&](int k, u32x4_t (&Bx)[NT][NCB][2]) {
+            const u32x4_t *bb = bm + (int64_t)k * BLK;
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int c = 0; c < NCB; ++c)
+#pragma unroll
+                    for (int hl = 0; hl < 2; ++hl)
+                        Bx[t][c][hl] = bb[((t * NCB + c) * 2 + hl) * 64];
+        };
+        auto products = [&](const AOps (&Ax)[NT], const u32x4_t (&Bx)[NT][NCB][2]) {
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int c = 0; c < NCB; ++c)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        f32x16_t x = acc[h][t][c];
+                        x = mma(Ax[t].v[h], Bx[t][c][0], x);
+                        x = mma(Ax[t].v[h], Bx[t][c][1], x);
+                        x = mma(Ax[t].v[2 + h], Bx[t][c][0], x);
+                        acc[h][t][c] = x;
+                    }
+        };
+        // blocks in which rings still enter, one at a time
+        const int kent = min(kmax / KB + 1, nkb);
+#pragma unroll 1
+        for (; kb < kent; ++kb) {
+            load_b(kb, Bc);
+            make_a<SPIN, true>(rg, rs, ent[0], KB * kb, abm, l0 + MK * kb, lmax, A[0], A[NT - 1]);
+            products(A, Bc);
         }
+        // Two blocks per iteration with the operand sets swapping roles, so no register
+        // copies between blocks; the next block's operands (past the end: a harmless
+        // repeat of the last tile and recurrence steps on zero coefficients) are formed
+        // while the current block's products run.
         if (kb < nkb) {
-            AOps A[NT], An[NT];
-            u32x4_t Bc[NT][NCB][2], Bn[NT][NCB][2];
-            auto load_b = [&](int k, u32x4_t (&Bx)[NT][NCB][2]) {
-                const u32x4_t *bb = bm + (int64_t)k * BLK;
-#pragma unroll
-                for (int t = 0; t < NT; ++t)
-#pragma unroll
-                    for (int c = 0; c < NCB; ++c)
-#pragma unroll
-                        for (int hl = 0; hl < 2; ++hl)
-                            Bx[t][c][hl] = bb[((t * NCB + c) * 2 + hl) * 64];
-            };
-            auto products = [&](const AOps (&Ax)[NT], const u32x4_t (&Bx)[NT][NCB][2]) {
-#pragma unroll
-                for (int t = 0; t < NT; ++t)
-#pragma unroll
-                    for (int c = 0; c < NCB; ++c)
-#pragma unroll
-                        for (int h = 0; h < 2; ++h) {
-                            f32x16_t x = acc[h][t][c];
-                            x = mma(Ax[t].v[h], Bx[t][c][0], x);
-                            x = mma(Ax[t].v[h], Bx[t][c][1], x);
-                            x = mma(Ax[t].v[2 + h], Bx[t][c][0], x);
-                            acc[h][t][c] = x;
-                        }
+            auto make = [&](int k, AOps (&Ax)[NT]) {
+                make_a<SPIN, false>(rg, rs, ent[0], 0, abm, l0 + MK * k, lmax, Ax[0], Ax[NT - 1]);
             };
             load_b(kb, Bc);
-            make_a<SPIN>(rg, abm, l0 + MK * kb, lmax, A[0], A[NT - 1]);
-            // two blocks per iteration with the operand sets swapping roles, so no
-            // register copies between blocks; the next block's operands (past the
-            // end: a harmless repeat of the last tile and recurrence steps on zero
-            // coefficients) are formed while the current block's products run
+            make(kb, A);
             for (; kb + 1 < nkb; kb += 2) {
                 load_b(kb + 1, Bn);
-                make_a<SPIN>(rg, abm, l0 + MK * (kb + 1), lmax, An[0], An[NT - 1]);
+                make(kb + 1, An);
                 products(A, Bc);
                 load_b(kb + 2 < nkb ? kb + 2 : kb + 1, Bc);
-                make_a<SPIN>(rg, abm, l0 + MK * (kb + 2), lmax, A[0], A[NT - 1]);
+                make(kb + 2, A);
                 products(An, Bn);
             }
             if (kb < nkb)
@@ -219,7 +223,7 @@ __global__ __launch_bounds__(64, 2) void leg_synth_mfma_kernel(
                 for (int r = 0; r < 16; ++r)
                     tile[32 * h + 8 * (r / 4) + rbase + r % 4][col] = acc[h][t][c][r];
             __syncthreads();
-            if (q < npairs) {
+            if (q >= 0) {
 #pragma unroll 1
                 for (int k = 0; k < 8; ++k) {
                     const int map = 8 * c + k;
@@ -253,26 +257,26 @@ __global__ __launch_bounds__(64, 2) void leg_synth_mfma_kernel(
 }
 
 hipError_t launch_leg_synth_mfma(const gsht_plan &p, int nm, const void *Bt, const float *oscale,
-                                 const int64_t *boff, const int32_t *lfirst1, void *Dout,
-                                 size_t dstride, hipStream_t s)
+                                 const int64_t *boff, void *Dout, size_t dstride, hipStream_t s)
 {
     if (p.prec != GSHT_F32 || nm < 1 || nm > 16)
         return hipErrorInvalidValue;
     const int nchunk = (p.npairs + 63) / 64;
-    dim3 blk(64), grd(xcd_grid(p.mmax, nchunk));
 #define GSHT_LEG_MFMA(SP, NCB)                                                                   \
     hipLaunchKernelGGL((leg_synth_mfma_kernel<SP, NCB>), grd, blk, 0, s, p.leg.ab, p.leg.start,  \
-                       lfirst1, boff, (const u32x4_t *)Bt, oscale, nm, p.lmax, p.mmax, p.spin,    \
-                       p.ntheta, p.nd, p.npairs, nchunk, dstride, (float2 *)Dout)
-    if (p.spin) {
-        if (nm > 8) GSHT_LEG_MFMA(true, 2);
-        else GSHT_LEG_MFMA(true, 1);
-    } else {
-        if (nm > 8) GSHT_LEG_MFMA(false, 2);
-        else GSHT_LEG_MFMA(false, 1);
-    }
+                       tab, boff, (const u32x4_t *)Bt, oscale, nm, p.lmax, tab.m0 + n, p.mmax,    \
+                       p.spin, p.ntheta, p.nd, p.npairs, nchunk, dstride, (float2 *)Dout)
+    return leg_bands(p, s, [&](const RingStarts &tab, int n) {
+        dim3 blk(64), grd(xcd_grid(n, nchunk));
+        if (p.spin) {
+            if (nm > 8) GSHT_LEG_MFMA(true, 2);
+            else GSHT_LEG_MFMA(true, 1);
+        } else {
+            if (nm > 8) GSHT_LEG_MFMA(false, 2);
+            else GSHT_LEG_MFMA(false, 1);
+        }
+    });
 #undef GSHT_LEG_MFMA
-    return hipGetLastError();
 }
 
 // ---- adjoint of several maps on the matrix cores (FP32 form) ------------------------
@@ -284,8 +288,8 @@ hipError_t launch_leg_synth_mfma(const gsht_plan &p, int nm, const void *Bt, con
 // times (-1)^(l0+m), exactly the inputs of leg_adjoint_kernel) and then
 //   S+ = C_a[F+(N)] + SG C_b[F+(S')],  S- = C_b[conj F-(N)] + SG C_a[conj F-(S')],
 //   spin 0: b = C[F(N)] + SG C[F(S')],  SG = (-1)^(l - l0).
-// One workgroup per m; its W waves split the ring slices (64 pairs each, S slices per
-// wave, recurrence state in registers, FP64, threshold 2^-256 as the FP64 adjoint).
+// One workgroup per m; its W waves split the ring slices (64 pairs each, counted from
+// the equator, S slices per wave, FP64 recurrence, starts as in the FP64 adjoint).
 // Per block a wave writes the FP16 hi/lo parts of its slice's Legendre values to an
 // LDS slab [hi, lo][16 degrees][64 rings (+4 pad)] as (channel +s, channel -s) pairs,
 // reads them back in the B layout of v_mfma_f32_16x16x32_f16 (degree = lane % 16,
@@ -320,7 +324,7 @@ __device__ inline void adj_inputs(const float2 *__restrict__ D, int m, int mmax,
 #pragma unroll
     for (int k = 0; k < 8; ++k)
         v[k] = 0.f;
-    if (q >= npairs)
+    if (q < 0)
         return;
     const double ms = ((spin + m) & 1) ? -1.0 : 1.0;
     const int l0 = m > spin ? m : spin;
@@ -347,8 +351,8 @@ __device__ inline void adj_inputs(const float2 *__restrict__ D, int m, int mmax,
 }
 
 // F tiles: per (m, slice, 32-ring step ks) [type][cb][hi, lo][lane] half8 entries,
-// column lane % 16 (map 4 cb + (lane % 16) / 4, entry lane % 4), ring pairs
-// 64 slice + 32 ks + 8 (lane / 16) + j; per (m, map) scale 2^e (largest scaled input in
+// column lane % 16 (map 4 cb + (lane % 16) / 4, entry lane % 4), ring positions
+// 64 slice + 32 ks + 8 (lane / 16) + j from the equator; per (m, map) scale 2^e (largest scaled input in
 // [2^7, 2^8)), oscale[m][map] = 2^-e.  One workgroup per m.
 template <int NCB>
 __global__ __launch_bounds__(256) void prep_adj_mfma_kernel(
@@ -395,7 +399,8 @@ __global__ __launch_bounds__(256) void prep_adj_mfma_kernel(
             for (int h = 0; h < 2; ++h) {
                 float v[8];
                 adj_inputs(D + (size_t)(tmap < nm ? tmap : 0) * dstride, m, mmax, spin,
-                           tmap < nm ? qb + tq + 16 * h : npairs, ntheta, nd, npairs, v);
+                           tmap < nm ? npairs - 1 - (qb + tq + 16 * h) : -1, ntheta, nd, npairs,
+                           v);
 #pragma unroll
                 for (int k = 0; k < 8; ++k)
                     V[tmap][k][tq + 16 * h] = v[k] * sc[tmap];
@@ -430,41 +435,35 @@ constexpr int adj_wmax()
 }
 
 // Recurrence state of every ring of one m between blocks, structure of arrays over
-// n = 64 nslice rings: x, a0, a1, b0, b1 (double), then ea, eb (int).
-constexpr size_t RS_BYTES = 5 * sizeof(double) + 2 * sizeof(int);  // per ring
+// n = 64 nslice rings: x, a0, a1, b0, b1 (double).
+constexpr size_t RS_BYTES = 5 * sizeof(double);  // per ring
 
 __device__ inline void ring_load(Ring &r, const unsigned char *rs, int n, int idx)
 {
     const double *d = reinterpret_cast<const double *>(rs);
-    const int *e = reinterpret_cast<const int *>(d + 5 * (size_t)n);
     r.x = d[idx];
     r.a0 = d[n + idx];
     r.a1 = d[2 * n + idx];
     r.b0 = d[3 * n + idx];
     r.b1 = d[4 * n + idx];
-    r.ea = e[idx];
-    r.eb = e[n + idx];
 }
 
 __device__ inline void ring_store(const Ring &r, unsigned char *rs, int n, int idx)
 {
     double *d = reinterpret_cast<double *>(rs);
-    int *e = reinterpret_cast<int *>(d + 5 * (size_t)n);
     d[idx] = r.x;
     d[n + idx] = r.a0;
     d[2 * n + idx] = r.a1;
     d[3 * n + idx] = r.b0;
     d[4 * n + idx] = r.b1;
-    e[idx] = r.ea;
-    e[n + idx] = r.eb;
 }
 
 template <bool SPIN, int NCB, int NB>
 __global__ __launch_bounds__(64 * adj_wmax<NB>()) void leg_adjoint_mfma_kernel(
-    const double2 *__restrict__ ab, const StartInfo *__restrict__ st,
-    const int32_t *__restrict__ lfirst, const u32x4_t *__restrict__ At,
-    const float *__restrict__ oscale, int nm, int lmax, int mmax, int ntheta, int npairs,
-    int nslice, int64_t nalm, unsigned char *__restrict__ rstate, double *__restrict__ accm)
+    const double *__restrict__ ab, const StartInfo *__restrict__ st, RingStarts tab,
+    const u32x4_t *__restrict__ At, const float *__restrict__ oscale, int nm, int lmax, int mend,
+    int ntheta, int npairs, int nslice, int64_t nalm, unsigned char *__restrict__ rstate,
+    double *__restrict__ accm)
 {
     constexpr int NT = SPIN ? 2 : 1;
     constexpr int NR = SPIN ? 4 : 2;
@@ -474,27 +473,25 @@ __global__ __launch_bounds__(64 * adj_wmax<NB>()) void leg_adjoint_mfma_kernel(
     extern __shared__ unsigned smem[];
     const int W = blockDim.x / 64;
     const int w = threadIdx.x / 64, lane = threadIdx.x % 64;
-    const int m = blockIdx.x;
-    if (m > mmax)
+    const int m = tab.m0 + blockIdx.x;
+    if (m >= mend)
         return;
-    const StartInfo si = st[m];
-    const int l0 = si.l0;
+    const int l0 = st[m].l0;
     if (l0 > lmax)
         return;
     const int64_t base = (int64_t)m * (2 * lmax + 1 - m) / 2;
-    const double2 *abm = ab + base;
+    const double *abm = ab + (SPIN ? 2 : 1) * base;
     unsigned *slab = smem + w * (2 * BK * PROW);
     f32x4_t *red = reinterpret_cast<f32x4_t *>(smem);  // [W][NB][NT][NCB][64], after a barrier
     const int nr = 64 * nslice;
     unsigned char *rs = rstate + (size_t)m * nr * RS_BYTES;
-    // slices of this wave: w, w + W, ...; live ones in a bit mask
-    unsigned live = 0;
-    for (int i = 0, sl = w; sl < nslice; ++i, sl += W) {
-        const bool act = lfirst[m * nslice + sl] <= lmax;
-        live |= act ? (1u << i) : 0u;
-        const int q = 64 * sl + lane;
-        const Ring r0 = ring_init<ADJ_IN_EXP>(si, q, ntheta, act && q < npairs, SPIN);
-        ring_store(r0, rs, nr, q);
+    // slices of this wave: w, w + W, ...
+    for (int sl = w; sl < nslice; sl += W) {
+        const int e = 64 * sl + lane;
+        Ring r0;
+        r0.x = ring_x(e < npairs ? npairs - 1 - e : 0, ntheta);
+        r0.a0 = r0.a1 = r0.b0 = r0.b1 = 0.0;
+        ring_store(r0, rs, nr, e);
     }
     const int n = lane % 16, g = lane / 16;
     for (int lb = l0; lb <= lmax; lb += BK) {
@@ -507,25 +504,16 @@ __global__ __launch_bounds__(64 * adj_wmax<NB>()) void leg_adjoint_mfma_kernel(
                 for (int c = 0; c < NCB; ++c)
                     acc[b][t][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
-        for (int i = 0, sl = w; sl < nslice; ++i, sl += W) {
-            if (!((live >> i) & 1u))
-                continue;
-            const int q = 64 * sl + lane;
+        for (int sl = w; sl < nslice; sl += W) {
+            const int e = 64 * sl + lane;
+            const RingStart en = ring_start(tab, m, e, SPIN);
+            const int k0 = (lb - l0) / START_DEG;  // entry blocks k0 .. k0 + BK / 8 - 1
+            if (!__any(min(en.ka, en.kb) < k0 + BK / START_DEG))
+                continue;  // every ring of the slice enters later
+            const bool entering = __any((en.ka >= k0 && en.ka < k0 + BK / START_DEG) ||
+                                        (en.kb >= k0 && en.kb < k0 + BK / START_DEG));
             Ring rg;
-            ring_load(rg, rs, nr, q);
-            if (slice_phase<SPIN>(rg) == 0) {  // nothing in range: recurrence only
-#pragma unroll 4
-                for (int j = 0; j < BK; ++j) {
-                    const int l = lb + j;
-                    const double2 c = abm[l < lmax ? l : lmax];
-                    ring_advance<SPIN>(rg, c.x, c.y);
-                }
-                rescale_channel<ADJ_IN_EXP>(rg.a0, rg.a1, rg.ea);
-                if (SPIN)
-                    rescale_channel<ADJ_IN_EXP>(rg.b0, rg.b1, rg.eb);
-                ring_store(rg, rs, nr, q);
-                continue;
-            }
+            ring_load(rg, rs, nr, e);
             // F tiles of both 32-ring steps, requested before the recurrence runs
             const u32x4_t *ap = At + ((int64_t)m * 2 * nslice + 2 * sl) * PER + lane;
             u32x4_t ah[2][NT][NCB], al[2][NT][NCB];
@@ -539,23 +527,36 @@ __global__ __launch_bounds__(64 * adj_wmax<NB>()) void leg_adjoint_mfma_kernel(
                         al[ks][t][c] = ap[ks * PER + ((t * NCB + c) * 2 + 1) * 64];
                     }
             // Legendre values of degrees lb .. lb + BK - 1 -> slab (hi, lo planes)
-            const bool ia = rg.ea == 0, ib = SPIN && rg.eb == 0;
-#pragma unroll 4
-            for (int j = 0; j < BK; ++j) {
-                const float fa = ia ? (float)rg.a1 : 0.f;
-                const float fb = ib ? (float)rg.b1 : 0.f;
-                const half2_t h = __builtin_bit_cast(half2_t, __builtin_amdgcn_cvt_pkrtz(fa, fb));
-                const auto lo = __builtin_amdgcn_cvt_pkrtz(fa - (float)h[0], fb - (float)h[1]);
-                slab[j * PROW + lane] = __builtin_bit_cast(unsigned, h);
-                slab[(BK + j) * PROW + lane] = __builtin_bit_cast(unsigned, lo);
-                const int l = lb + j;
-                const double2 c = abm[l < lmax ? l : lmax];
-                ring_advance<SPIN>(rg, c.x, c.y);
+#pragma unroll 1
+            for (int jb = 0; jb < BK; jb += START_DEG) {
+                if (entering) {
+                    const size_t idx = (size_t)(m - tab.m0) * tab.np + e;
+                    const int kk = k0 + jb / START_DEG;
+                    if (en.ka == kk) {
+                        const double2 v = tab.a[idx];
+                        rg.a0 = v.x;
+                        rg.a1 = v.y;
+                    }
+                    if (SPIN && en.kb == kk) {
+                        const double2 v = tab.b[idx];
+                        rg.b0 = v.x;
+                        rg.b1 = v.y;
+                    }
+                }
+#pragma unroll
+                for (int j = jb; j < jb + START_DEG; ++j) {
+                    const float fa = (float)rg.a1, fb = (float)rg.b1;
+                    const half2_t h =
+                        __builtin_bit_cast(half2_t, __builtin_amdgcn_cvt_pkrtz(fa, fb));
+                    const auto lo = __builtin_amdgcn_cvt_pkrtz(fa - (float)h[0], fb - (float)h[1]);
+                    slab[j * PROW + lane] = __builtin_bit_cast(unsigned, h);
+                    slab[(BK + j) * PROW + lane] = __builtin_bit_cast(unsigned, lo);
+                    const int l = lb + j;
+                    const double2 c = rec_coef<SPIN>(abm, l < lmax ? l : lmax);
+                    ring_advance<SPIN>(rg, c.x, c.y);
+                }
             }
-            rescale_channel<ADJ_IN_EXP>(rg.a0, rg.a1, rg.ea);
-            if (SPIN)
-                rescale_channel<ADJ_IN_EXP>(rg.b0, rg.b1, rg.eb);
-            ring_store(rg, rs, nr, q);
+            ring_store(rg, rs, nr, e);
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -684,46 +685,45 @@ hipError_t launch_prep_adj_mfma(const gsht_plan &p, int nm, const void *Din, siz
 
 template <bool SP, int NCB, int NB>
 static hipError_t adj_mfma_go(const gsht_plan &p, int nm, int W, const void *tiles,
-                              const float *oscale, const int32_t *lfirst1, void *rstate,
-                              double *accm, hipStream_t s)
+                              const float *oscale, void *rstate, double *accm, hipStream_t s)
 {
     const size_t lds = adj_mfma_lds(W, NB);
     hipError_t e = hipFuncSetAttribute((const void *)leg_adjoint_mfma_kernel<SP, NCB, NB>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess)
         return e;
-    hipLaunchKernelGGL((leg_adjoint_mfma_kernel<SP, NCB, NB>), dim3(p.mmax + 1), dim3(64 * W), lds,
-                       s, p.leg.ab, p.leg.start, lfirst1, (const u32x4_t *)tiles, oscale, nm,
-                       p.lmax, p.mmax, p.ntheta, p.npairs, (p.npairs + 63) / 64, p.nalm,
-                       (unsigned char *)rstate, accm);
-    return hipGetLastError();
+    return leg_bands(p, s, [&](const RingStarts &tab, int n) {
+        hipLaunchKernelGGL((leg_adjoint_mfma_kernel<SP, NCB, NB>), dim3(n), dim3(64 * W), lds, s,
+                           p.leg.ab, p.leg.start, tab, (const u32x4_t *)tiles, oscale, nm, p.lmax,
+                           tab.m0 + n, p.ntheta, p.npairs, (p.npairs + 63) / 64, p.nalm,
+                           (unsigned char *)rstate, accm);
+    });
 }
 
 template <bool SP, int NCB>
 static hipError_t adj_mfma_nb(const gsht_plan &p, int nm, int W, const void *tiles,
-                              const float *oscale, const int32_t *lfirst1, void *rstate,
-                              double *accm, hipStream_t s)
+                              const float *oscale, void *rstate, double *accm, hipStream_t s)
 {
     switch (adj_nb()) {
-    case 1: return adj_mfma_go<SP, NCB, 1>(p, nm, W, tiles, oscale, lfirst1, rstate, accm, s);
-    case 2: return adj_mfma_go<SP, NCB, 2>(p, nm, W, tiles, oscale, lfirst1, rstate, accm, s);
-    default: return adj_mfma_go<SP, NCB, 4>(p, nm, W, tiles, oscale, lfirst1, rstate, accm, s);
+    case 1: return adj_mfma_go<SP, NCB, 1>(p, nm, W, tiles, oscale, rstate, accm, s);
+    case 2: return adj_mfma_go<SP, NCB, 2>(p, nm, W, tiles, oscale, rstate, accm, s);
+    default: return adj_mfma_go<SP, NCB, 4>(p, nm, W, tiles, oscale, rstate, accm, s);
     }
 }
 
 hipError_t launch_leg_adjoint_mfma(const gsht_plan &p, int nm, const void *tiles,
-                                   const float *oscale, const int32_t *lfirst1, void *rstate,
-                                   double *accm, hipStream_t s)
+                                   const float *oscale, void *rstate, double *accm,
+                                   hipStream_t s)
 {
     int S, W;
     adj_mfma_shape(p, S, W);
     if (p.prec != GSHT_F32 || nm < 1 || nm > 16 || W == 0)
         return hipErrorInvalidValue;
     if (p.spin)
-        return nm > 8 ? adj_mfma_nb<true, 4>(p, nm, W, tiles, oscale, lfirst1, rstate, accm, s)
-                      : adj_mfma_nb<true, 2>(p, nm, W, tiles, oscale, lfirst1, rstate, accm, s);
-    return nm > 8 ? adj_mfma_nb<false, 4>(p, nm, W, tiles, oscale, lfirst1, rstate, accm, s)
-                  : adj_mfma_nb<false, 2>(p, nm, W, tiles, oscale, lfirst1, rstate, accm, s);
+        return nm > 8 ? adj_mfma_nb<true, 4>(p, nm, W, tiles, oscale, rstate, accm, s)
+                      : adj_mfma_nb<true, 2>(p, nm, W, tiles, oscale, rstate, accm, s);
+    return nm > 8 ? adj_mfma_nb<false, 4>(p, nm, W, tiles, oscale, rstate, accm, s)
+                  : adj_mfma_nb<false, 2>(p, nm, W, tiles, oscale, rstate, accm, s);
 }
 
 }  // namespace gsht
