@@ -165,7 +165,7 @@ struct gsht_plan {
     int color_start[7] = {};                // items of colour c: [color_start[c], color_start[c+1])
     int2 *tile_items = nullptr;             // (first chunk, number of chunks) per tile
     // work buffers
-    void *D = nullptr;     // [ncol][nd] complex
+    void *D = nullptr;     // [ncol][nd] complex: doubled meridians (colmode 2: the rings alone)
     void *E = nullptr;     // [ncol][n1] complex
     void *G = nullptr;     // complex grid [nrows][n2] (spin > 0) or half spectrum [nrows][n2/2+1]
     void *g = nullptr;     // real grid [nrows][n2] (spin 0 only)

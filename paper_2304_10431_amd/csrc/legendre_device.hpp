@@ -273,13 +273,14 @@ __device__ inline void store_c(typename cplxk<T>::type *p, double re, double im)
     *p = v;
 }
 
-// Ring value and, for interior rings, its doubled mirror with sign ms.
+// Ring value and, with dbl and for interior rings, its doubled mirror with sign ms.  (A
+// plan whose column stage takes pairs of columns wants the rings alone.)
 template <typename T>
-__device__ inline void put_ring(typename cplxk<T>::type *col, int j, int ntheta, int nd, double ms,
-                                double re, double im)
+__device__ inline void put_ring(typename cplxk<T>::type *col, int j, int ntheta, int nd, int dbl,
+                                double ms, double re, double im)
 {
     store_c<T>(col + j, re, im);
-    if (j > 0 && j < ntheta - 1)
+    if (dbl && j > 0 && j < ntheta - 1)
         store_c<T>(col + (nd - j), ms * re, ms * im);
 }
 
@@ -290,13 +291,14 @@ __device__ inline double2 ld_c(const typename cplxk<T>::type *p)
     return make_double2((double)v.x, (double)v.y);
 }
 
-// Undoubled ring value H(j) from the doubled column.
+// Ring value H(j) of the adjoint: the undoubled sum of a doubled column (dbl), or the
+// entry itself.
 template <typename T>
 __device__ inline double2 ring_in(const typename cplxk<T>::type *col, int j, int ntheta, int nd,
-                                  double ms)
+                                  int dbl, double ms)
 {
     double2 v = ld_c<T>(col + j);
-    if (j > 0 && j < ntheta - 1) {
+    if (dbl && j > 0 && j < ntheta - 1) {
         const double2 w = ld_c<T>(col + (nd - j));
         v.x += ms * w.x;
         v.y += ms * w.y;

@@ -216,7 +216,7 @@ constexpr int LB = START_DEG;  // degrees per block
 template <typename T, bool SPIN, int R, bool GRAD = false>
 __global__ __launch_bounds__(64) void leg_synth_kernel(
     const double *__restrict__ ab, const double *__restrict__ u, const StartInfo *__restrict__ st,
-    RingStarts tab, int lmax, int mend, int mmax, int s, int ntheta, int nd, int npairs, int nchunk,
+    RingStarts tab, int lmax, int mend, int mmax, int s, int ntheta, int nd, int dbl, int npairs, int nchunk,
     typename cplxk<T>::type *__restrict__ D)
 {
     static_assert(SPIN || !GRAD, "gradient-only needs spin > 0");
@@ -347,14 +347,14 @@ __global__ __launch_bounds__(64) void leg_synth_kernel(
         }
         const int jn = q, js = ntheta - 1 - q;
         typename cplxk<T>::type *colp = D + (size_t)(SPIN ? m + mmax : m) * nd;
-        put_ring<T>(colp, jn, ntheta, nd, ms, c[r][0], c[r][1]);
+        put_ring<T>(colp, jn, ntheta, nd, dbl, ms, c[r][0], c[r][1]);
         if (js != jn)
-            put_ring<T>(colp, js, ntheta, nd, ms, sfix * c[r][2], sfix * c[r][3]);
+            put_ring<T>(colp, js, ntheta, nd, dbl, ms, sfix * c[r][2], sfix * c[r][3]);
         if (SPIN && m > 0) {
             typename cplxk<T>::type *colm = D + (size_t)(mmax - m) * nd;
-            put_ring<T>(colm, jn, ntheta, nd, ms, c[r][4], c[r][5]);
+            put_ring<T>(colm, jn, ntheta, nd, dbl, ms, c[r][4], c[r][5]);
             if (js != jn)
-                put_ring<T>(colm, js, ntheta, nd, ms, sfix * c[r][6], sfix * c[r][7]);
+                put_ring<T>(colm, js, ntheta, nd, dbl, ms, sfix * c[r][6], sfix * c[r][7]);
         }
     }
 }
@@ -367,7 +367,7 @@ static void synth_launch(const gsht_plan &p, const RingStarts &tab, int nm, void
 #define GSHT_LEG_SYNTH(T, SP, G, C)                                                              \
     hipLaunchKernelGGL((leg_synth_kernel<T, SP, R, G>), grd, blk, 0, s, p.leg.ab, p.uprep,       \
                        p.leg.start, tab, p.lmax, tab.m0 + nm, p.mmax, p.spin, p.ntheta, p.nd,     \
-                       p.npairs, p.syn_nchunk, (C *)Dout)
+                       p.colmode != 2, p.npairs, p.syn_nchunk, (C *)Dout)
     if (p.prec == GSHT_F64) {
         if (p.spin && grad) GSHT_LEG_SYNTH(double, true, true, double2);
         else if (p.spin) GSHT_LEG_SYNTH(double, true, false, double2);
@@ -402,7 +402,7 @@ hipError_t launch_leg_synth(const gsht_plan &p, void *Dout, bool grad, hipStream
 template <typename T, bool SPIN, int R, int NM>
 __global__ __launch_bounds__(64) void leg_synth_multi_kernel(
     const double *__restrict__ ab, const double *__restrict__ u, const StartInfo *__restrict__ st,
-    RingStarts tab, int lmax, int mend, int mmax, int s, int ntheta, int nd, int npairs, int nchunk,
+    RingStarts tab, int lmax, int mend, int mmax, int s, int ntheta, int nd, int dbl, int npairs, int nchunk,
     size_t dstride, typename cplxk<T>::type *__restrict__ D)
 {
     constexpr int US = SPIN ? 4 : 2;
@@ -466,14 +466,14 @@ __global__ __launch_bounds__(64) void leg_synth_multi_kernel(
                 parity_rings(c[r][k]);
             typename cplxk<T>::type *Dk = D + k * dstride;
             typename cplxk<T>::type *colp = Dk + (size_t)(SPIN ? m + mmax : m) * nd;
-            put_ring<T>(colp, jn, ntheta, nd, ms, c[r][k][0], c[r][k][1]);
+            put_ring<T>(colp, jn, ntheta, nd, dbl, ms, c[r][k][0], c[r][k][1]);
             if (js != jn)
-                put_ring<T>(colp, js, ntheta, nd, ms, sfix * c[r][k][2], sfix * c[r][k][3]);
+                put_ring<T>(colp, js, ntheta, nd, dbl, ms, sfix * c[r][k][2], sfix * c[r][k][3]);
             if (SPIN && m > 0) {
                 typename cplxk<T>::type *colm = Dk + (size_t)(mmax - m) * nd;
-                put_ring<T>(colm, jn, ntheta, nd, ms, c[r][k][4], c[r][k][5]);
+                put_ring<T>(colm, jn, ntheta, nd, dbl, ms, c[r][k][4], c[r][k][5]);
                 if (js != jn)
-                    put_ring<T>(colm, js, ntheta, nd, ms, sfix * c[r][k][6], sfix * c[r][k][7]);
+                    put_ring<T>(colm, js, ntheta, nd, dbl, ms, sfix * c[r][k][6], sfix * c[r][k][7]);
             }
         }
     }
@@ -488,7 +488,7 @@ static void synth_multi_launch(const gsht_plan &p, const RingStarts &tab, int nm
 #define GSHT_LEG_SYNTH_M(T, SP, C)                                                               \
     hipLaunchKernelGGL((leg_synth_multi_kernel<T, SP, R, NM>), grd, blk, 0, s, p.leg.ab, u,      \
                        p.leg.start, tab, p.lmax, tab.m0 + nm, p.mmax, p.spin, p.ntheta, p.nd,     \
-                       p.npairs, nchunk, dstride, (C *)Dout)
+                       p.colmode != 2, p.npairs, nchunk, dstride, (C *)Dout)
     if (p.prec == GSHT_F64) {
         if (p.spin) GSHT_LEG_SYNTH_M(double, true, double2);
         else GSHT_LEG_SYNTH_M(double, false, double2);
@@ -641,7 +641,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(adj_waves<R,
 void leg_adjoint_kernel(
     const double *__restrict__ ab, const StartInfo *__restrict__ st, RingStarts tab,
     const typename cplxk<T>::type *__restrict__ D, int lmax, int mend, int mmax, int s, int ntheta,
-    int nd, int npairs, int nchunk, double *__restrict__ acc)
+    int nd, int dbl, int npairs, int nchunk, double *__restrict__ acc)
 {
     static_assert(SPIN || !GRAD, "gradient-only needs spin > 0");
     constexpr int NC = SPIN ? 4 : 2;         // per-lane sums per degree
@@ -677,17 +677,17 @@ void leg_adjoint_kernel(
         if (active) {
             const int jn = q, js = ntheta - 1 - q;
             const typename cplxk<T>::type *colp = D + (size_t)(SPIN ? m + mmax : m) * nd;
-            fpn = ring_in<T>(colp, jn, ntheta, nd, ms);
+            fpn = ring_in<T>(colp, jn, ntheta, nd, dbl, ms);
             if (js != jn) {
-                fps = ring_in<T>(colp, js, ntheta, nd, ms);
+                fps = ring_in<T>(colp, js, ntheta, nd, dbl, ms);
                 fps.x *= sfix;
                 fps.y *= sfix;
             }
             if (SPIN) {
                 const typename cplxk<T>::type *colm = D + (size_t)(mmax - m) * nd;
-                fmn = ring_in<T>(colm, jn, ntheta, nd, ms);
+                fmn = ring_in<T>(colm, jn, ntheta, nd, dbl, ms);
                 if (js != jn) {
-                    fms = ring_in<T>(colm, js, ntheta, nd, ms);
+                    fms = ring_in<T>(colm, js, ntheta, nd, dbl, ms);
                     fms.x *= sfix;
                     fms.y *= sfix;
                 }
@@ -864,7 +864,7 @@ static void adj_launch(const gsht_plan &p, const RingStarts &tab, int nm, const 
 #define GSHT_LEG_ADJ(T, SP, G, C)                                                                \
     hipLaunchKernelGGL((leg_adjoint_kernel<T, SP, R, B, G>), grd, blk, 0, s, p.leg.ab,           \
                        p.leg.start, tab, (const C *)Din, p.lmax, tab.m0 + nm, p.mmax, p.spin,     \
-                       p.ntheta, p.nd, p.npairs, p.adj_nchunk, p.acc)
+                       p.ntheta, p.nd, p.colmode != 2, p.npairs, p.adj_nchunk, p.acc)
     if (p.prec == GSHT_F64) {
         if (p.spin && grad) GSHT_LEG_ADJ(double, true, true, double2);
         else if (p.spin) GSHT_LEG_ADJ(double, true, false, double2);

@@ -114,7 +114,7 @@ __global__ __launch_bounds__(64, 2) void leg_synth_mfma_kernel(
     const double *__restrict__ ab, const StartInfo *__restrict__ st, RingStarts tab,
     const int64_t *__restrict__ boff, const u32x4_t *__restrict__ Bt,
     const float *__restrict__ oscale, int nm, int lmax, int mend, int mmax, int s, int ntheta,
-    int nd, int npairs, int nchunk, size_t dstride, float2 *__restrict__ D)
+    int nd, int dbl, int npairs, int nchunk, size_t dstride, float2 *__restrict__ D)
 {
     constexpr int NT = SPIN ? 2 : 1;
     constexpr int NMX = 8 * NCB;
@@ -235,19 +235,19 @@ __global__ __launch_bounds__(64, 2) void leg_synth_mfma_kernel(
                     float2 *Dk = D + (size_t)map * dstride;
                     if (!SPIN) {
                         float2 *colp = Dk + (size_t)m * nd;
-                        put_ring<float>(colp, jn, ntheta, nd, ms, v0, v1);
+                        put_ring<float>(colp, jn, ntheta, nd, dbl, ms, v0, v1);
                         if (js != jn)
-                            put_ring<float>(colp, js, ntheta, nd, ms, sfix * v2, sfix * v3);
+                            put_ring<float>(colp, js, ntheta, nd, dbl, ms, sfix * v2, sfix * v3);
                     } else if (t == 0) {  // N+, S-
-                        put_ring<float>(Dk + (size_t)(m + mmax) * nd, jn, ntheta, nd, ms, v0, v1);
+                        put_ring<float>(Dk + (size_t)(m + mmax) * nd, jn, ntheta, nd, dbl, ms, v0, v1);
                         if (m > 0 && js != jn)
-                            put_ring<float>(Dk + (size_t)(mmax - m) * nd, js, ntheta, nd, ms,
+                            put_ring<float>(Dk + (size_t)(mmax - m) * nd, js, ntheta, nd, dbl, ms,
                                             sfix * v2, sfix * v3);
                     } else {  // N-, S+
                         if (m > 0)
-                            put_ring<float>(Dk + (size_t)(mmax - m) * nd, jn, ntheta, nd, ms, v0, v1);
+                            put_ring<float>(Dk + (size_t)(mmax - m) * nd, jn, ntheta, nd, dbl, ms, v0, v1);
                         if (js != jn)
-                            put_ring<float>(Dk + (size_t)(m + mmax) * nd, js, ntheta, nd, ms,
+                            put_ring<float>(Dk + (size_t)(m + mmax) * nd, js, ntheta, nd, dbl, ms,
                                             sfix * v2, sfix * v3);
                     }
                 }
@@ -265,7 +265,7 @@ hipError_t launch_leg_synth_mfma(const gsht_plan &p, int nm, const void *Bt, con
 #define GSHT_LEG_MFMA(SP, NCB)                                                                   \
     hipLaunchKernelGGL((leg_synth_mfma_kernel<SP, NCB>), grd, blk, 0, s, p.leg.ab, p.leg.start,  \
                        tab, boff, (const u32x4_t *)Bt, oscale, nm, p.lmax, tab.m0 + n, p.mmax,    \
-                       p.spin, p.ntheta, p.nd, p.npairs, nchunk, dstride, (float2 *)Dout)
+                       p.spin, p.ntheta, p.nd, p.colmode != 2, p.npairs, nchunk, dstride, (float2 *)Dout)
     return leg_bands(p, s, [&](const RingStarts &tab, int n) {
         dim3 blk(64), grd(xcd_grid(n, nchunk));
         if (p.spin) {
@@ -319,7 +319,7 @@ __device__ inline unsigned halves(unsigned x, unsigned y)
 
 // The eight per-ring adjoint inputs of ring pair q from one map's doubled columns.
 __device__ inline void adj_inputs(const float2 *__restrict__ D, int m, int mmax, int spin, int q,
-                                  int ntheta, int nd, int npairs, float (&v)[8])
+                                  int ntheta, int nd, int dbl, int npairs, float (&v)[8])
 {
 #pragma unroll
     for (int k = 0; k < 8; ++k)
@@ -331,18 +331,18 @@ __device__ inline void adj_inputs(const float2 *__restrict__ D, int m, int mmax,
     const double sfix = ((l0 + m) & 1) ? -1.0 : 1.0;
     const int jn = q, js = ntheta - 1 - q;
     const float2 *colp = D + (size_t)(spin ? m + mmax : m) * nd;
-    double2 n = ring_in<float>(colp, jn, ntheta, nd, ms), so = make_double2(0.0, 0.0);
+    double2 n = ring_in<float>(colp, jn, ntheta, nd, dbl, ms), so = make_double2(0.0, 0.0);
     if (js != jn) {
-        so = ring_in<float>(colp, js, ntheta, nd, ms);
+        so = ring_in<float>(colp, js, ntheta, nd, dbl, ms);
         so.x *= sfix;
         so.y *= sfix;
     }
     v[0] = (float)n.x; v[1] = (float)n.y; v[2] = (float)so.x; v[3] = (float)so.y;
     if (spin) {
         const float2 *colm = D + (size_t)(mmax - m) * nd;
-        double2 mn = ring_in<float>(colm, jn, ntheta, nd, ms), msn = make_double2(0.0, 0.0);
+        double2 mn = ring_in<float>(colm, jn, ntheta, nd, dbl, ms), msn = make_double2(0.0, 0.0);
         if (js != jn) {
-            msn = ring_in<float>(colm, js, ntheta, nd, ms);
+            msn = ring_in<float>(colm, js, ntheta, nd, dbl, ms);
             msn.x *= sfix;
             msn.y *= sfix;
         }
@@ -357,7 +357,7 @@ __device__ inline void adj_inputs(const float2 *__restrict__ D, int m, int mmax,
 template <int NCB>
 __global__ __launch_bounds__(256) void prep_adj_mfma_kernel(
     const float2 *__restrict__ D, size_t dstride, int mmax, int spin, int ntheta, int nd,
-    int npairs, int nslice, int nm, u32x4_t *__restrict__ At, float *__restrict__ oscale)
+    int dbl, int npairs, int nslice, int nm, u32x4_t *__restrict__ At, float *__restrict__ oscale)
 {
     constexpr int NMX = 4 * NCB;
     const int m = blockIdx.x, tid = threadIdx.x;
@@ -373,7 +373,7 @@ __global__ __launch_bounds__(256) void prep_adj_mfma_kernel(
         float lm = 0.f;
         for (int q = tq; q < npairs; q += 16) {
             float v[8];
-            adj_inputs(D + (size_t)tmap * dstride, m, mmax, spin, q, ntheta, nd, npairs, v);
+            adj_inputs(D + (size_t)tmap * dstride, m, mmax, spin, q, ntheta, nd, dbl, npairs, v);
 #pragma unroll
             for (int k = 0; k < 8; ++k)
                 lm = fmaxf(lm, fabsf(v[k]));
@@ -399,8 +399,8 @@ __global__ __launch_bounds__(256) void prep_adj_mfma_kernel(
             for (int h = 0; h < 2; ++h) {
                 float v[8];
                 adj_inputs(D + (size_t)(tmap < nm ? tmap : 0) * dstride, m, mmax, spin,
-                           tmap < nm ? npairs - 1 - (qb + tq + 16 * h) : -1, ntheta, nd, npairs,
-                           v);
+                           tmap < nm ? npairs - 1 - (qb + tq + 16 * h) : -1, ntheta, nd, dbl,
+                           npairs, v);
 #pragma unroll
                 for (int k = 0; k < 8; ++k)
                     V[tmap][k][tq + 16 * h] = v[k] * sc[tmap];
@@ -674,11 +674,11 @@ hipError_t launch_prep_adj_mfma(const gsht_plan &p, int nm, const void *Din, siz
     dim3 blk(256), grd(p.mmax + 1);
     if (nm > 8)
         hipLaunchKernelGGL(prep_adj_mfma_kernel<4>, grd, blk, 0, s, (const float2 *)Din, dstride,
-                           p.mmax, p.spin, p.ntheta, p.nd, p.npairs, nslice, nm, (u32x4_t *)tiles,
+                           p.mmax, p.spin, p.ntheta, p.nd, p.colmode != 2, p.npairs, nslice, nm, (u32x4_t *)tiles,
                            oscale);
     else
         hipLaunchKernelGGL(prep_adj_mfma_kernel<2>, grd, blk, 0, s, (const float2 *)Din, dstride,
-                           p.mmax, p.spin, p.ntheta, p.nd, p.npairs, nslice, nm, (u32x4_t *)tiles,
+                           p.mmax, p.spin, p.ntheta, p.nd, p.colmode != 2, p.npairs, nslice, nm, (u32x4_t *)tiles,
                            oscale);
     return hipGetLastError();
 }
