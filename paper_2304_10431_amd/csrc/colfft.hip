@@ -40,39 +40,21 @@ template <typename C> struct cx2;  // two complex values
 template <> struct cx2<float2> { using type = float4; };
 template <> struct cx2<double2> { using type = double4; };
 
-// Mode 2 (split theta transform): threads per workgroup and the largest nd or
+// Mode 2 (split theta transform): threads per workgroup at most, and the largest nd or
 // n1 / 2 it takes; each thread stages up to col_half_maxn / threads values in
-// registers.  FP32: two workgroups of 512 threads (2 x 66 KB of LDS at lmax 4096)
-// share a CU.  FP64: one workgroup per CU (132 KB) of 1024 threads, so that four
-// waves per SIMD hide the LDS latency of the passes (18 % faster than 512 threads
-// with radix-16 passes).  Either way 16 waves per CU and 128 VGPRs.
+// registers.  At lmax 4096 two FP32 workgroups of 512 threads (2 x 66 KB of LDS) share a
+// CU, and one FP64 workgroup of 1024 threads (132 KB) fills it (18 % faster than 512
+// threads with radix-16 passes).  Either way 16 waves per CU and 128 VGPRs.
 template <typename T>
 constexpr int col_half_threads()
 {
     return sizeof(T) == 4 ? 512 : 1024;
 }
-template <typename T>
-constexpr int col_half_waves()  // waves per SIMD
-{
-    return 4;
-}
+constexpr int COL_HALF_WAVES = 4;  // waves per SIMD
 template <typename T>
 constexpr int col_half_maxn()
 {
     return sizeof(T) == 4 ? 17 * 512 : 20 * 512;
-}
-
-// FP64 mode-2 kernels are instantiated for every register slot count MAXV up to
-// col_half_maxn / threads and launched with the smallest that holds the plan's
-// transforms (the forward kernel's slots cover nh = n1 / 2, the adjoint's max(nd, nh)):
-// slots sized for the largest case held 40 VGPRs per array and spilled 24 registers
-// to scratch at lmax 4096, where 6 and 9 slots suffice (column forward 1.70 -> 1.61 ms,
-// adjoint 1.72 -> 1.67 ms at sigma 1.5).  FP32 runs with the largest count: its 512
-// threads leave it 128 registers for half the slots, and it does not spill.
-template <typename T>
-constexpr int col_half_maxv()
-{
-    return col_half_maxn<T>() / col_half_threads<T>();
 }
 
 template <typename C>
@@ -402,7 +384,7 @@ __device__ inline void load_rows(const C *ec, int i, C &ev, C &od, const ColArgs
 // most two k per residue, since nh > lmax), so the LDS buffer holds max(nd, nh)
 // values.  twist[k] = e^{-2 pi i k / n1}, k < n1.
 template <typename T, int NT, int MAXV>
-__global__ __launch_bounds__(NT, col_half_waves<T>()) void column_fwd_half_kernel(
+__global__ __launch_bounds__(NT, COL_HALF_WAVES) void column_fwd_half_kernel(
     const typename cx<T>::type *__restrict__ D, typename cx<T>::type *__restrict__ E, ColArgs a,
     ColFFT fd, ColFFT fh, const typename cx<T>::type *__restrict__ twist)
 {
@@ -527,7 +509,7 @@ __global__ __launch_bounds__(NT, col_half_waves<T>()) void column_fwd_half_kerne
 // column's kfac2, into its own place and sigma times that into its mirror's.  (Where
 // sigma = -1 the pole entries become 0; the harmonics vanish there.)
 template <typename T, int NT, int MAXV>
-__global__ __launch_bounds__(NT, col_half_waves<T>()) void column_adj_half_kernel(
+__global__ __launch_bounds__(NT, COL_HALF_WAVES) void column_adj_half_kernel(
     const typename cx<T>::type *__restrict__ E, typename cx<T>::type *__restrict__ D, ColArgs a,
     ColFFT fd, ColFFT fh, const typename cx<T>::type *__restrict__ twist)
 {
@@ -743,33 +725,62 @@ size_t col_lds(const gsht_plan &p)
     return sizeof(typename cx<T>::type) * (size_t)n;
 }
 
-// Register slots of the mode-2 kernels for this plan (see col_half_maxv).
+// Threads of the mode-2 workgroups (one per pair of columns).  A pass of an n-point
+// transform has n / 8 butterflies, so large workgroups leave most of their waves idle on
+// short columns; but while all pairs fit the chip at once (1024 / NT workgroups per CU),
+// more threads shorten each of them.  So: the most threads with which every pair is
+// resident, and enough for 12 (FP32) or 9 (FP64) values per thread.  Forward + adjoint,
+// spin 2: FP64 lmax 512 (513 pairs) 256 threads 0.061, 512 0.081, 1024 0.106 ms; lmax 255
+// (256 pairs) 0.039, 0.037, 0.039; FP32 lmax 700 256 threads 0.064, 512 0.081 ms; lmax
+// 1024 128 threads 0.115, 256 0.107, 512 0.130 ms.
 template <typename T>
-int half_slots(const gsht_plan &p, bool adjoint)
+int half_threads(const gsht_plan &p)
 {
-    constexpr int NT = col_half_threads<T>();
-    const int nh = p.n1 / 2, n = adjoint ? (p.nd > nh ? p.nd : nh) : nh;
-    const int v = (n + NT - 1) / NT;
-    return v < 1 ? 1 : v;
+    constexpr int top = col_half_threads<T>(), per = sizeof(T) == 4 ? 12 : 9;
+    const int nh = p.n1 / 2, n = p.nd > nh ? p.nd : nh, pairs = (p.ncol + 1) / 2;
+    int nt = top;
+    while (nt > 64 && pairs > 256 * (1024 / nt) && n <= per * (nt / 2))
+        nt /= 2;
+    return nt;
 }
 
-// Calls f with the kernel instance of MV = v slots (MV counts down from the largest;
-// FP32 has only the largest).
-template <typename T, int MV, typename F>
-hipError_t with_fwd_half(int v, F &&f)
+// Calls f(kernel, threads) with the mode-2 instance for this plan, forward or adjoint.
+// MAXV register slots per thread hold the forward's n1 / 2 or the adjoint's max(nd,
+// n1 / 2) values; slots beyond that cost registers (FP64 with the most, 10, spills 36 to
+// scratch: at lmax 4096 the forward took 1.70 instead of 1.61 ms, single columns).
+template <typename T, bool ADJ, int NT, int MAXV, int... MORE, typename F>
+hipError_t with_slots(int v, F &&f)
 {
-    if constexpr (sizeof(T) == 8 && MV > 1)
-        if (v < MV)
-            return with_fwd_half<T, MV - 1>(v, f);
-    return f(column_fwd_half_kernel<T, col_half_threads<T>(), MV>);
+    if constexpr (sizeof...(MORE) > 0)
+        if (v > MAXV)
+            return with_slots<T, ADJ, NT, MORE...>(v, f);
+    if constexpr (ADJ)
+        return f(column_adj_half_kernel<T, NT, MAXV>, NT);
+    else
+        return f(column_fwd_half_kernel<T, NT, MAXV>, NT);
 }
-template <typename T, int MV, typename F>
-hipError_t with_adj_half(int v, F &&f)
+
+template <typename T, bool ADJ, typename F>
+hipError_t with_half(const gsht_plan &p, F &&f)
 {
-    if constexpr (sizeof(T) == 8 && MV > 1)
-        if (v < MV)
-            return with_adj_half<T, MV - 1>(v, f);
-    return f(column_adj_half_kernel<T, col_half_threads<T>(), MV>);
+    const int nt = half_threads<T>(p), nh = p.n1 / 2;
+    const int v = ((ADJ && p.nd > nh ? p.nd : nh) + nt - 1) / nt;
+    if constexpr (sizeof(T) == 4) {
+        switch (nt) {
+        case 64: return with_slots<T, ADJ, 64, 9, 12>(v, f);
+        case 128: return with_slots<T, ADJ, 128, 9, 12>(v, f);
+        case 256: return with_slots<T, ADJ, 256, 9, 12>(v, f);
+        default: return with_slots<T, ADJ, 512, 9, 12, 17>(v, f);
+        }
+    } else {
+        switch (nt) {
+        case 64: return with_slots<T, ADJ, 64, 6, 9>(v, f);
+        case 128: return with_slots<T, ADJ, 128, 6, 9>(v, f);
+        case 256: return with_slots<T, ADJ, 256, 6, 8, 9>(v, f);
+        case 512: return with_slots<T, ADJ, 512, 6, 8, 9>(v, f);
+        default: return with_slots<T, ADJ, 1024, 4, 5, 6, 7, 8, 9, 10>(v, f);
+        }
+    }
 }
 
 template <typename T>
@@ -778,13 +789,13 @@ hipError_t set_lds(const gsht_plan &p)
     const int b = (int)col_lds<T>(p);
     hipError_t e;
     if (p.colmode == 2) {
-        auto attr = [&](auto kern) {
+        auto attr = [&](auto kern, int) {
             return hipFuncSetAttribute((const void *)kern,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, b);
         };
-        e = with_fwd_half<T, col_half_maxv<T>()>(half_slots<T>(p, false), attr);
+        e = with_half<T, false>(p, attr);
         if (e == hipSuccess)
-            e = with_adj_half<T, col_half_maxv<T>()>(half_slots<T>(p, true), attr);
+            e = with_half<T, true>(p, attr);
     } else {
         e = hipFuncSetAttribute((const void *)column_fwd_kernel<T>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, b);
@@ -802,9 +813,8 @@ void launch_fwd(const gsht_plan &p, hipStream_t s)
     const ColArgs a = col_args(p);
     const size_t b = col_lds<T>(p);
     if (p.colmode == 2) {
-        constexpr int NT = col_half_threads<T>();
-        (void)with_fwd_half<T, col_half_maxv<T>()>(half_slots<T>(p, false), [&](auto kern) {
-            hipLaunchKernelGGL(kern, dim3((p.ncol + 1) / 2), dim3(NT), b, s, (const C *)p.D, (C *)p.E, a,
+        (void)with_half<T, false>(p, [&](auto kern, int nt) {
+            hipLaunchKernelGGL(kern, dim3((p.ncol + 1) / 2), dim3(nt), b, s, (const C *)p.D, (C *)p.E, a,
                                p.cf_d, p.cf_h, (const C *)p.twist);
             return hipSuccess;
         });
@@ -821,9 +831,8 @@ void launch_adj(const gsht_plan &p, hipStream_t s)
     const ColArgs a = col_args(p);
     const size_t b = col_lds<T>(p);
     if (p.colmode == 2) {
-        constexpr int NT = col_half_threads<T>();
-        (void)with_adj_half<T, col_half_maxv<T>()>(half_slots<T>(p, true), [&](auto kern) {
-            hipLaunchKernelGGL(kern, dim3((p.ncol + 1) / 2), dim3(NT), b, s, (const C *)p.E, (C *)p.D, a,
+        (void)with_half<T, true>(p, [&](auto kern, int nt) {
+            hipLaunchKernelGGL(kern, dim3((p.ncol + 1) / 2), dim3(nt), b, s, (const C *)p.E, (C *)p.D, a,
                                p.cf_d, p.cf_h, (const C *)p.twist);
             return hipSuccess;
         });
