@@ -160,9 +160,11 @@ constexpr int kNumEs = 3;
 // cell offset dx in (w/2 - 1, w/2] weighs psi((dx - i) 2 / w); with y = 2 dx - w + 1
 // in (-1, 1] that is a smooth function of y for 0 < i < w - 1 (the kernel's
 // square-root edges lie outside those intervals; the two edge taps keep the exact
-// formula).  Chebyshev interpolation at pdeg + 1 nodes in long double, converted to
-// monomial coefficients; accepted only if the double Horner evaluation stays within
-// 5e-15 of the kernel at 2001 points per tap (else the plan uses the exact formula).
+// formula).  Taps i and w - 1 - i are mirror images in y, so only i < (w + 1) / 2 are
+// kept.  Chebyshev interpolation at pdeg + 1 nodes in long double, converted to monomial
+// coefficients; accepted only if the kernels' double evaluation of both taps (even and
+// odd parts by Horner in y^2) stays within 5e-15 of the kernel at 2001 points per tap
+// (else the plan uses the exact formula).
 bool es_poly_fit(int w, double beta, std::vector<double> &coef)
 {
     const int D = es_pdeg_rt(w), N = D + 1;
@@ -187,7 +189,7 @@ bool es_poly_fit(int w, double beta, std::vector<double> &coef)
         for (int m = 0; m < N; ++m)
             tm[(size_t)k * N + m] = (m > 0 ? 2.0L * tm[(size_t)(k - 1) * N + m - 1] : 0.0L) -
                                     tm[(size_t)(k - 2) * N + m];
-    for (int i = 1; i < w - 1; ++i) {
+    for (int i = 1; i < (w + 1) / 2; ++i) {
         for (int j = 0; j < N; ++j)
             f[j] = psi(zof(cosl(pi * (j + 0.5L) / N), i));
         for (int k = 0; k < N; ++k) {
@@ -203,12 +205,19 @@ bool es_poly_fit(int w, double beta, std::vector<double> &coef)
                 a += c[k] * tm[(size_t)k * N + m];
             coef[(size_t)i * N + m] = (double)a;
         }
+        const bool middle = 2 * i == w - 1;  // even in y
+        const double *ci = coef.data() + (size_t)i * N;
         for (int t = 0; t <= 2000; ++t) {
-            const double y = -1.0 + t / 1000.0;
-            double v = coef[(size_t)i * N + D];
-            for (int k = D - 1; k >= 0; --k)
-                v = std::fma(v, y, coef[(size_t)i * N + k]);
-            if (fabsl((long double)v - psi(zof(y, i))) > 5e-15L)
+            const double y = -1.0 + t / 1000.0, y2 = y * y;
+            const int de = D & ~1, dn = (D - 1) | 1;
+            double e = ci[de], o = ci[dn];
+            for (int m = de - 2; m >= 0; m -= 2)
+                e = std::fma(e, y2, ci[m]);
+            for (int m = dn - 2; m >= 1; m -= 2)
+                o = std::fma(o, y2, ci[m]);
+            const double v = middle ? e : std::fma(y, o, e), u = middle ? e : std::fma(-y, o, e);
+            if (fabsl((long double)v - psi(zof(y, i))) > 5e-15L ||
+                fabsl((long double)u - psi(zof(y, w - 1 - i))) > 5e-15L)
                 return false;
         }
     }

@@ -477,9 +477,44 @@ struct GridGeom {
     int64_t npts;
 };
 
+// FP64 weights of the W taps at cell offset dx, from the plan's polynomials: with y = 2 dx
+// - W + 1 in (-1, 1], taps i and W - 1 - i are e(y^2) + y o(y^2) and e(y^2) - y o(y^2), so
+// one pair costs little more than one tap.  The two edge taps, whose interval ends at the
+// kernel's square-root edge, by the formula.  Against a polynomial per tap the w = 12
+// interpolation took 2.16 -> 1.90 ms (lmax 4096, spin 2).
+template <int W>
+__device__ inline void poly_weights(double dx, const double *__restrict__ poly, double beta,
+                                    double (&w)[W])
+{
+    constexpr int PD = es_pdeg<W>();
+    constexpr int DE = PD & ~1, DO = (PD - 1) | 1;  // highest even and odd powers
+    const double y = 2.0 * dx - (double)(W - 1), t = y * y;
+    w[0] = es_kernel<double>(dx * (2.0 / W), beta);
+    w[W - 1] = es_kernel<double>((dx - (double)(W - 1)) * (2.0 / W), beta);
+#pragma unroll
+    for (int i = 1; i < (W + 1) / 2; ++i) {
+        const double *c = poly + i * (PD + 1);
+        double e = c[DE];
+#pragma unroll
+        for (int k = DE - 2; k >= 0; k -= 2)
+            e = fma(e, t, c[k]);
+        if (2 * i == W - 1) {  // the middle tap of an odd W is even in y
+            w[i] = e;
+        } else {
+            double o = c[DO];
+#pragma unroll
+            for (int k = DO - 2; k >= 1; k -= 2)
+                o = fma(o, t, c[k]);
+            w[i] = fma(y, o, e);
+            w[W - 1 - i] = fma(-y, o, e);
+        }
+    }
+}
+
 // Cell indices and kernel weights of one point, relative to a patch origin.
-// POLY: FP64 interior taps by polynomial when the plan has them (interpolation; the
-// spreading kernels keep the exact formula, which measured faster there).
+// POLY: FP64 interior taps by polynomial when the plan has them (interpolation).  The
+// spreading kernels keep the formula: the polynomials of a couple's four sets of weights
+// spill there (w = 12: 5.56 against 4.97 ms).
 template <typename T, int W, bool POLY = false>
 __device__ inline void point_weights(double th, double ph, const GridGeom &g, int row0, int col0,
                                      T beta, int &lr, int &lc, T (&wx)[W], T (&wy)[W])
@@ -492,27 +527,8 @@ __device__ inline void point_weights(double th, double ph, const GridGeom &g, in
     const T fx = (T)dx, fy = (T)dy;
     if constexpr (POLY && std::is_same<T, double>::value) {
         if (g.poly != nullptr) {
-            // FP64: the two edge taps (whose interval ends at the kernel's square-root
-            // edge) exactly; each interior tap i by its polynomial in y = 2 dx - W + 1
-            // (the offset mapped to (-1, 1]), fitted on the host to ~1e-15 absolute.
-            constexpr int PD = es_pdeg<W>();
-            const double yx = 2.0 * dx - (double)(W - 1), yy = 2.0 * dy - (double)(W - 1);
-            wx[0] = es_kernel<T>(fx * sc, beta);
-            wy[0] = es_kernel<T>(fy * sc, beta);
-            wx[W - 1] = es_kernel<T>((fx - (T)(W - 1)) * sc, beta);
-            wy[W - 1] = es_kernel<T>((fy - (T)(W - 1)) * sc, beta);
-#pragma unroll
-            for (int i = 1; i < W - 1; ++i) {
-                const double *c = g.poly + i * (PD + 1);
-                double px = c[PD], py = c[PD];
-#pragma unroll
-                for (int k = PD - 1; k >= 0; --k) {
-                    px = fma(px, yx, c[k]);
-                    py = fma(py, yy, c[k]);
-                }
-                wx[i] = px;
-                wy[i] = py;
-            }
+            poly_weights<W>(dx, g.poly, beta, wx);
+            poly_weights<W>(dy, g.poly, beta, wy);
             return;
         }
     }
@@ -523,11 +539,50 @@ __device__ inline void point_weights(double th, double ph, const GridGeom &g, in
     }
 }
 
+// Row of cell idx of a patch with rows of pc cells: idx / pc by the 32-bit reciprocal m of
+// patch_recip(pc), exact for idx pc < 2^32.
+__device__ inline unsigned patch_recip(int pc) { return 0xffffffffu / (unsigned)pc + 1u; }
+__device__ inline int patch_row(int idx, unsigned m) { return (int)__umulhi((unsigned)idx, m); }
+
+// Loads the patch at (row0, col0), pr x pc cells (zero beyond the grid's rows), into LDS,
+// PATCH_BATCH cells per thread at a time: their loads are in flight together (one by
+// one, a 43 x 43 patch took eight round trips to memory).
+constexpr int PATCH_BATCH = 8;
+
+template <typename V>
+__device__ inline void load_patch(V *__restrict__ patch, const V *__restrict__ grid,
+                                  const GridGeom &g, int row0, int col0, int pr, int pc)
+{
+    const int n = pr * pc;
+    const unsigned m = patch_recip(pc);
+    for (int base = threadIdx.x; base < n; base += PATCH_BATCH * NUFFT_THREADS) {
+        V v[PATCH_BATCH];
+#pragma unroll
+        for (int u = 0; u < PATCH_BATCH; ++u) {
+            const int idx = base + u * NUFFT_THREADS;
+            const int i = patch_row(idx, m), r = row0 + i;
+            int c = col0 + idx - i * pc;
+            while (c >= g.n2)  // patches may span the torus more than once when n2 is small
+                c -= g.n2;
+            v[u] = V{};
+            if (idx < n && r < g.nrows)
+                v[u] = grid[(size_t)r * g.stride + c];
+        }
+#pragma unroll
+        for (int u = 0; u < PATCH_BATCH; ++u) {
+            const int idx = base + u * NUFFT_THREADS;
+            const int i = patch_row(idx, m);
+            if (idx < n)
+                patch[i * g.ps + idx - i * pc] = v[u];
+        }
+    }
+}
+
 // One workgroup per chunk, or (items non-null) per tile: items[b] = (first chunk, number
 // of chunks) of one tile, whose points are then one contiguous range, and the patch is
 // loaded once for all of them.
 template <typename T, int W, bool CPLX>
-__global__ __launch_bounds__(NUFFT_THREADS) void interp_kernel(
+__global__ __launch_bounds__(NUFFT_THREADS, 4) void interp_kernel(
     const int4 *__restrict__ chunks, const int2 *__restrict__ items,
     const double *__restrict__ sth, const double *__restrict__ sph,
     const int32_t *__restrict__ perm, const void *__restrict__ gridv, GridGeom g, T beta,
@@ -548,18 +603,7 @@ __global__ __launch_bounds__(NUFFT_THREADS) void interp_kernel(
     }
     const int tr = ck.x / g.nt2, tc = ck.x - (ck.x / g.nt2) * g.nt2;
     const int row0 = tr * g.t1, col0 = tc * g.t2;
-    const int PR = g.t1 + W - 1, PC = g.t2 + W - 1;
-    for (int idx = threadIdx.x; idx < PR * PC; idx += NUFFT_THREADS) {
-        const int pr = idx / PC, pc = idx - (idx / PC) * PC;
-        const int r = row0 + pr;
-        int c = col0 + pc;
-        while (c >= g.n2)  // patches may span the torus more than once when n2 is small
-            c -= g.n2;
-        V v{};
-        if (r < g.nrows)
-            v = grid[(size_t)r * g.stride + c];
-        patch[pr * g.ps + pc] = v;
-    }
+    load_patch(patch, grid, g, row0, col0, g.t1 + W - 1, g.t2 + W - 1);
     __syncthreads();
     for (int p = ck.y + threadIdx.x; p < ck.z; p += NUFFT_THREADS) {
         T wx[W], wy[W];
@@ -627,18 +671,7 @@ __global__ __launch_bounds__(NUFFT_THREADS) void interp_deriv_kernel(
     const int4 ck = chunks[blockIdx.x];
     const int tr = ck.x / g.nt2, tc = ck.x - (ck.x / g.nt2) * g.nt2;
     const int row0 = tr * g.t1, col0 = tc * g.t2;
-    const int PR = g.t1 + W - 1, PC = g.t2 + W - 1;
-    for (int idx = threadIdx.x; idx < PR * PC; idx += NUFFT_THREADS) {
-        const int pr = idx / PC, pc = idx - (idx / PC) * PC;
-        const int r = row0 + pr;
-        int c = col0 + pc;
-        while (c >= g.n2)  // patches may span the torus more than once when n2 is small
-            c -= g.n2;
-        V v{};
-        if (r < g.nrows)
-            v = grid[(size_t)r * g.stride + c];
-        patch[pr * g.ps + pc] = v;
-    }
+    load_patch(patch, grid, g, row0, col0, g.t1 + W - 1, g.t2 + W - 1);
     __syncthreads();
     const T cu = (T)g.c1, cv = (T)g.c2;
     const T sc = (T)(2.0 / W);
@@ -1158,43 +1191,59 @@ __device__ inline void flush_patch(const typename SpreadAcc<T, FQ>::U *patch, co
 {
     using A = SpreadAcc<T, FQ>;
     constexpr bool PACK = SpreadPack<T, CPLX>::value;
-    constexpr int NC = CPLX ? 2 : 1;
     const int PR = g.t1 + W - 1, PC = g.t2 + W - 1;
     const int plane = PR * g.ps;  // FP64 complex: real parts, then imaginary parts
     const double inv = 1.0 / scale;
-    for (int idx = threadIdx.x; idx < PR * PC; idx += NUFFT_THREADS) {
-        const int pr = idx / PC, pc = idx - (idx / PC) * PC;
-        const int r = row0 + pr;
-        if (r >= g.nrows)
-            continue;
-        int c = col0 + pc;
-        while (c >= g.n2)  // patches may span the torus more than once when n2 is small
-            c -= g.n2;
-        T *dst = grid + ((size_t)r * g.stride + c) * NC;
-        const int pidx = pr * g.ps + pc;
-        typename A::S qr, qi;
-        if constexpr (PACK) {
-            const long long t = (long long)reinterpret_cast<const unsigned long long *>(patch)[pidx];
-            qi = (int)(unsigned int)(t & 0xffffffffll);
-            qr = (int)((t - (long long)qi) >> 32);
-        } else {
-            qr = A::total(patch[pidx]);
-            qi = CPLX ? A::total(patch[plane + pidx]) : 0;
+    const int n = PR * PC;
+    const unsigned m = patch_recip(PC);
+    using G = typename std::conditional<CPLX, typename cpl<T>::type, T>::type;
+    // FLUSH_BATCH cells per thread at a time: the reads of the grid are in flight together
+    constexpr int FLUSH_BATCH = sizeof(T) == 8 ? 4 : 1;
+    for (int base = threadIdx.x; base < n; base += FLUSH_BATCH * NUFFT_THREADS) {
+        typename A::S qr[FLUSH_BATCH], qi[FLUSH_BATCH];
+        G *dst[FLUSH_BATCH], v[FLUSH_BATCH];
+#pragma unroll
+        for (int u = 0; u < FLUSH_BATCH; ++u) {
+            const int idx = base + u * NUFFT_THREADS;
+            const int pr = patch_row(idx, m), pc = idx - pr * PC;
+            const int r = row0 + pr;
+            int c = col0 + pc;
+            while (c >= g.n2)  // patches may span the torus more than once when n2 is small
+                c -= g.n2;
+            dst[u] = reinterpret_cast<G *>(grid) + (size_t)r * g.stride + c;
+            qr[u] = qi[u] = 0;
+            if (idx < n && r < g.nrows) {
+                const int pidx = pr * g.ps + pc;
+                if constexpr (PACK) {
+                    const long long t =
+                        (long long)reinterpret_cast<const unsigned long long *>(patch)[pidx];
+                    qi[u] = (int)(unsigned int)(t & 0xffffffffll);
+                    qr[u] = (int)((t - (long long)qi[u]) >> 32);
+                } else {
+                    qr[u] = A::total(patch[pidx]);
+                    qi[u] = CPLX ? A::total(patch[plane + pidx]) : 0;
+                }
+            }
+            if (!ATOMIC && (qr[u] != 0 || qi[u] != 0))
+                v[u] = *dst[u];
         }
-        if (ATOMIC) {
-            if (qr != 0)
-                unsafeAtomicAdd(dst, (T)((double)qr * inv));
-            if (CPLX && qi != 0)
-                unsafeAtomicAdd(dst + 1, (T)((double)qi * inv));
-        } else if (qr != 0 || qi != 0) {
-            if constexpr (CPLX) {
-                using C2 = typename cpl<T>::type;
-                C2 v = *reinterpret_cast<C2 *>(dst);
-                v.x += (T)((double)qr * inv);
-                v.y += (T)((double)qi * inv);
-                *reinterpret_cast<C2 *>(dst) = v;
-            } else {
-                *dst += (T)((double)qr * inv);
+#pragma unroll
+        for (int u = 0; u < FLUSH_BATCH; ++u) {
+            const T fr = (T)((double)qr[u] * inv), fi = (T)((double)qi[u] * inv);
+            if constexpr (ATOMIC) {
+                T *d = reinterpret_cast<T *>(dst[u]);
+                if (qr[u] != 0)
+                    unsafeAtomicAdd(d, fr);
+                if (CPLX && qi[u] != 0)
+                    unsafeAtomicAdd(d + 1, fi);
+            } else if (qr[u] != 0 || qi[u] != 0) {
+                if constexpr (CPLX) {
+                    v[u].x += fr;
+                    v[u].y += fi;
+                } else {
+                    v[u] += fr;
+                }
+                *dst[u] = v[u];
             }
         }
     }
