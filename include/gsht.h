@@ -406,8 +406,9 @@ typedef struct {
                            FFT in one kernel per column (column in LDS), 1 = doubled FFT and
                            deconvolution fused with a separate theta FFT, 0 = separate
                            library FFTs; chosen from the LDS size per workgroup */
-    int spread_colors;  /* > 0: spreading runs tile by tile in this many launches of
-                           mutually disjoint patches, flushed without atomics; 0: one
+    int spread_colors;  /* > 0: spreading without atomics, in this many launches of mutually
+                           disjoint tiles, or (few tiles, room under the workspace cap)
+                           with a patch buffer per chunk, summed in order; 0: one
                            workgroup per chunk with an atomic flush */
     int syn_r;          /* Legendre synthesis: slices of 64 ring pairs per wave */
     int adj_r, adj_b;   /* Legendre adjoint: slices per wave, degrees per reduction block */

@@ -835,6 +835,7 @@ int plan_create_impl(gsht_plan **out, int lmax, int mmax, int spin, const double
     tr.mark("sizes");
     if ((rc = setup_legendre(p, s, true)) != GSHT_OK) { free_plan(p); return rc; }
     p->workspace_bytes = ws + (int64_t)(leg_start_bytes(*p) * (size_t)p->leg.band);
+    p->gather_room = (size_t)std::max<int64_t>(workspace_cap() - p->workspace_bytes, 0);
     tr.mark("legendre tables");
     if ((rc = dev_alloc(p, &p->D, (size_t)p->ncol * p->nd * cs)) != GSHT_OK) { free_plan(p); return rc; }
     if ((rc = dev_alloc(p, &p->E, (size_t)p->ncol * p->n1 * cs)) != GSHT_OK) { free_plan(p); return rc; }
@@ -1052,10 +1053,9 @@ int plan_adjoint_to_D(gsht_plan *p, const void *map, hipStream_t s)
     if (rc != GSHT_OK)
         return rc;
     const size_t cs = csize(p->prec);
-    if (p->spin)
-        RUN(ST_ZERO_GRID, launch_zero(p->G, (size_t)p->nrows * p->n2 * cs, s));
-    else
-        RUN(ST_ZERO_GRID, launch_zero(p->g, (size_t)p->nrows * p->n2 * (cs / 2), s));
+    if (!p->patches)  // (summing the patch buffers writes every cell)
+        RUN(ST_ZERO_GRID, p->spin ? launch_zero(p->G, (size_t)p->nrows * p->n2 * cs, s)
+                                  : launch_zero(p->g, (size_t)p->nrows * p->n2 * (cs / 2), s));
     RUN(ST_SPREAD, launch_spread(*p, map, s));
     if (p->spin)
         RUNFFT(ST_FFT_PHI_FWD, run_fft(p->fP_fwd, p->G, nullptr, p->fftwork, p->fftwork_bytes, s));
@@ -1148,7 +1148,8 @@ int gsht_plan_set_points(gsht_plan *p, const double *theta, const double *phi, i
     p->points_ok = false;
     p->ncolors = 0;
     p->nchunks = 0;
-    for (void **q : {(void **)&p->chunks, (void **)&p->tile_items}) {
+    p->tile_chunk = nullptr;
+    for (void **q : {(void **)&p->chunks, (void **)&p->tile_items, &p->patches}) {
         if (!*q)
             continue;
         auto it = std::find(p->allocations.begin(), p->allocations.end(), *q);

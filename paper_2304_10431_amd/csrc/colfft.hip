@@ -1,7 +1,8 @@
 // Column FFT stage of the general SHT on gfx950 (Sect. 3: the FFT of the
 // doubled meridians, the deconvolution / zero padding of the NUFFT, and the
-// oversampled theta transform), with one workgroup per column and the column held
-// in LDS, so that each column crosses HBM once on the way in and once on the way out.
+// oversampled theta transform), with one workgroup per column (two neighbouring columns
+// where both transforms fit) and its columns held in LDS, so that each column crosses HBM
+// once on the way in and once on the way out.
 //
 //   forward:  D[col][0..nd)  --FFT_nd(-)-->  D^  --f(k,m), zero pad-->  E^[0..n1)
 //             --FFT_n1(+)-->  E[col][a]   (only the torus rows the grid keeps)

@@ -160,8 +160,11 @@ struct gsht_plan {
     int32_t *perm = nullptr;                // sorted position -> input index
     int32_t *tile_start = nullptr;          // [ntiles + 1]
     int4 *chunks = nullptr;                 // [nchunks] (tile, begin, end, 0)
-    // spreading by tile colour (0 colours = one workgroup per chunk, atomic flush)
+    // spreading by tile colour (0 colours: the grid's patches of a colour could meet)
     int ncolors = 0;
+    void *patches = nullptr;                // a patch buffer per chunk (grids of few chunks)
+    int32_t *tile_chunk = nullptr;          // [ntiles + 1] first chunk of every tile, with patches
+    size_t gather_room = 0;                 // bytes the patch buffers may take
     int color_start[7] = {};                // items of colour c: [color_start[c], color_start[c+1])
     int2 *tile_items = nullptr;             // (first chunk, number of chunks) per tile
     // work buffers

@@ -402,7 +402,24 @@ out:  // scratch of the sort; a failed free cannot change the result
 // neighbour of column 0 across phi = 0) gets cc = 2.  Tiles of one colour are then
 // at least two tiles apart, and with tiles at least W - 1 cells wide their patches
 // are disjoint.  Needs at least two tile columns; otherwise ncolors stays 0 and the
-// spreading flushes with atomics.  GSHT_SPREAD_COLORS=0 forces the atomic flush.
+// spreading flushes with atomics.  GSHT_SPREAD_COLORS=0 forces the atomic flush,
+// GSHT_SPREAD_COLORS=1 the launches by colour.
+//
+// Colours cost four or six launches one after the other, each with a quarter of the tiles
+// and every tile's chunks in turn.  Grids of few tiles do better with two launches over
+// all of them: every chunk's patch goes to a buffer of its own, and each grid cell then
+// sums the patches that cover it, in chunk order (the same bits every time, and no
+// clearing of the grid).  Colours / patch buffers, spin 2, clearing included, in ms:
+//     tiles   chunks      FP32 eps 1e-5      FP64 eps 1e-10
+//        40       32     0.054 / 0.016      0.111 / 0.031
+//        40      533     0.770 / 0.046      1.992 / 0.079
+//       544     1276     0.165 / 0.040      0.397 / 0.093
+//      2112     2049     0.074 / 0.045      0.172 / 0.115
+//      8320     8093     0.087 / 0.088      0.267 / 0.275 (2 points a tile; 25: equal)
+// so the line lies below 8320 tiles.  SPREAD_GATHER_BYTES bounds the buffers (30 KB a
+// chunk for FP64 pairs at w = 12).
+constexpr size_t SPREAD_GATHER_TILES = 6144, SPREAD_GATHER_BYTES = (size_t)512 << 20;
+
 hipError_t build_tile_colors(gsht_plan &p, hipStream_t s)
 {
     p.ncolors = 0;
@@ -450,6 +467,31 @@ hipError_t build_tile_colors(gsht_plan &p, hipStream_t s)
     if ((e = hipStreamSynchronize(s)) != hipSuccess)
         return e;
     p.ncolors = ncol;
+    if (!env && items.size() <= SPREAD_GATHER_TILES) {
+        // a buffer per chunk and the first chunk of every tile, where the cap leaves room
+        const size_t cells = (size_t)(p.t1 + p.w - 1) * (p.t2 + p.w - 1);
+        const size_t b1 = ck.size() * cells * (p.spin ? 2 : 1) * (p.prec == GSHT_F64 ? 8 : 4);
+        const size_t b2 = sizeof(int32_t) * (size_t)(p.ntiles + 1);
+        if (b1 + b2 > std::min(p.gather_room, SPREAD_GATHER_BYTES))
+            return hipSuccess;
+        std::vector<int32_t> first((size_t)p.ntiles + 1, 0);
+        for (const int4 &k : ck)
+            ++first[(size_t)k.x + 1];
+        for (size_t t = 0; t < (size_t)p.ntiles; ++t)
+            first[t + 1] += first[t];
+        void *buf = nullptr;
+        if (hipMalloc(&buf, b1 + b2) != hipSuccess) {
+            (void)hipGetLastError();
+            return hipSuccess;  // the colours serve without it
+        }
+        p.allocations.push_back(buf);
+        if ((e = hipMemcpyAsync((char *)buf + b1, first.data(), b2, hipMemcpyHostToDevice, s)) !=
+                hipSuccess ||
+            (e = hipStreamSynchronize(s)) != hipSuccess)
+            return e;
+        p.patches = buf;
+        p.tile_chunk = (int32_t *)((char *)buf + b1);
+    }
     return hipSuccess;
 }
 
@@ -1182,10 +1224,14 @@ __device__ inline bool spread_paired(int4 ck, const double *__restrict__ sth,
     return true;
 }
 
-// Adds a spread patch (fixed point, step 1 / scale) to the grid: with global atomics
-// (ATOMIC), or with plain read-add-write when no other workgroup can touch the patch
-// at the same time (tiles launched by colour).  The caller has synchronised the block.
-template <typename T, int W, bool CPLX, bool ATOMIC, bool FQ>
+// Where a spread patch goes: added to the grid with global atomics, or with plain
+// read-add-write when no other workgroup can touch the patch at the same time (tiles
+// launched by colour), or stored as it is (patch buffers).
+enum Flush { FLUSH_ATOMIC, FLUSH_ADD, FLUSH_STORE };
+
+// Flushes a spread patch (fixed point, step 1 / scale).  The caller has synchronised the
+// block.  FLUSH_STORE: grid is the patch's own buffer, PR x PC cells.
+template <typename T, int W, bool CPLX, Flush MODE, bool FQ>
 __device__ inline void flush_patch(const typename SpreadAcc<T, FQ>::U *patch, const GridGeom &g,
                                    int row0, int col0, double scale, T *__restrict__ grid)
 {
@@ -1210,9 +1256,10 @@ __device__ inline void flush_patch(const typename SpreadAcc<T, FQ>::U *patch, co
             int c = col0 + pc;
             while (c >= g.n2)  // patches may span the torus more than once when n2 is small
                 c -= g.n2;
-            dst[u] = reinterpret_cast<G *>(grid) + (size_t)r * g.stride + c;
+            dst[u] = reinterpret_cast<G *>(grid) +
+                     (MODE == FLUSH_STORE ? (size_t)idx : (size_t)r * g.stride + c);
             qr[u] = qi[u] = 0;
-            if (idx < n && r < g.nrows) {
+            if (idx < n && (MODE == FLUSH_STORE || r < g.nrows)) {
                 const int pidx = pr * g.ps + pc;
                 if constexpr (PACK) {
                     const long long t =
@@ -1224,13 +1271,22 @@ __device__ inline void flush_patch(const typename SpreadAcc<T, FQ>::U *patch, co
                     qi[u] = CPLX ? A::total(patch[plane + pidx]) : 0;
                 }
             }
-            if (!ATOMIC && (qr[u] != 0 || qi[u] != 0))
+            if (MODE == FLUSH_ADD && (qr[u] != 0 || qi[u] != 0))
                 v[u] = *dst[u];
         }
 #pragma unroll
         for (int u = 0; u < FLUSH_BATCH; ++u) {
             const T fr = (T)((double)qr[u] * inv), fi = (T)((double)qi[u] * inv);
-            if constexpr (ATOMIC) {
+            if constexpr (MODE == FLUSH_STORE) {
+                if constexpr (CPLX) {
+                    v[u].x = fr;
+                    v[u].y = fi;
+                } else {
+                    v[u] = fr;
+                }
+                if (base + u * NUFFT_THREADS < n)
+                    *dst[u] = v[u];
+            } else if constexpr (MODE == FLUSH_ATOMIC) {
                 T *d = reinterpret_cast<T *>(dst[u]);
                 if (qr[u] != 0)
                     unsafeAtomicAdd(d, fr);
@@ -1252,7 +1308,7 @@ __device__ inline void flush_patch(const typename SpreadAcc<T, FQ>::U *patch, co
 // Spreading of one chunk into its patch, then the flush of the patch to the grid.
 // FP64 grids spread couples of neighbouring points as one window (fewer LDS
 // atomics, which bound them); FP32 grids, bound by their arithmetic, point by point.
-template <typename T, int W, bool CPLX, bool ATOMIC, bool FQ>
+template <typename T, int W, bool CPLX, Flush MODE, bool FQ>
 __device__ inline void spread_chunk(int4 ck, const double *__restrict__ sth,
                                     const double *__restrict__ sph,
                                     const int32_t *__restrict__ perm, const T *__restrict__ in,
@@ -1273,10 +1329,14 @@ __device__ inline void spread_chunk(int4 ck, const double *__restrict__ sth,
     else
         any = spread_single<T, W, CPLX, FQ>(ck, sth, sph, perm, in, g, beta, patch, sg.wsum, row0,
                                             col0, scale);
-    if (!any)
+    if (!any) {
+        if constexpr (MODE == FLUSH_STORE)
+            for (int idx = threadIdx.x; idx < PR * (g.t2 + W - 1) * NC; idx += NUFFT_THREADS)
+                grid[idx] = (T)0;
         return;
+    }
     __syncthreads();
-    flush_patch<T, W, CPLX, ATOMIC, FQ>(patch, g, row0, col0, scale, grid);
+    flush_patch<T, W, CPLX, MODE, FQ>(patch, g, row0, col0, scale, grid);
     __syncthreads();  // the patch is reused by the next chunk of the same workgroup
 }
 
@@ -1330,11 +1390,11 @@ __device__ inline void spread_tile_f64(int2 it, const int4 *__restrict__ chunks,
         spread_paired<double, W, CPLX, FQ, false>(chunks[it.x + c], sth, sph, perm, in, g, beta,
                                                   patch, sg, row0, col0, scale);
     __syncthreads();
-    flush_patch<double, W, CPLX, false, FQ>(patch, g, row0, col0, scale, grid);
+    flush_patch<double, W, CPLX, FLUSH_ADD, FQ>(patch, g, row0, col0, scale, grid);
 }
 
-// One workgroup per chunk, atomic flush (any grid).
-template <typename T, int W, bool CPLX, bool FQ>
+// One workgroup per chunk: atomic flush (any grid), or each patch to its own buffer.
+template <typename T, int W, bool CPLX, bool FQ, Flush MODE>
 __global__ __launch_bounds__(NUFFT_THREADS, SPREAD_WAVES) void spread_kernel(
     const int4 *__restrict__ chunks, const double *__restrict__ sth, const double *__restrict__ sph,
     const int32_t *__restrict__ perm, const T *__restrict__ in, GridGeom g, T beta,
@@ -1342,9 +1402,51 @@ __global__ __launch_bounds__(NUFFT_THREADS, SPREAD_WAVES) void spread_kernel(
 {
     extern __shared__ unsigned char smem_raw[];
     __shared__ SpreadStage sg;
-    spread_chunk<T, W, CPLX, true, FQ>(chunks[blockIdx.x], sth, sph, perm, in, g, beta, grid,
+    if constexpr (MODE == FLUSH_STORE)
+        grid += (size_t)blockIdx.x * (g.t1 + W - 1) * (g.t2 + W - 1) * (CPLX ? 2 : 1);
+    spread_chunk<T, W, CPLX, MODE, FQ>(chunks[blockIdx.x], sth, sph, perm, in, g, beta, grid,
                                        reinterpret_cast<typename SpreadAcc<T, FQ>::U *>(smem_raw),
                                        sg);
+}
+
+// Sums the patch buffers into the grid, one thread per cell: the patches of the tile it
+// lies in and of the tiles above, to the left (across phi = 0 too) and both, every tile's
+// chunks in order.  w - 1 <= t1, so one row of tiles above reaches it; the last column of
+// tiles may be narrower than the overlap, so the columns are walked until one does not.
+// Bound by its reads of the patches (1.8 cells per cell of the grid at one chunk a tile).
+template <typename V>
+__global__ __launch_bounds__(256) void gather_kernel(const V *__restrict__ patches,
+                                                     const int32_t *__restrict__ tile_chunk,
+                                                     GridGeom g, int w, V *__restrict__ grid)
+{
+    const int c = blockIdx.x * 256 + threadIdx.x, r = blockIdx.y;
+    if (c >= g.n2)
+        return;
+    const int PR = g.t1 + w - 1, PC = g.t2 + w - 1;
+    const int tr0 = r / g.t1, tc0 = c / g.t2;
+    V s{};
+    for (int a = 0; a < 2; ++a) {
+        const int tr = tr0 - a, pr = r - tr * g.t1;
+        if (tr < 0 || pr >= PR)
+            break;
+        for (int b = 0; b < g.nt2; ++b) {
+            const int tc = tc0 >= b ? tc0 - b : tc0 - b + g.nt2;
+            const int pc = c - tc * g.t2 + (tc0 >= b ? 0 : g.n2);
+            if (pc >= PC)
+                break;
+            const int t = tr * g.nt2 + tc, k1 = tile_chunk[t + 1];
+            for (int k = tile_chunk[t]; k < k1; ++k) {
+                const V v = patches[((size_t)k * PR + pr) * PC + pc];
+                if constexpr (std::is_floating_point<V>::value) {
+                    s += v;
+                } else {
+                    s.x += v.x;
+                    s.y += v.y;
+                }
+            }
+        }
+    }
+    grid[(size_t)r * g.stride + c] = s;
 }
 
 // One workgroup per tile of one colour (all of the tile's chunks in turn), plain
@@ -1367,7 +1469,7 @@ __global__ __launch_bounds__(NUFFT_THREADS, SPREAD_WAVES) void spread_tile_kerne
             spread_tile_f64<W, CPLX, FQ>(it, chunks, sth, sph, perm, in, g, beta, grid, patch, sg);
     } else {
         for (int c = 0; c < it.y; ++c)
-            spread_chunk<T, W, CPLX, false, FQ>(chunks[it.x + c], sth, sph, perm, in, g, beta,
+            spread_chunk<T, W, CPLX, FLUSH_ADD, FQ>(chunks[it.x + c], sth, sph, perm, in, g, beta,
                                                 grid, patch, sg);
     }
 }
@@ -1460,8 +1562,26 @@ static hipError_t spread_wq(const gsht_plan &p, const void *map, hipStream_t s)
     const GridGeom g = make_geom(p);
     const int PR = p.t1 + W - 1, PS = p.t2 + W - 1;
     using U = typename SpreadAcc<T, FQ>::U;
+    const size_t sm = (size_t)PR * PS * (p.spin ? 2 : 1) * sizeof(U);
+    auto per_chunk = [&](auto kern, void *to) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)p.nchunks), dim3(NUFFT_THREADS), sm, s, p.chunks,
+                           p.sth, p.sph, p.perm, (const T *)map, g, (T)p.beta, (T *)to);
+    };
+    if (p.patches) {
+        const dim3 grd((p.n2 + 255) / 256, p.nrows);
+        if (p.spin) {
+            using V = typename cpl<T>::type;
+            per_chunk(spread_kernel<T, W, true, FQ, FLUSH_STORE>, p.patches);
+            hipLaunchKernelGGL(gather_kernel<V>, grd, dim3(256), 0, s, (const V *)p.patches,
+                               p.tile_chunk, g, W, (V *)p.G);
+        } else {
+            per_chunk(spread_kernel<T, W, false, FQ, FLUSH_STORE>, p.patches);
+            hipLaunchKernelGGL(gather_kernel<T>, grd, dim3(256), 0, s, (const T *)p.patches,
+                               p.tile_chunk, g, W, (T *)p.g);
+        }
+        return hipGetLastError();
+    }
     if (p.ncolors > 0) {
-        const size_t sm = (size_t)PR * PS * (p.spin ? 2 : 1) * sizeof(U);
         for (int c = 0; c < p.ncolors; ++c) {
             const int n = p.color_start[c + 1] - p.color_start[c];
             if (n == 0)
@@ -1478,17 +1598,10 @@ static hipError_t spread_wq(const gsht_plan &p, const void *map, hipStream_t s)
         }
         return hipGetLastError();
     }
-    if (p.spin) {
-        const size_t sm = (size_t)PR * PS * 2 * sizeof(U);
-        hipLaunchKernelGGL((spread_kernel<T, W, true, FQ>), dim3((unsigned)p.nchunks),
-                           dim3(NUFFT_THREADS), sm, s, p.chunks, p.sth, p.sph, p.perm,
-                           (const T *)map, g, (T)p.beta, (T *)p.G);
-    } else {
-        const size_t sm = (size_t)PR * PS * sizeof(U);
-        hipLaunchKernelGGL((spread_kernel<T, W, false, FQ>), dim3((unsigned)p.nchunks),
-                           dim3(NUFFT_THREADS), sm, s, p.chunks, p.sth, p.sph, p.perm,
-                           (const T *)map, g, (T)p.beta, (T *)p.g);
-    }
+    if (p.spin)
+        per_chunk(spread_kernel<T, W, true, FQ, FLUSH_ATOMIC>, p.G);
+    else
+        per_chunk(spread_kernel<T, W, false, FQ, FLUSH_ATOMIC>, p.g);
     return hipGetLastError();
 }
 
