@@ -12,7 +12,9 @@
 // Points are processed in tile order: every work item ("chunk") holds at most
 // CHUNK consecutive sorted points of one tile, and stages that tile's grid patch
 // (tile plus a w - 1 halo) in LDS.  Spreading accumulates into the LDS patch with
-// fixed-point integer LDS atomics and then flushes it to the grid with global atomics.
+// fixed-point integer LDS atomics; the patches then reach the grid tile colour by tile
+// colour, through a buffer per chunk that is summed in order (few tiles), or with global
+// atomics (a torus of few tile columns).
 #include <cstdlib>
 #include <vector>
 
