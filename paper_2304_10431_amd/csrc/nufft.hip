@@ -1416,39 +1416,46 @@ __global__ __launch_bounds__(NUFFT_THREADS, SPREAD_WAVES) void spread_kernel(
 // chunks in order.  w - 1 <= t1, so one row of tiles above reaches it; the last column of
 // tiles may be narrower than the overlap, so the columns are walked until one does not.
 // Bound by its reads of the patches (1.8 cells per cell of the grid at one chunk a tile).
+// Rows go over grid.y in strides of GATHER_ROWS at most: a launch takes 65535 workgroups
+// there, and a torus of 131072 rows (lmax above 24600 at sigma 2) keeps more rows.
+constexpr int GATHER_ROWS = 32768;
+
 template <typename V>
 __global__ __launch_bounds__(256) void gather_kernel(const V *__restrict__ patches,
                                                      const int32_t *__restrict__ tile_chunk,
                                                      GridGeom g, int w, V *__restrict__ grid)
 {
-    const int c = blockIdx.x * 256 + threadIdx.x, r = blockIdx.y;
+    const int c = blockIdx.x * 256 + threadIdx.x;
     if (c >= g.n2)
         return;
     const int PR = g.t1 + w - 1, PC = g.t2 + w - 1;
-    const int tr0 = r / g.t1, tc0 = c / g.t2;
-    V s{};
-    for (int a = 0; a < 2; ++a) {
-        const int tr = tr0 - a, pr = r - tr * g.t1;
-        if (tr < 0 || pr >= PR)
-            break;
-        for (int b = 0; b < g.nt2; ++b) {
-            const int tc = tc0 >= b ? tc0 - b : tc0 - b + g.nt2;
-            const int pc = c - tc * g.t2 + (tc0 >= b ? 0 : g.n2);
-            if (pc >= PC)
+    const int tc0 = c / g.t2;
+    for (int r = blockIdx.y; r < g.nrows; r += gridDim.y) {
+        const int tr0 = r / g.t1;
+        V s{};
+        for (int a = 0; a < 2; ++a) {
+            const int tr = tr0 - a, pr = r - tr * g.t1;
+            if (tr < 0 || pr >= PR)
                 break;
-            const int t = tr * g.nt2 + tc, k1 = tile_chunk[t + 1];
-            for (int k = tile_chunk[t]; k < k1; ++k) {
-                const V v = patches[((size_t)k * PR + pr) * PC + pc];
-                if constexpr (std::is_floating_point<V>::value) {
-                    s += v;
-                } else {
-                    s.x += v.x;
-                    s.y += v.y;
+            for (int b = 0; b < g.nt2; ++b) {
+                const int tc = tc0 >= b ? tc0 - b : tc0 - b + g.nt2;
+                const int pc = c - tc * g.t2 + (tc0 >= b ? 0 : g.n2);
+                if (pc >= PC)
+                    break;
+                const int t = tr * g.nt2 + tc, k1 = tile_chunk[t + 1];
+                for (int k = tile_chunk[t]; k < k1; ++k) {
+                    const V v = patches[((size_t)k * PR + pr) * PC + pc];
+                    if constexpr (std::is_floating_point<V>::value) {
+                        s += v;
+                    } else {
+                        s.x += v.x;
+                        s.y += v.y;
+                    }
                 }
             }
         }
+        grid[(size_t)r * g.stride + c] = s;
     }
-    grid[(size_t)r * g.stride + c] = s;
 }
 
 // One workgroup per tile of one colour (all of the tile's chunks in turn), plain
@@ -1570,7 +1577,7 @@ static hipError_t spread_wq(const gsht_plan &p, const void *map, hipStream_t s)
                            p.sth, p.sph, p.perm, (const T *)map, g, (T)p.beta, (T *)to);
     };
     if (p.patches) {
-        const dim3 grd((p.n2 + 255) / 256, p.nrows);
+        const dim3 grd((p.n2 + 255) / 256, std::min(p.nrows, GATHER_ROWS));
         if (p.spin) {
             using V = typename cpl<T>::type;
             per_chunk(spread_kernel<T, W, true, FQ, FLUSH_STORE>, p.patches);
