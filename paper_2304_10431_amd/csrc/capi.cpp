@@ -747,7 +747,8 @@ int setup_columns(gsht_plan *p, hipStream_t s)
 }
 
 // Opt-in timing of the plan-creation phases (GSHT_PLAN_TRACE=1: one line per phase on
-// stderr; the stream is synchronised at each mark, so traced creation is slower).
+// stderr, and how the spreading flushes its patches; the stream is synchronised at each
+// mark, so traced creation is slower).
 struct PlanTrace {
     bool on;
     hipStream_t s;
@@ -766,6 +767,12 @@ struct PlanTrace {
         fprintf(stderr, "gsht plan: %-18s %9.3f ms\n", what,
                 std::chrono::duration<double, std::milli>(now - t).count());
         t = now;
+    }
+    void spreading(const gsht_plan &p) const
+    {
+        if (on)
+            fprintf(stderr, "gsht plan: spreading by %s\n",
+                    p.patches ? "patch buffers" : p.ncolors ? "tile colours" : "atomic adds");
     }
 };
 
@@ -869,6 +876,7 @@ int plan_create_impl(gsht_plan **out, int lmax, int mmax, int spin, const double
             return fail(GSHT_EHIP, "tile colouring failed: %s", hipGetErrorString(e));
         }
         tr.mark("tile colours");
+        tr.spreading(*p);
         p->points_ok = true;
     }
     // per-column stage, then the rocFFT plans it leaves to rocFFT

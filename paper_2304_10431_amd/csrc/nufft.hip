@@ -418,9 +418,31 @@ out:  // scratch of the sort; a failed free cannot change the result
 //       544     1276     0.165 / 0.040      0.397 / 0.093
 //      2112     2049     0.074 / 0.045      0.172 / 0.115
 //      8320     8093     0.087 / 0.088      0.267 / 0.275 (2 points a tile; 25: equal)
-// so the line lies below 8320 tiles.  SPREAD_GATHER_BYTES bounds the buffers (30 KB a
-// chunk for FP64 pairs at w = 12).
+// so a grid of up to 6144 tiles of 32 x 32 cells takes the buffers.  On a larger one the
+// sum's pass over every cell costs more than clearing the grid (1.5 to 3.5 ps a cell more)
+// and the buffers some 30 ns a chunk, against 20 us (FP64; FP32 8) for every chunk that
+// the colours run one after another (the chain: the most chunks of one tile, summed over
+// the colours).  The buffers then serve only chains long enough for that:
+//     cells      tiles  chunks  chain   FP32 eps 1e-5      FP64 eps 1e-10
+//     33.7 M        81      81      4   0.089 / 0.152      0.184 / 0.186
+//     33.7 M        81     209     13   0.154 / 0.151      0.383 / 0.208
+//     33.7 M      1984    1984      4   0.075 / 0.174      0.145 / 0.265
+//     33.7 M         2    5860   5860         -            416   / 4.2
+//    134.4 M        81     209     13   0.289 / 0.544      0.667 / 0.627
+//    134.4 M      5461    5461      4   0.216 / 0.666      0.486 / 0.967
+// SPREAD_GATHER_BYTES bounds the buffers (30 KB a chunk for FP64 pairs at w = 12).
 constexpr size_t SPREAD_GATHER_TILES = 6144, SPREAD_GATHER_BYTES = (size_t)512 << 20;
+
+static bool gather_pays(const gsht_plan &p, size_t tiles, size_t chunks, int64_t chain)
+{
+    const int64_t cells = (int64_t)p.nrows * p.n2;
+    if (chain < 2 || tiles > SPREAD_GATHER_TILES)
+        return false;
+    if (cells <= (int64_t)SPREAD_GATHER_TILES * 32 * 32)
+        return true;
+    const int64_t per_link = p.prec == GSHT_F64 ? 10000000 : 2500000;
+    return (chain - 1) * per_link > cells + 16000 * (int64_t)chunks;
+}
 
 hipError_t build_tile_colors(gsht_plan &p, hipStream_t s)
 {
@@ -456,7 +478,12 @@ hipError_t build_tile_colors(gsht_plan &p, hipStream_t s)
     std::vector<int2> items;
     items.reserve(ck.size());
     p.color_start[0] = 0;
+    int64_t chain = 0;  // chunks that the colours run one after another
     for (int c = 0; c < ncol; ++c) {
+        int longest = 0;
+        for (const int2 &t : lists[(size_t)c])
+            longest = std::max(longest, t.y);
+        chain += longest;
         items.insert(items.end(), lists[(size_t)c].begin(), lists[(size_t)c].end());
         p.color_start[c + 1] = (int)items.size();
     }
@@ -469,7 +496,7 @@ hipError_t build_tile_colors(gsht_plan &p, hipStream_t s)
     if ((e = hipStreamSynchronize(s)) != hipSuccess)
         return e;
     p.ncolors = ncol;
-    if (!env && items.size() <= SPREAD_GATHER_TILES) {
+    if (!env && gather_pays(p, items.size(), ck.size(), chain)) {
         // a buffer per chunk and the first chunk of every tile, where the cap leaves room
         const size_t cells = (size_t)(p.t1 + p.w - 1) * (p.t2 + p.w - 1);
         const size_t b1 = ck.size() * cells * (p.spin ? 2 : 1) * (p.prec == GSHT_F64 ? 8 : 4);
