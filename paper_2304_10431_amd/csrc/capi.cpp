@@ -419,11 +419,14 @@ void choose_sizes(gsht_plan *p)
     p->npairs = (p->ntheta + 1) / 2;
 }
 
-// Places the three arrays of the ring starts of `band` values of m in one buffer.
-void place_starts(gsht_plan *p, void *buf, int band)
+// Places the three arrays of the ring starts of `band` values of m in one buffer: one that
+// keeps the starts of every m (resident), or one they are rebuilt in, band by band, in
+// each Legendre launch.
+void place_starts(gsht_plan *p, void *buf, int band, bool resident)
 {
     const size_t n = (size_t)band * p->leg.np;
     p->leg.band = band;
+    p->leg.resident = resident;
     p->leg.sta = (double2 *)buf;
     p->leg.stb = p->leg.sta + n;
     p->leg.stk = (int32_t *)(p->leg.sta + n * (p->spin ? 2 : 1));
@@ -438,30 +441,62 @@ void set_leg_shapes(gsht_plan *p, int syn_r, int adj_r, int adj_b)
     p->adj_nchunk = (p->npairs + 64 * adj_r - 1) / (64 * adj_r);
 }
 
+// Values of m whose ring starts fit in `bytes`, at most all of them.
+int start_band(const gsht_plan &p, size_t bytes)
+{
+    return (int)std::min<size_t>((size_t)p.mmax + 1, bytes / leg_start_bytes(p));
+}
+
 // Bytes of ring starts that the stage entry points take at most (more rings than any
 // plan has: bands of m).
 constexpr size_t kStageStartLimit = (size_t)2 << 30;
 
-// Ring starts: all m at once within start_limit bytes (0: no limit) and the device's
-// memory, otherwise the largest band that fits, down to one m.
-int alloc_starts(gsht_plan *p)
+// Ring starts of a stage entry point, in a buffer of their own: all m at once within
+// kStageStartLimit and the device's memory, otherwise the largest band that fits, down to
+// one m.
+int stage_starts(gsht_plan *p, hipStream_t s)
 {
-    p->leg.np = (p->npairs + 63) / 64 * 64;
-    const size_t per = leg_start_bytes(*p);
-    int band = p->mmax + 1;
-    if (p->start_limit)
-        band = (int)std::max<size_t>(1, std::min<size_t>((size_t)band, p->start_limit / per));
+    int band = std::max(start_band(*p, kStageStartLimit), 1);
     for (;;) {
         void *buf = nullptr;
-        const int rc = dev_alloc(p, &buf, per * (size_t)band);
+        const int rc = dev_alloc(p, &buf, leg_start_bytes(*p) * (size_t)band);
         if (rc == GSHT_OK) {
-            place_starts(p, buf, band);
-            return GSHT_OK;
+            place_starts(p, buf, band, band > p->mmax);
+            break;
         }
         if (band == 1)
             return rc;
         band = (band + 1) / 2;
     }
+    if (p->leg.resident)
+        HIP_TRY(launch_leg_starts(*p, 0, p->mmax + 1, s));
+    return GSHT_OK;
+}
+
+// Ring starts of a plan, after everything else it allocates: resident in a buffer of
+// their own where `room` bytes of the workspace cap and the device's memory hold all of
+// them.  Otherwise each Legendre launch rebuilds them in E (e_bytes), whose contents are
+// always dead then: a synthesis writes E after its Legendre step, an adjoint reads it for
+// the last time before.  E holds the starts of every m at nearly all sizes (20 or 36
+// bytes per m and ring pair against at least 5 lmax complex values per m).  Rebuilding
+// takes 2 ms at lmax 4096, spin 2, where the Legendre steps with masks that needed no
+// starts took 2.3 ms more.
+int plan_starts(gsht_plan *p, size_t room, size_t e_bytes, hipStream_t s)
+{
+    const size_t all = leg_start_bytes(*p) * ((size_t)p->mmax + 1);
+    const int band = start_band(*p, e_bytes);
+    void *buf = nullptr;
+    if ((all <= room || band < 1) && dev_alloc(p, &buf, all) == GSHT_OK) {
+        place_starts(p, buf, p->mmax + 1, true);
+        p->workspace_bytes += (int64_t)all;
+        HIP_TRY(launch_leg_starts(*p, 0, p->mmax + 1, s));
+        HIP_TRY(hipStreamSynchronize(s));  // the plan's calls may come on other streams
+        return GSHT_OK;
+    }
+    if (band < 1)
+        return GSHT_ENOMEM;
+    place_starts(p, p->E, band, false);
+    return GSHT_OK;
 }
 
 // Launch shapes of the Legendre kernels: slices of 64 ring pairs per wave, and degrees
@@ -511,7 +546,8 @@ int choose_leg_shapes(gsht_plan *p)
     return GSHT_OK;
 }
 
-// Allocate the Legendre tables and upload the start data and deconvolution tables.
+// Allocate the Legendre tables and upload the start data and, for a plan, the deconvolution
+// tables (its ring starts follow in plan_starts); a stage entry point gets its ring starts.
 int setup_legendre(gsht_plan *p, hipStream_t s, bool with_deconv)
 {
     int rc;
@@ -523,13 +559,12 @@ int setup_legendre(gsht_plan *p, hipStream_t s, bool with_deconv)
         return rc;
     p->acc = p->uprep;  // a call is a synthesis or an adjoint: one buffer serves both
     if ((rc = choose_leg_shapes(p)) != GSHT_OK) return rc;
-    if ((rc = alloc_starts(p)) != GSHT_OK) return rc;
+    p->leg.np = p->npairs;
     std::vector<StartInfo> si = make_start_info(p->lmax, p->mmax, p->spin);
     HIP_TRY(hipMemcpyAsync(p->leg.start, si.data(), sizeof(StartInfo) * si.size(),
                            hipMemcpyHostToDevice, s));
     HIP_TRY(launch_leg_tables(*p, s));
-    if (p->leg.band > p->mmax)
-        HIP_TRY(launch_leg_starts(*p, 0, p->mmax + 1, s));
+    if (!with_deconv && (rc = stage_starts(p, s)) != GSHT_OK) return rc;
     if (with_deconv) {
         std::vector<double> k1 = deconv_table(p->lmax, p->n1, p->w, p->beta, 1.0 / p->nd);
         std::vector<double> k2 = deconv_table(p->mmax, p->n2, p->w, p->beta, 1.0);
@@ -832,21 +867,20 @@ int plan_create_impl(gsht_plan **out, int lmax, int mmax, int spin, const double
     ws += (int64_t)p->ncol * p->nd * cs + (int64_t)p->ncol * p->n1 * cs;
     ws += (int64_t)p->nrows * gcols * cs + (spin ? 0 : (int64_t)p->nrows * p->n2 * rs);
     ws += npts * (16 + 4) + (p->ntiles + 1) * 4;
-    // the ring starts take what the cap leaves, at least 16 ncomp nalm bytes (the cap is
-    // checked with as much for them); under a tighter cap they are kept in bands of m
-    const int64_t least = (int64_t)p->nalm * 16 * p->ncomp;
-    if (ws + least > workspace_cap()) {
-        const int64_t want = ws + least;
+    // the cap is checked with accumulators of their own (16 ncomp nalm bytes) counted in;
+    // the ring starts take what it leaves (plan_starts)
+    const int64_t want = ws + (int64_t)p->nalm * 16 * p->ncomp, cap = workspace_cap();
+    if (want > cap) {
         delete p;
         return fail(GSHT_ENOMEM, "workspace of %lld bytes exceeds GSHT_MAX_WORKSPACE_BYTES",
                     (long long)want);
     }
-    p->start_limit = (size_t)std::max<int64_t>(workspace_cap() - ws, 1);
     std::call_once(g_fft_once, []() { rocfft_setup(); });
     tr.mark("sizes");
     if ((rc = setup_legendre(p, s, true)) != GSHT_OK) { free_plan(p); return rc; }
-    p->workspace_bytes = ws + (int64_t)(leg_start_bytes(*p) * (size_t)p->leg.band);
-    p->gather_room = (size_t)std::max<int64_t>(workspace_cap() - p->workspace_bytes, 0);
+    p->workspace_bytes = ws;
+    p->gather_room = (size_t)std::max<int64_t>(
+        cap - ws - (int64_t)(leg_start_bytes(*p) * ((size_t)p->mmax + 1)), 0);
     tr.mark("legendre tables");
     if ((rc = dev_alloc(p, &p->D, (size_t)p->ncol * p->nd * cs)) != GSHT_OK) { free_plan(p); return rc; }
     if ((rc = dev_alloc(p, &p->E, (size_t)p->ncol * p->n1 * cs)) != GSHT_OK) { free_plan(p); return rc; }
@@ -940,6 +974,12 @@ int plan_create_impl(gsht_plan **out, int lmax, int mmax, int spin, const double
     }
     p->workspace_bytes += (int64_t)wb;
     tr.mark("library FFT plans");
+    if ((rc = plan_starts(p, (size_t)std::max<int64_t>(cap - p->workspace_bytes, 0),
+                          (size_t)p->ncol * p->n1 * cs, s)) != GSHT_OK) {
+        free_plan(p);
+        return rc;
+    }
+    tr.mark(p->leg.resident ? "ring starts" : "no ring starts");
     *out = p;
     return ok();
 }
@@ -2010,7 +2050,6 @@ int gsht_legendre_rings(const void *alm, int lmax, int mmax, int spin, int nthet
     p->nd = 2 * ntheta - 2;
     p->ncol = spin ? 2 * mmax + 1 : mmax + 1;
     p->npairs = (ntheta + 1) / 2;
-    p->start_limit = kStageStartLimit;
     if ((rc = setup_legendre(p, s, false)) != GSHT_OK) { free_plan(p); return rc; }
     int rc2 = check_launch(launch_prep_alm(*p, alm, 1.0, false, s), "prep_alm");
     if (rc2 == GSHT_OK)
@@ -2111,7 +2150,6 @@ int gsht_analysis_minimal(const void *map, int lmax, int mmax, int spin, int nph
     p->nd = nd;
     p->ncol = ncol;
     p->npairs = (ntheta + 1) / 2;
-    p->start_limit = kStageStartLimit;
     if ((rc = setup_legendre(p, s, false)) != GSHT_OK) {
         free_plan(p);
         cleanup();
@@ -2150,7 +2188,6 @@ int gsht_legendre_rings_adjoint(const void *F, int lmax, int mmax, int spin, int
     p->nd = 2 * ntheta - 2;
     p->ncol = spin ? 2 * mmax + 1 : mmax + 1;
     p->npairs = (ntheta + 1) / 2;
-    p->start_limit = kStageStartLimit;
     if ((rc = setup_legendre(p, s, false)) != GSHT_OK) { free_plan(p); return rc; }
     int rc2 = check_launch(launch_leg_adjoint(*p, F, false, s), "legendre_adjoint");
     if (rc2 == GSHT_OK)
@@ -2213,16 +2250,16 @@ int gsht_legendre_rings_adjoint_noalloc(const void *F, int lmax, int mmax, int s
     p.acc = (double *)q;
     q += b_acc;
     p.leg.start = (StartInfo *)q;
-    p.leg.np = (p.npairs + 63) / 64 * 64;
-    place_starts(&p, (char *)base + kScratchBytes,
-                 (int)std::min<size_t>((size_t)mmax + 1, kStartScratchBytes / leg_start_bytes(p)));
+    p.leg.np = p.npairs;
+    const int band = start_band(p, kStartScratchBytes);
+    place_starts(&p, (char *)base + kScratchBytes, band, band > mmax);
     // start data: computed on the host, sent from a host copy kept until the next call
     g_scratch_start[dev] = make_start_info(lmax, mmax, spin);
     HIP_TRY(hipMemcpyAsync(p.leg.start, g_scratch_start[dev].data(),
                            sizeof(StartInfo) * (size_t)(mmax + 1), hipMemcpyHostToDevice, s));
     rc = check_launch(launch_leg_tables(p, s), "legendre tables");
     if (rc == GSHT_OK)
-        rc = check_launch(p.leg.band > mmax ? launch_leg_starts(p, 0, mmax + 1, s) : hipSuccess,
+        rc = check_launch(p.leg.resident ? launch_leg_starts(p, 0, mmax + 1, s) : hipSuccess,
                           "ring starts");
     if (rc == GSHT_OK)
         rc = check_launch(launch_leg_adjoint(p, F, false, s), "legendre_adjoint");

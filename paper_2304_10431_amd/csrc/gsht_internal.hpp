@@ -32,13 +32,14 @@ struct LegendreTables {
                                // spin 0: [nalm] a_l (b_l = 0)
     double *norm = nullptr;    // [nalm]  N_l
     StartInfo *start = nullptr;  // [mmax + 1]
-    // recurrence starts of every ring pair for a band of m (leg_starts_kernel): all m
-    // when they fit, otherwise rebuilt band by band within each Legendre launch
+    // recurrence starts of every ring pair for a band of m (leg_starts_kernel): all m,
+    // built once (resident), or rebuilt band by band within each Legendre launch
     double2 *sta = nullptr;    // [band][np] (p_{l-1}, p_l) of channel +s at its entry degree
     double2 *stb = nullptr;    // [band][np] channel -s (spin > 0)
     int32_t *stk = nullptr;    // [band][np] entry blocks, channel +s low half, -s high half
-    int np = 0;                // ring pairs, rounded up to whole waves
+    int np = 0;                // ring pairs
     int band = 0;              // values of m the buffers hold
+    bool resident = false;     // the buffers hold the starts of every m
 };
 
 // Entry block of a channel that stays below the threshold up to lmax.
@@ -149,7 +150,6 @@ struct gsht_plan {
     int syn_nchunk = 0;  // chunks of 64 * syn_r ring pairs
     int adj_nchunk = 0;  // chunks of 64 * adj_r ring pairs
     int64_t workspace_bytes = 0;
-    size_t start_limit = 0;  // bytes the ring starts may take (0: no limit)
     // device tables
     gsht::LegendreTables leg;
     double *uprep = nullptr;   // prepared coefficients [nalm][2 or 4]
@@ -169,7 +169,7 @@ struct gsht_plan {
     int2 *tile_items = nullptr;             // (first chunk, number of chunks) per tile
     // work buffers
     void *D = nullptr;     // [ncol][nd] complex: doubled meridians (colmode 2: the rings alone)
-    void *E = nullptr;     // [ncol][n1] complex
+    void *E = nullptr;     // [ncol][n1] complex (idle during the Legendre step: see place_starts)
     void *G = nullptr;     // complex grid [nrows][n2] (spin > 0) or half spectrum [nrows][n2/2+1]
     void *g = nullptr;     // real grid [nrows][n2] (spin 0 only)
     double *acc = nullptr; // adjoint accumulators [nalm][2 * ncomp] (the uprep buffer)
@@ -213,8 +213,8 @@ hipError_t launch_leg_tables(const gsht_plan &p, hipStream_t s);
 // ring starts of the m values m0 .. m0 + nm - 1 into the plan's buffers
 hipError_t launch_leg_starts(const gsht_plan &p, int m0, int nm, hipStream_t s);
 size_t leg_start_bytes(const gsht_plan &p);  // bytes of the starts of one m
-// Runs f(starts, nm) over the plan's bands of m, rebuilding the starts of each band
-// first where the buffers do not hold all of them.
+// Runs f(starts, nm) over the plan's bands of m, building the starts of each band first
+// where they are not resident.
 template <typename F>
 hipError_t leg_bands(const gsht_plan &p, hipStream_t s, F f);
 // mscale multiplies the coefficients (prep) or results (finalize) of every m > 0:
@@ -311,7 +311,7 @@ hipError_t leg_bands(const gsht_plan &p, hipStream_t s, F f)
 {
     for (int m0 = 0; m0 <= p.mmax; m0 += p.leg.band) {
         const int nm = p.mmax + 1 - m0 < p.leg.band ? p.mmax + 1 - m0 : p.leg.band;
-        if (p.leg.band <= p.mmax) {
+        if (!p.leg.resident) {
             const hipError_t e = launch_leg_starts(p, m0, nm, s);
             if (e != hipSuccess)
                 return e;

@@ -70,7 +70,7 @@ __device__ inline void rescale_channel(double &p0, double &p1, int &ex)
 
 // One lane per (m, ring pair), the pair's position counted from the equator.  Runs the
 // recurrence with exponent offsets through the degrees where the values are negligible;
-// done once per plan (or per band of m), 2 ms at lmax 4096.
+// done once per plan (or in each Legendre launch), 2 ms at lmax 4096.
 template <bool SPIN>
 __global__ __launch_bounds__(64) void leg_starts_kernel(
     const double *__restrict__ ab, const StartInfo *__restrict__ st, int lmax, int m0, int ntheta,
@@ -125,6 +125,8 @@ __global__ __launch_bounds__(64) void leg_starts_kernel(
         if (SPIN && wb)
             rescale_channel(b0, b1, eb);
     }
+    if (e >= np)
+        return;
     sta[idx] = va;
     if (SPIN)
         stb[idx] = vb;
@@ -138,7 +140,7 @@ size_t leg_start_bytes(const gsht_plan &p)
 
 hipError_t launch_leg_starts(const gsht_plan &p, int m0, int nm, hipStream_t s)
 {
-    dim3 blk(64), grd(p.leg.np / 64, nm);
+    dim3 blk(64), grd((p.leg.np + 63) / 64, nm);
     if (p.spin)
         hipLaunchKernelGGL(leg_starts_kernel<true>, grd, blk, 0, s, p.leg.ab, p.leg.start, p.lmax,
                            m0, p.ntheta, p.npairs, p.leg.np, p.leg.sta, p.leg.stb, p.leg.stk);

@@ -506,7 +506,8 @@ __global__ __launch_bounds__(64 * adj_wmax<NB>()) void leg_adjoint_mfma_kernel(
 #pragma unroll 1
         for (int sl = w; sl < nslice; sl += W) {
             const int e = 64 * sl + lane;
-            const RingStart en = ring_start(tab, m, e, SPIN);
+            const RingStart en =
+                e < npairs ? ring_start(tab, m, e, SPIN) : RingStart{START_NEVER, START_NEVER};
             const int k0 = (lb - l0) / START_DEG;  // entry blocks k0 .. k0 + BK / 8 - 1
             if (!__any(min(en.ka, en.kb) < k0 + BK / START_DEG))
                 continue;  // every ring of the slice enters later
