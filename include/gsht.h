@@ -401,7 +401,11 @@ typedef struct {
     int tile1, tile2;   /* tile size in grid cells (rows, columns) */
     int ntile1, ntile2; /* tiles per dimension; tile key = (row / tile1) * ntile2 + col / tile2 */
     int64_t nchunks;    /* work items of the interpolation / spreading kernels */
-    int64_t workspace_bytes;
+    int64_t workspace_bytes; /* tables, work buffers and sorted points held by the plan, with
+                           the patch buffers of the spreading (up to 512 MiB, see
+                           spread_colors), which gsht_plan_set_points allocates anew;
+                           buffers of several maps at once, taken on their first use, are
+                           not counted */
     int column_mode;    /* per-column FFT stage: 2 = doubled FFT, deconvolution and theta
                            FFT in one kernel per column (column in LDS), 1 = doubled FFT and
                            deconvolution fused with a separate theta FFT, 0 = separate

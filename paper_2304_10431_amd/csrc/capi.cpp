@@ -879,8 +879,8 @@ int plan_create_impl(gsht_plan **out, int lmax, int mmax, int spin, const double
     tr.mark("sizes");
     if ((rc = setup_legendre(p, s, true)) != GSHT_OK) { free_plan(p); return rc; }
     p->workspace_bytes = ws;
-    p->gather_room = (size_t)std::max<int64_t>(
-        cap - ws - (int64_t)(leg_start_bytes(*p) * ((size_t)p->mmax + 1)), 0);
+    p->ws_cap = cap;
+    p->spreads = (dirs & DIR_ADJOINT) != 0;
     tr.mark("legendre tables");
     if ((rc = dev_alloc(p, &p->D, (size_t)p->ncol * p->nd * cs)) != GSHT_OK) { free_plan(p); return rc; }
     if ((rc = dev_alloc(p, &p->E, (size_t)p->ncol * p->n1 * cs)) != GSHT_OK) { free_plan(p); return rc; }
@@ -904,14 +904,6 @@ int plan_create_impl(gsht_plan **out, int lmax, int mmax, int spin, const double
                         (long long)ninv);
         }
         tr.mark("bin sort");
-        e = build_tile_colors(*p, s);
-        if (e != hipSuccess) {
-            free_plan(p);
-            return fail(GSHT_EHIP, "tile colouring failed: %s", hipGetErrorString(e));
-        }
-        tr.mark("tile colours");
-        tr.spreading(*p);
-        p->points_ok = true;
     }
     // per-column stage, then the rocFFT plans it leaves to rocFFT
     if (p->prec == GSHT_F64) {  // interior-tap weight polynomials (GSHT_ES_POLY=0: off)
@@ -980,6 +972,14 @@ int plan_create_impl(gsht_plan **out, int lmax, int mmax, int spin, const double
         return rc;
     }
     tr.mark(p->leg.resident ? "ring starts" : "no ring starts");
+    const hipError_t ce = build_tile_colors(*p, s);
+    if (ce != hipSuccess) {
+        free_plan(p);
+        return fail(GSHT_EHIP, "tile colouring failed: %s", hipGetErrorString(ce));
+    }
+    p->points_ok = true;
+    tr.mark("tile colours");
+    tr.spreading(*p);
     *out = p;
     return ok();
 }
@@ -1217,6 +1217,8 @@ int gsht_plan_set_points(gsht_plan *p, const double *theta, const double *phi, i
     p->ncolors = 0;
     p->nchunks = 0;
     p->tile_chunk = nullptr;
+    p->workspace_bytes -= p->patch_bytes;
+    p->patch_bytes = 0;
     for (void **q : {(void **)&p->chunks, (void **)&p->tile_items, &p->patches}) {
         if (!*q)
             continue;

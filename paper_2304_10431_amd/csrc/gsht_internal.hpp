@@ -150,6 +150,7 @@ struct gsht_plan {
     int syn_nchunk = 0;  // chunks of 64 * syn_r ring pairs
     int adj_nchunk = 0;  // chunks of 64 * adj_r ring pairs
     int64_t workspace_bytes = 0;
+    int64_t ws_cap = INT64_MAX;  // what they may come to
     // device tables
     gsht::LegendreTables leg;
     double *uprep = nullptr;   // prepared coefficients [nalm][2 or 4]
@@ -164,7 +165,8 @@ struct gsht_plan {
     int ncolors = 0;
     void *patches = nullptr;                // a patch buffer per chunk (grids of few chunks)
     int32_t *tile_chunk = nullptr;          // [ntiles + 1] first chunk of every tile, with patches
-    size_t gather_room = 0;                 // bytes the patch buffers may take
+    int64_t patch_bytes = 0;                // bytes of both
+    bool spreads = true;                    // false: a one-shot synthesis
     int color_start[7] = {};                // items of colour c: [color_start[c], color_start[c+1])
     int2 *tile_items = nullptr;             // (first chunk, number of chunks) per tile
     // work buffers

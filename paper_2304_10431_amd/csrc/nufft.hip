@@ -430,7 +430,8 @@ out:  // scratch of the sort; a failed free cannot change the result
 //     33.7 M         2    5860   5860         -            416   / 4.2
 //    134.4 M        81     209     13   0.289 / 0.544      0.667 / 0.627
 //    134.4 M      5461    5461      4   0.216 / 0.666      0.486 / 0.967
-// SPREAD_GATHER_BYTES bounds the buffers (30 KB a chunk for FP64 pairs at w = 12).
+// SPREAD_GATHER_BYTES bounds the buffers (30 KB a chunk for FP64 pairs at w = 12),
+// and they only take what the workspace cap leaves after everything else.
 constexpr size_t SPREAD_GATHER_TILES = 6144, SPREAD_GATHER_BYTES = (size_t)512 << 20;
 
 static bool gather_pays(const gsht_plan &p, size_t tiles, size_t chunks, int64_t chain)
@@ -496,12 +497,12 @@ hipError_t build_tile_colors(gsht_plan &p, hipStream_t s)
     if ((e = hipStreamSynchronize(s)) != hipSuccess)
         return e;
     p.ncolors = ncol;
-    if (!env && gather_pays(p, items.size(), ck.size(), chain)) {
+    if (!env && p.spreads && gather_pays(p, items.size(), ck.size(), chain)) {
         // a buffer per chunk and the first chunk of every tile, where the cap leaves room
         const size_t cells = (size_t)(p.t1 + p.w - 1) * (p.t2 + p.w - 1);
         const size_t b1 = ck.size() * cells * (p.spin ? 2 : 1) * (p.prec == GSHT_F64 ? 8 : 4);
         const size_t b2 = sizeof(int32_t) * (size_t)(p.ntiles + 1);
-        if (b1 + b2 > std::min(p.gather_room, SPREAD_GATHER_BYTES))
+        if (b1 + b2 > SPREAD_GATHER_BYTES || (int64_t)(b1 + b2) > p.ws_cap - p.workspace_bytes)
             return hipSuccess;
         std::vector<int32_t> first((size_t)p.ntiles + 1, 0);
         for (const int4 &k : ck)
@@ -514,6 +515,8 @@ hipError_t build_tile_colors(gsht_plan &p, hipStream_t s)
             return hipSuccess;  // the colours serve without it
         }
         p.allocations.push_back(buf);
+        p.patch_bytes = (int64_t)(b1 + b2);
+        p.workspace_bytes += p.patch_bytes;
         if ((e = hipMemcpyAsync((char *)buf + b1, first.data(), b2, hipMemcpyHostToDevice, s)) !=
                 hipSuccess ||
             (e = hipStreamSynchronize(s)) != hipSuccess)

@@ -95,3 +95,51 @@ def test_reported_bytes_within_the_cap(G, monkeypatch, lmax, spin, prec, eps):
             assert got <= max(c, bare)
     assert bytes_at(full) == full
     sys.stdout.flush()
+
+
+@pytest.mark.parametrize("lmax,spin,prec,eps", [(200, 2, "f64", 1e-10), (150, 0, "f32", 1e-5)])
+def test_patch_buffers_are_counted(G, monkeypatch, capfd, lmax, spin, prec, eps):
+    """The spreading's patch buffers are part of what a plan reports, follow its points,
+    and take only what the cap leaves; a one-shot synthesis, which never spreads, has none."""
+    print("patch bytes", lmax, spin, prec, flush=True)
+    rng = np.random.default_rng(9)
+    pts = [tuple(torch.from_numpy(x).cuda() for x in wl.uniform_sphere(n, rng))
+           for n in (5000, 800)]
+    monkeypatch.setenv("GSHT_PLAN_TRACE", "1")
+
+    def make(k):
+        capfd.readouterr()
+        plan = G.Plan(*pts[k], lmax, lmax, spin, eps, prec)
+        return plan, capfd.readouterr().err
+
+    def patch_bytes(inf):
+        cells = (inf["tile1"] + inf["w"] - 1) * (inf["tile2"] + inf["w"] - 1)
+        value = (8 if prec == "f64" else 4) * (2 if spin else 1)
+        return inf["nchunks"] * cells * value + 4 * (inf["ntile1"] * inf["ntile2"] + 1)
+
+    plan, err = make(0)
+    assert "spreading by patch buffers" in err
+    inf = plan.info()
+    total, bare = inf["workspace_bytes"], inf["workspace_bytes"] - patch_bytes(inf)
+    for k in (1, 0):
+        plan.set_points(*pts[k])
+        inf = plan.info()
+        assert inf["workspace_bytes"] == bare + patch_bytes(inf)
+    plan.close()
+    for cap, flush in ((total - 1, "tile colours"), (total, "patch buffers")):
+        monkeypatch.setenv("GSHT_MAX_WORKSPACE_BYTES", str(cap))
+        plan, err = make(0)
+        assert "spreading by " + flush in err
+        assert plan.info()["workspace_bytes"] == (total if flush == "patch buffers" else bare)
+        plan.set_points(*pts[1])  # fewer chunks: room again
+        assert plan.info()["workspace_bytes"] == bare + patch_bytes(plan.info())
+        plan.close()
+    monkeypatch.delenv("GSHT_MAX_WORKSPACE_BYTES")
+    cdt = torch.complex128 if prec == "f64" else torch.complex64
+    a = torch.from_numpy(wl.gaussian_alm(lmax, lmax, spin, rng)).cuda().to(cdt)
+    capfd.readouterr()
+    m = G.synth_general(a, *pts[0], lmax, lmax, spin, eps, prec)
+    assert "spreading by tile colours" in capfd.readouterr().err
+    G.adjoint_synth_general(m, *pts[0], lmax, lmax, spin, eps, prec)
+    assert "spreading by patch buffers" in capfd.readouterr().err
+    sys.stdout.flush()
