@@ -771,6 +771,7 @@ int setup_columns(gsht_plan *p, hipStream_t s)
             return fail(GSHT_EHIP, "column stage LDS size refused: %s", hipGetErrorString(he));
     }
     p->colmode = mode;
+    p->ds = mode == 2 ? (p->ntheta + 7) / 8 * 8 : p->nd;  // whole cache lines
     int rc;
     if (mode >= 1 && (rc = setup_colfft(p, p->cf_d, p->nd, s)) != GSHT_OK) return rc;
     if (mode == 2) {
@@ -878,11 +879,13 @@ int plan_create_impl(gsht_plan **out, int lmax, int mmax, int spin, const double
     std::call_once(g_fft_once, []() { rocfft_setup(); });
     tr.mark("sizes");
     if ((rc = setup_legendre(p, s, true)) != GSHT_OK) { free_plan(p); return rc; }
-    p->workspace_bytes = ws;
     p->ws_cap = cap;
     p->spreads = (dirs & DIR_ADJOINT) != 0;
     tr.mark("legendre tables");
-    if ((rc = dev_alloc(p, &p->D, (size_t)p->ncol * p->nd * cs)) != GSHT_OK) { free_plan(p); return rc; }
+    if ((rc = setup_columns(p, s)) != GSHT_OK) { free_plan(p); return rc; }
+    p->workspace_bytes = ws - (int64_t)p->ncol * (p->nd - p->ds) * (int64_t)cs;
+    tr.mark("column setup");
+    if ((rc = dev_alloc(p, &p->D, (size_t)p->ncol * p->ds * cs)) != GSHT_OK) { free_plan(p); return rc; }
     if ((rc = dev_alloc(p, &p->E, (size_t)p->ncol * p->n1 * cs)) != GSHT_OK) { free_plan(p); return rc; }
     if ((rc = dev_alloc(p, &p->G, (size_t)p->nrows * gcols * cs)) != GSHT_OK) { free_plan(p); return rc; }
     if (!spin && (rc = dev_alloc(p, &p->g, (size_t)p->nrows * p->n2 * rs)) != GSHT_OK) { free_plan(p); return rc; }
@@ -905,7 +908,6 @@ int plan_create_impl(gsht_plan **out, int lmax, int mmax, int spin, const double
         }
         tr.mark("bin sort");
     }
-    // per-column stage, then the rocFFT plans it leaves to rocFFT
     if (p->prec == GSHT_F64) {  // interior-tap weight polynomials (GSHT_ES_POLY=0: off)
         const char *ep = getenv("GSHT_ES_POLY");
         std::vector<double> coef;
@@ -924,8 +926,7 @@ int plan_create_impl(gsht_plan **out, int lmax, int mmax, int spin, const double
         }
     }
     tr.mark("kernel polynomials");
-    if ((rc = setup_columns(p, s)) != GSHT_OK) { free_plan(p); return rc; }
-    tr.mark("column setup");
+    // the FFTs that the column stage leaves to rocFFT
     const size_t nd = p->nd, n1 = p->n1, n2 = p->n2;
     rc = GSHT_OK;
     auto add = [&](int dir, FFTPlan &f, rocfft_transform_type type, rocfft_result_placement place,
@@ -1359,7 +1360,7 @@ int gsht_plan_autotune(gsht_plan *p, void *hip_stream)
         return fail(GSHT_EINVAL, "plan has no Legendre buffers");
     hipStream_t s = (hipStream_t)hip_stream;
     HIP_TRY(launch_zero(p->uprep, sizeof(double) * 2 * p->ncomp * (size_t)p->nalm, s));
-    HIP_TRY(launch_zero(p->D, (size_t)p->ncol * p->nd * csize(p->prec), s));
+    HIP_TRY(launch_zero(p->D, (size_t)p->ncol * p->ds * csize(p->prec), s));
     hipEvent_t e0, e1;
     HIP_TRY(hipEventCreate(&e0));
     if (hipEventCreate(&e1) != hipSuccess) {
@@ -1441,7 +1442,7 @@ static int setup_mfma(gsht_plan *p, hipStream_t s)
     }
     const size_t nt = p->spin ? 2 : 1;
     const size_t tile_bytes = (size_t)nblk * nt * 2 /* column blocks */ * 2 /* hi, lo */ * 64 * 16;
-    const size_t dstride = (size_t)p->ncol * p->nd;
+    const size_t dstride = (size_t)p->ncol * p->ds;
     if ((rc = dev_alloc(p, &p->mfma_boff, sizeof(int64_t) * boff.size())) != GSHT_OK) return rc;
     if ((rc = dev_alloc(p, &p->mfma_scale, sizeof(float) * 16 * boff.size())) != GSHT_OK) return rc;
     if ((rc = dev_alloc(p, &p->Dmfma, 16 * dstride * csize(p->prec))) != GSHT_OK) return rc;
@@ -1500,7 +1501,7 @@ int gsht_plan_adjoint_many(gsht_plan *p, int nmaps, const void *map, void *alm, 
     const size_t cs = csize(p->prec);
     const size_t astride = (size_t)p->ncomp * p->nalm * cs;
     const size_t mstride = (size_t)p->ncomp * p->npts * (cs / 2);
-    const size_t dstride = (size_t)p->ncol * p->nd;
+    const size_t dstride = (size_t)p->ncol * p->ds;
     const size_t nr = (size_t)2 * p->ncomp;
     int rc;
     const bool mfma = use_mfma_adj(p);
@@ -1555,7 +1556,7 @@ int gsht_plan_synth_many(gsht_plan *p, int nmaps, const void *alm, void *map, vo
     const size_t cs = csize(p->prec);
     const size_t astride = (size_t)p->ncomp * p->nalm * cs;
     const size_t mstride = (size_t)p->ncomp * p->npts * (cs / 2);
-    const size_t dstride = (size_t)p->ncol * p->nd;  // complex elements per map
+    const size_t dstride = (size_t)p->ncol * p->ds;  // complex elements per map
     int rc;
     const bool mfma = use_mfma(p);
     for (int k = 0; k < nmaps;) {
@@ -2049,7 +2050,7 @@ int gsht_legendre_rings(const void *alm, int lmax, int mmax, int spin, int nthet
     p->ncomp = spin ? 2 : 1;
     p->nalm = (int64_t)(mmax + 1) * (lmax + 1) - (int64_t)mmax * (mmax + 1) / 2;
     p->ntheta = ntheta;
-    p->nd = 2 * ntheta - 2;
+    p->ds = p->nd = 2 * ntheta - 2;
     p->ncol = spin ? 2 * mmax + 1 : mmax + 1;
     p->npairs = (ntheta + 1) / 2;
     if ((rc = setup_legendre(p, s, false)) != GSHT_OK) { free_plan(p); return rc; }
@@ -2149,7 +2150,7 @@ int gsht_analysis_minimal(const void *map, int lmax, int mmax, int spin, int nph
     p->ncomp = spin ? 2 : 1;
     p->nalm = (int64_t)(mmax + 1) * (lmax + 1) - (int64_t)mmax * (mmax + 1) / 2;
     p->ntheta = ntheta;
-    p->nd = nd;
+    p->ds = p->nd = nd;
     p->ncol = ncol;
     p->npairs = (ntheta + 1) / 2;
     if ((rc = setup_legendre(p, s, false)) != GSHT_OK) {
@@ -2187,7 +2188,7 @@ int gsht_legendre_rings_adjoint(const void *F, int lmax, int mmax, int spin, int
     p->ncomp = spin ? 2 : 1;
     p->nalm = (int64_t)(mmax + 1) * (lmax + 1) - (int64_t)mmax * (mmax + 1) / 2;
     p->ntheta = ntheta;
-    p->nd = 2 * ntheta - 2;
+    p->ds = p->nd = 2 * ntheta - 2;
     p->ncol = spin ? 2 * mmax + 1 : mmax + 1;
     p->npairs = (ntheta + 1) / 2;
     if ((rc = setup_legendre(p, s, false)) != GSHT_OK) { free_plan(p); return rc; }
@@ -2219,7 +2220,7 @@ int gsht_legendre_rings_adjoint_noalloc(const void *F, int lmax, int mmax, int s
     p.ncomp = spin ? 2 : 1;
     p.nalm = (int64_t)(mmax + 1) * (lmax + 1) - (int64_t)mmax * (mmax + 1) / 2;
     p.ntheta = ntheta;
-    p.nd = 2 * ntheta - 2;
+    p.ds = p.nd = 2 * ntheta - 2;
     p.ncol = spin ? 2 * mmax + 1 : mmax + 1;
     p.npairs = (ntheta + 1) / 2;
     auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };

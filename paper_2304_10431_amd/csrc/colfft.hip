@@ -298,7 +298,7 @@ __host__ __device__ inline int col_half_lds_n(int nd, int nh) { return nd > nh ?
 
 struct ColArgs {
     const double *kf1, *kf2;
-    int lmax, mmax, spin, ncol, nd, n1, nrows, a_min;
+    int lmax, mmax, spin, ncol, nd, ds, n1, nrows, a_min;
 };
 
 __device__ inline int col_m(const ColArgs &a, int col) { return a.spin ? col - a.mmax : col; }
@@ -373,8 +373,7 @@ __device__ inline void load_rows(const C *ec, int i, C &ev, C &od, const ColArgs
 // m + 1 one is even and one odd, and so are their transforms (the deconvolution in theta
 // is even in k): the two run as one complex transform z = f_m + f_{m+1} and separate at
 // the end by f_m[a] = (z[a] + sigma_m z[-a]) / 2, f_{m+1}[a] = (z[a] - sigma_m z[-a]) / 2.
-// D then holds the ntheta rings alone, not the doubled meridian (the first ntheta entries
-// of each column of stride nd).  Half the transforms and half the traffic of D; at lmax
+// D then holds the ntheta rings alone, not the doubled meridian.  Half the transforms and half the traffic of D; at lmax
 // 4096, sigma 2: FP64 1.90 -> 1.12 ms forward, 1.80 -> 1.18 ms adjoint (sigma 1.5, FP32:
 // 0.90 -> 0.48 and 0.96 -> 0.59 ms).
 //
@@ -400,7 +399,7 @@ __global__ __launch_bounds__(NT, COL_HALF_WAVES) void column_fwd_half_kernel(
     const T sg = ((a.spin + m0) & 1) ? (T)-1 : (T)1;
     const double f0 = 0.5 * a.kf2[m0 < 0 ? -m0 : m0];
     const double f1 = two ? 0.5 * a.kf2[m0 + 1 < 0 ? -(m0 + 1) : m0 + 1] : 0.0;
-    const C *d0 = D + (size_t)c0 * a.nd, *d1 = d0 + a.nd;
+    const C *d0 = D + (size_t)c0 * a.ds, *d1 = d0 + a.ds;
     C *e0 = E + (size_t)c0 * a.n1, *e1 = e0 + a.n1;
     const int half = a.nd / 2;
     for (int i = tid; i <= half; i += NT) {
@@ -526,7 +525,7 @@ __global__ __launch_bounds__(NT, COL_HALF_WAVES) void column_adj_half_kernel(
     const double f0 = 0.5 * a.kf2[m0 < 0 ? -m0 : m0];
     const double f1 = two ? 0.5 * a.kf2[m0 + 1 < 0 ? -(m0 + 1) : m0 + 1] : 0.0;
     const C *e0 = E + (size_t)c0 * a.n1, *e1 = e0 + a.n1;
-    C *d0 = D + (size_t)c0 * a.nd, *d1 = d0 + a.nd;
+    C *d0 = D + (size_t)c0 * a.ds, *d1 = d0 + a.ds;
     // theta frequency k of output i (|k| <= lmax contributes) and its residue mod nh
     auto freq = [&](int i, int &k, int &kh) {
         k = (i <= a.nd / 2) ? i : i - a.nd;
@@ -711,6 +710,7 @@ ColArgs col_args(const gsht_plan &p)
     a.spin = p.spin;
     a.ncol = p.ncol;
     a.nd = p.nd;
+    a.ds = p.ds;
     a.n1 = p.n1;
     a.nrows = p.nrows;
     a.a_min = p.a_min;

@@ -144,6 +144,7 @@ struct gsht_plan {
     int tile_req = 0;      // requested tile edge (0: the default 32)
     int64_t ntiles = 0, nchunks = 0;
     int ncol = 0, npairs = 0;
+    int ds = 0;          // entries per column of D: nd, or (colmode 2) the rings, padded
     int syn_r = 1;       // ring pairs per lane, Legendre synthesis (slices of 64)
     int adj_r = 1;       // ring pairs per lane, Legendre adjoint
     int adj_b = 8;       // degrees per reduction block of the adjoint
@@ -170,15 +171,15 @@ struct gsht_plan {
     int color_start[7] = {};                // items of colour c: [color_start[c], color_start[c+1])
     int2 *tile_items = nullptr;             // (first chunk, number of chunks) per tile
     // work buffers
-    void *D = nullptr;     // [ncol][nd] complex: doubled meridians (colmode 2: the rings alone)
+    void *D = nullptr;     // [ncol][ds] complex: doubled meridians (colmode 2: the rings alone)
     void *E = nullptr;     // [ncol][n1] complex (idle during the Legendre step: see place_starts)
     void *G = nullptr;     // complex grid [nrows][n2] (spin > 0) or half spectrum [nrows][n2/2+1]
     void *g = nullptr;     // real grid [nrows][n2] (spin 0 only)
     double *acc = nullptr; // adjoint accumulators [nalm][2 * ncomp] (the uprep buffer)
     double *umulti = nullptr;  // several-map coefficients [nalm][4][2 or 4] (on first use)
-    void *Dmulti = nullptr;    // several-map doubled columns [4][ncol][nd] (on first use)
+    void *Dmulti = nullptr;    // columns of several maps, [4] as D (on first use)
     // matrix-core synthesis of up to 16 maps (FP32 plans, on first use)
-    void *Dmfma = nullptr;         // doubled columns [16][ncol][nd]
+    void *Dmfma = nullptr;         // columns, [16] as D
     void *mfma_tiles = nullptr;    // FP16 coefficient tiles (16 maps)
     int64_t *mfma_boff = nullptr;  // [mmax + 1] first tile block of each m
     float *mfma_scale = nullptr;   // [mmax + 1][16] output scales

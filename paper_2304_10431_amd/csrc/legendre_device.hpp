@@ -274,7 +274,8 @@ __device__ inline void store_c(typename cplxk<T>::type *p, double re, double im)
 }
 
 // Ring value and, with dbl and for interior rings, its doubled mirror with sign ms.  (A
-// plan whose column stage takes pairs of columns wants the rings alone.)
+// plan whose column stage takes pairs of columns wants the rings alone; nd is then only
+// the stride of its columns.)
 template <typename T>
 __device__ inline void put_ring(typename cplxk<T>::type *col, int j, int ntheta, int nd, int dbl,
                                 double ms, double re, double im)

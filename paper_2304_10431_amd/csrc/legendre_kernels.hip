@@ -368,7 +368,7 @@ static void synth_launch(const gsht_plan &p, const RingStarts &tab, int nm, void
     dim3 blk(64), grd(xcd_grid(nm, p.syn_nchunk));
 #define GSHT_LEG_SYNTH(T, SP, G, C)                                                              \
     hipLaunchKernelGGL((leg_synth_kernel<T, SP, R, G>), grd, blk, 0, s, p.leg.ab, p.uprep,       \
-                       p.leg.start, tab, p.lmax, tab.m0 + nm, p.mmax, p.spin, p.ntheta, p.nd,     \
+                       p.leg.start, tab, p.lmax, tab.m0 + nm, p.mmax, p.spin, p.ntheta, p.ds,     \
                        p.colmode != 2, p.npairs, p.syn_nchunk, (C *)Dout)
     if (p.prec == GSHT_F64) {
         if (p.spin && grad) GSHT_LEG_SYNTH(double, true, true, double2);
@@ -489,7 +489,7 @@ static void synth_multi_launch(const gsht_plan &p, const RingStarts &tab, int nm
     dim3 blk(64), grd(xcd_grid(nm, nchunk));
 #define GSHT_LEG_SYNTH_M(T, SP, C)                                                               \
     hipLaunchKernelGGL((leg_synth_multi_kernel<T, SP, R, NM>), grd, blk, 0, s, p.leg.ab, u,      \
-                       p.leg.start, tab, p.lmax, tab.m0 + nm, p.mmax, p.spin, p.ntheta, p.nd,     \
+                       p.leg.start, tab, p.lmax, tab.m0 + nm, p.mmax, p.spin, p.ntheta, p.ds,     \
                        p.colmode != 2, p.npairs, nchunk, dstride, (C *)Dout)
     if (p.prec == GSHT_F64) {
         if (p.spin) GSHT_LEG_SYNTH_M(double, true, double2);
@@ -866,7 +866,7 @@ static void adj_launch(const gsht_plan &p, const RingStarts &tab, int nm, const 
 #define GSHT_LEG_ADJ(T, SP, G, C)                                                                \
     hipLaunchKernelGGL((leg_adjoint_kernel<T, SP, R, B, G>), grd, blk, 0, s, p.leg.ab,           \
                        p.leg.start, tab, (const C *)Din, p.lmax, tab.m0 + nm, p.mmax, p.spin,     \
-                       p.ntheta, p.nd, p.colmode != 2, p.npairs, p.adj_nchunk, p.acc)
+                       p.ntheta, p.ds, p.colmode != 2, p.npairs, p.adj_nchunk, p.acc)
     if (p.prec == GSHT_F64) {
         if (p.spin && grad) GSHT_LEG_ADJ(double, true, true, double2);
         else if (p.spin) GSHT_LEG_ADJ(double, true, false, double2);

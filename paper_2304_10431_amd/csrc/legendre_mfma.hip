@@ -265,7 +265,7 @@ hipError_t launch_leg_synth_mfma(const gsht_plan &p, int nm, const void *Bt, con
 #define GSHT_LEG_MFMA(SP, NCB)                                                                   \
     hipLaunchKernelGGL((leg_synth_mfma_kernel<SP, NCB>), grd, blk, 0, s, p.leg.ab, p.leg.start,  \
                        tab, boff, (const u32x4_t *)Bt, oscale, nm, p.lmax, tab.m0 + n, p.mmax,    \
-                       p.spin, p.ntheta, p.nd, p.colmode != 2, p.npairs, nchunk, dstride, (float2 *)Dout)
+                       p.spin, p.ntheta, p.ds, p.colmode != 2, p.npairs, nchunk, dstride, (float2 *)Dout)
     return leg_bands(p, s, [&](const RingStarts &tab, int n) {
         dim3 blk(64), grd(xcd_grid(n, nchunk));
         if (p.spin) {
@@ -675,11 +675,11 @@ hipError_t launch_prep_adj_mfma(const gsht_plan &p, int nm, const void *Din, siz
     dim3 blk(256), grd(p.mmax + 1);
     if (nm > 8)
         hipLaunchKernelGGL(prep_adj_mfma_kernel<4>, grd, blk, 0, s, (const float2 *)Din, dstride,
-                           p.mmax, p.spin, p.ntheta, p.nd, p.colmode != 2, p.npairs, nslice, nm, (u32x4_t *)tiles,
+                           p.mmax, p.spin, p.ntheta, p.ds, p.colmode != 2, p.npairs, nslice, nm, (u32x4_t *)tiles,
                            oscale);
     else
         hipLaunchKernelGGL(prep_adj_mfma_kernel<2>, grd, blk, 0, s, (const float2 *)Din, dstride,
-                           p.mmax, p.spin, p.ntheta, p.nd, p.colmode != 2, p.npairs, nslice, nm, (u32x4_t *)tiles,
+                           p.mmax, p.spin, p.ntheta, p.ds, p.colmode != 2, p.npairs, nslice, nm, (u32x4_t *)tiles,
                            oscale);
     return hipGetLastError();
 }
