@@ -771,7 +771,7 @@ int setup_columns(gsht_plan *p, hipStream_t s)
             return fail(GSHT_EHIP, "column stage LDS size refused: %s", hipGetErrorString(he));
     }
     p->colmode = mode;
-    p->ds = mode == 2 ? (p->ntheta + 7) / 8 * 8 : p->nd;  // whole cache lines
+    p->ds = mode == 2 ? std::min((p->ntheta + 15) / 16 * 16, p->nd) : p->nd;  // whole cache lines
     int rc;
     if (mode >= 1 && (rc = setup_colfft(p, p->cf_d, p->nd, s)) != GSHT_OK) return rc;
     if (mode == 2) {
