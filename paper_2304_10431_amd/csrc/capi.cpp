@@ -490,7 +490,6 @@ int plan_starts(gsht_plan *p, size_t room, size_t e_bytes, hipStream_t s)
         place_starts(p, buf, p->mmax + 1, true);
         p->workspace_bytes += (int64_t)all;
         HIP_TRY(launch_leg_starts(*p, 0, p->mmax + 1, s));
-        HIP_TRY(hipStreamSynchronize(s));  // the plan's calls may come on other streams
         return GSHT_OK;
     }
     if (band < 1)
@@ -546,9 +545,9 @@ int choose_leg_shapes(gsht_plan *p)
     return GSHT_OK;
 }
 
-// Allocate the Legendre tables and upload the start data and, for a plan, the deconvolution
-// tables (its ring starts follow in plan_starts); a stage entry point gets its ring starts.
-int setup_legendre(gsht_plan *p, hipStream_t s, bool with_deconv)
+// Allocate the Legendre tables and start filling them.  si is copied from on s: it must
+// outlive that.
+int setup_legendre(gsht_plan *p, std::vector<StartInfo> &si, hipStream_t s)
 {
     int rc;
     if ((rc = dev_alloc(p, &p->leg.ab, sizeof(double) * (p->spin ? 2 : 1) * (size_t)p->nalm)) != GSHT_OK) return rc;
@@ -560,22 +559,35 @@ int setup_legendre(gsht_plan *p, hipStream_t s, bool with_deconv)
     p->acc = p->uprep;  // a call is a synthesis or an adjoint: one buffer serves both
     if ((rc = choose_leg_shapes(p)) != GSHT_OK) return rc;
     p->leg.np = p->npairs;
-    std::vector<StartInfo> si = make_start_info(p->lmax, p->mmax, p->spin);
+    si = make_start_info(p->lmax, p->mmax, p->spin);
     HIP_TRY(hipMemcpyAsync(p->leg.start, si.data(), sizeof(StartInfo) * si.size(),
                            hipMemcpyHostToDevice, s));
     HIP_TRY(launch_leg_tables(*p, s));
-    if (!with_deconv && (rc = stage_starts(p, s)) != GSHT_OK) return rc;
-    if (with_deconv) {
-        std::vector<double> k1 = deconv_table(p->lmax, p->n1, p->w, p->beta, 1.0 / p->nd);
-        std::vector<double> k2 = deconv_table(p->mmax, p->n2, p->w, p->beta, 1.0);
-        if ((rc = dev_alloc(p, &p->kfac1, sizeof(double) * k1.size())) != GSHT_OK) return rc;
-        if ((rc = dev_alloc(p, &p->kfac2, sizeof(double) * k2.size())) != GSHT_OK) return rc;
-        HIP_TRY(hipMemcpyAsync(p->kfac1, k1.data(), sizeof(double) * k1.size(),
-                               hipMemcpyHostToDevice, s));
-        HIP_TRY(hipMemcpyAsync(p->kfac2, k2.data(), sizeof(double) * k2.size(),
-                               hipMemcpyHostToDevice, s));
-    }
-    // the host vectors above are synchronised before they go out of scope
+    return GSHT_OK;
+}
+
+// The same with the ring starts, complete on return, for a stage entry point.
+int setup_stage(gsht_plan *p, hipStream_t s)
+{
+    std::vector<StartInfo> si;
+    int rc = setup_legendre(p, si, s);
+    if (rc == GSHT_OK)
+        rc = stage_starts(p, s);
+    const hipError_t e = hipStreamSynchronize(s);  // si goes out of scope
+    if (rc == GSHT_OK)
+        HIP_TRY(e);
+    return rc;
+}
+
+// A deconvolution table (see deconv_table), complete on return, as is all that ran on s
+// before: the host computes it (3 ms at lmax 4096) while that runs.
+int setup_deconv(gsht_plan *p, double **out, int kmax, int n, double extra, hipStream_t s)
+{
+    const std::vector<double> k = deconv_table(kmax, n, p->w, p->beta, extra);
+    const int rc = dev_alloc(p, out, sizeof(double) * k.size());
+    if (rc != GSHT_OK)
+        return rc;
+    HIP_TRY(hipMemcpyAsync(*out, k.data(), sizeof(double) * k.size(), hipMemcpyHostToDevice, s));
     HIP_TRY(hipStreamSynchronize(s));
     return GSHT_OK;
 }
@@ -878,7 +890,12 @@ int plan_create_impl(gsht_plan **out, int lmax, int mmax, int spin, const double
     }
     std::call_once(g_fft_once, []() { rocfft_setup(); });
     tr.mark("sizes");
-    if ((rc = setup_legendre(p, s, true)) != GSHT_OK) { free_plan(p); return rc; }
+    std::vector<StartInfo> si;
+    if ((rc = setup_legendre(p, si, s)) != GSHT_OK ||
+        (rc = setup_deconv(p, &p->kfac1, lmax, p->n1, 1.0 / p->nd, s)) != GSHT_OK) {
+        free_plan(p);
+        return rc;
+    }
     p->ws_cap = cap;
     p->spreads = (dirs & DIR_ADJOINT) != 0;
     tr.mark("legendre tables");
@@ -973,6 +990,12 @@ int plan_create_impl(gsht_plan **out, int lmax, int mmax, int spin, const double
         return rc;
     }
     tr.mark(p->leg.resident ? "ring starts" : "no ring starts");
+    // (waits for the ring starts too: the plan's calls may come on other streams)
+    if ((rc = setup_deconv(p, &p->kfac2, mmax, p->n2, 1.0, s)) != GSHT_OK) {
+        free_plan(p);
+        return rc;
+    }
+    tr.mark("deconvolution");
     const hipError_t ce = build_tile_colors(*p, s);
     if (ce != hipSuccess) {
         free_plan(p);
@@ -2053,7 +2076,7 @@ int gsht_legendre_rings(const void *alm, int lmax, int mmax, int spin, int nthet
     p->ds = p->nd = 2 * ntheta - 2;
     p->ncol = spin ? 2 * mmax + 1 : mmax + 1;
     p->npairs = (ntheta + 1) / 2;
-    if ((rc = setup_legendre(p, s, false)) != GSHT_OK) { free_plan(p); return rc; }
+    if ((rc = setup_stage(p, s)) != GSHT_OK) { free_plan(p); return rc; }
     int rc2 = check_launch(launch_prep_alm(*p, alm, 1.0, false, s), "prep_alm");
     if (rc2 == GSHT_OK)
         rc2 = check_launch(launch_leg_synth(*p, F, false, s), "legendre_synth");
@@ -2153,7 +2176,7 @@ int gsht_analysis_minimal(const void *map, int lmax, int mmax, int spin, int nph
     p->ds = p->nd = nd;
     p->ncol = ncol;
     p->npairs = (ntheta + 1) / 2;
-    if ((rc = setup_legendre(p, s, false)) != GSHT_OK) {
+    if ((rc = setup_stage(p, s)) != GSHT_OK) {
         free_plan(p);
         cleanup();
         return rc;
@@ -2191,7 +2214,7 @@ int gsht_legendre_rings_adjoint(const void *F, int lmax, int mmax, int spin, int
     p->ds = p->nd = 2 * ntheta - 2;
     p->ncol = spin ? 2 * mmax + 1 : mmax + 1;
     p->npairs = (ntheta + 1) / 2;
-    if ((rc = setup_legendre(p, s, false)) != GSHT_OK) { free_plan(p); return rc; }
+    if ((rc = setup_stage(p, s)) != GSHT_OK) { free_plan(p); return rc; }
     int rc2 = check_launch(launch_leg_adjoint(*p, F, false, s), "legendre_adjoint");
     if (rc2 == GSHT_OK)
         rc2 = check_launch(launch_leg_finalize(*p, alm, 1.0, false, s), "finalize");
