@@ -460,7 +460,7 @@ const char *gsht_stage_name(int stage);
  * for m < 0).  Columns: spin 0 -> col = m, 0..mmax; spin > 0 -> col = m + mmax,
  * -mmax..mmax.  F is complex (complex128 for F64, complex64 for F32),
  * [ncol][2 ntheta - 2].  ntheta >= lmax + 2 is required only for the later steps;
- * here any ntheta >= 2 is accepted.
+ * here any ntheta >= 2 is accepted.  Harmonics below 2^-900 count as 0.
  */
 int gsht_legendre_rings(const void *alm, int lmax, int mmax, int spin, int ntheta,
                         gsht_precision prec, void *F, void *hip_stream);
@@ -471,7 +471,8 @@ int gsht_legendre_rings(const void *alm, int lmax, int mmax, int spin, int nthet
  *   H_m(theta_j) = F[col][j] + (-1)^(s+m) F[col][2 ntheta - 2 - j],
  * the poles H_m = F[col][j].  Output (overwritten): spin 0 b_lm = sum_j Y_lm(theta_j,0) H_m;
  * spin s: S+ = sum_j sY_lm H_m, S- = sum_j (-s)Y_lm conj(H_{-m}), then the
- * gradient/curl split as in gsht_adjoint_synth_general.
+ * gradient/curl split as in gsht_adjoint_synth_general.  Harmonics below 2^-256 count
+ * as 0.
  */
 int gsht_legendre_rings_adjoint(const void *F, int lmax, int mmax, int spin, int ntheta,
                                 gsht_precision prec, void *alm, void *hip_stream);

@@ -2076,6 +2076,7 @@ int gsht_legendre_rings(const void *alm, int lmax, int mmax, int spin, int nthet
     p->ds = p->nd = 2 * ntheta - 2;
     p->ncol = spin ? 2 * mmax + 1 : mmax + 1;
     p->npairs = (ntheta + 1) / 2;
+    p->start_exp = START_EXP_RINGS;
     if ((rc = setup_stage(p, s)) != GSHT_OK) { free_plan(p); return rc; }
     int rc2 = check_launch(launch_prep_alm(*p, alm, 1.0, false, s), "prep_alm");
     if (rc2 == GSHT_OK)
@@ -2214,6 +2215,7 @@ int gsht_legendre_rings_adjoint(const void *F, int lmax, int mmax, int spin, int
     p->ds = p->nd = 2 * ntheta - 2;
     p->ncol = spin ? 2 * mmax + 1 : mmax + 1;
     p->npairs = (ntheta + 1) / 2;
+    p->start_exp = START_EXP_RINGS_ADJOINT;
     if ((rc = setup_stage(p, s)) != GSHT_OK) { free_plan(p); return rc; }
     int rc2 = check_launch(launch_leg_adjoint(*p, F, false, s), "legendre_adjoint");
     if (rc2 == GSHT_OK)
@@ -2277,6 +2279,7 @@ int gsht_legendre_rings_adjoint_noalloc(const void *F, int lmax, int mmax, int s
     q += b_acc;
     p.leg.start = (StartInfo *)q;
     p.leg.np = p.npairs;
+    p.start_exp = START_EXP_RINGS_ADJOINT;
     const int band = start_band(p, kStartScratchBytes);
     place_starts(&p, (char *)base + kScratchBytes, band, band > mmax);
     // start data: computed on the host, sent from a host copy kept until the next call

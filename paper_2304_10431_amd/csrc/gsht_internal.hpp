@@ -42,6 +42,10 @@ struct LegendreTables {
     bool resident = false;     // the buffers hold the starts of every m
 };
 
+// Binary exponents of the values at which a channel enters the sums (legendre_kernels.hip):
+// whole transforms, and the stage entry points (rings, adjoint).
+constexpr int START_EXP = -100, START_EXP_RINGS = -900, START_EXP_RINGS_ADJOINT = -256;
+
 // Entry block of a channel that stays below the threshold up to lmax.
 constexpr int START_NEVER = 0x7fff;
 
@@ -152,6 +156,7 @@ struct gsht_plan {
     int adj_nchunk = 0;  // chunks of 64 * adj_r ring pairs
     int64_t workspace_bytes = 0;
     int64_t ws_cap = INT64_MAX;  // what they may come to
+    int start_exp = gsht::START_EXP;
     // device tables
     gsht::LegendreTables leg;
     double *uprep = nullptr;   // prepared coefficients [nalm][2 or 4]

@@ -10,8 +10,8 @@
 // column -m of a spin-s field through sY_{l,-m} = (-1)^(s+m) (-s)Y_lm.
 //
 // The start value at l0 = max(m, s) is a single half-angle power term that can
-// be far below the double range; a channel enters the sums at the degree where its value
-// has grown to 2^-100 (legendre_kernels.hip).
+// be far below the double range; a channel enters the sums where its value has grown to
+// 2^-100 (legendre_kernels.hip).
 #include "gsht_internal.hpp"
 
 #include <cmath>

@@ -12,11 +12,15 @@
 //
 // Start values at l0 = max(m, s) can lie far below the double range, and on each ring
 // the values stay negligible until l sin(theta) comes near m.  A table holds, for every
-// (m, ring pair), the 8-degree block at which each channel first reaches 2^-100 and its
-// two recurrence values there; the kernels start each wave at the first such block of
-// its rings, keep a lane's values at 0 until its own block, and then simply set them.
-// Terms below 2^-100, against values of order 1 in the oscillating region, are thus
-// dropped, 47 bits below the rounding of the sums they would enter.
+// (m, ring pair), the first 8-degree block at whose start each channel has reached 2^-100
+// and its two recurrence values there; the kernels start each wave at the first such block
+// of its rings, keep a lane's values at 0 until its own block, and then simply set them.
+// A channel just below 2^-100 at the start of a block is dropped up to its end, so the
+// dropped terms reach 2^-77 at spins up to 10, 2^-64 at spin 100 and 2^-61 at any spin (the
+// recurrence run over every accepted size), against values of order 1 in the oscillating
+// region: 24 (8) bits below the rounding of the sums they would enter.  The stage entry
+// points, whose callers see the rings and coefficients themselves, take 2^-900 (rings) and
+// 2^-256 (adjoint) instead, so that small values come out right, too.
 //
 // Work decomposition: one wave per (m, chunk); a chunk is R slices of 64 consecutive
 // ring pairs counted from the equator, lane L of slice r owning position 64 (R chunk +
@@ -29,19 +33,18 @@ namespace gsht {
 // ---- recurrence starts ----------------------------------------------------------------
 
 // A channel enters at the first multiple of START_DEG degrees above l0 at which its
-// value has reached 2^START_EXP.  At lmax 4096 (spin 2) 77 % of the (m, l, ring) volume
-// in waves of 128 rings lies past the entry; a threshold of 2^-256 would make it 81 %,
-// 2^-900 90 %, 2^-64 76 %.
-constexpr int START_EXP = -100;
+// value has reached 2^inx (gsht_plan::start_exp).  At lmax 4096 (spin 2) 77 % of the (m, l,
+// ring) volume in waves of 128 rings lies past the entry at inx = -100; -256 would make it
+// 81 %, -900 90 %, -64 76 %.
 
-// true value = p 2^ex; ex == 0 <=> at least 2^START_EXP, otherwise ex <= -512 is a
-// multiple of 512.
-__device__ inline void to_scaled(const XD &v, double &p, int &ex)
+// true value = p 2^ex; ex == 0 <=> at least 2^inx, otherwise ex <= -512 is a multiple of
+// 512.
+__device__ inline void to_scaled(const XD &v, int inx, double &p, int &ex)
 {
     if (v.m == 0.0) {
         p = 0.0;
         ex = -512;
-    } else if (v.e >= START_EXP + 1) {
+    } else if (v.e >= inx + 1) {
         p = ldexp(v.m, v.e);
         ex = 0;
     } else {
@@ -51,13 +54,15 @@ __device__ inline void to_scaled(const XD &v, double &p, int &ex)
     }
 }
 
-// Fold to ex = 0 once |p| 2^ex >= 2^START_EXP; step the offset when |p| has grown past
-// 2^256 (START_DEG degrees multiply it by less than 2^32, so |p| stays below 2^444).
-__device__ inline void rescale_channel(double &p0, double &p1, int &ex)
+// Fold to ex = 0 once |p| 2^ex >= 2^inx; step the offset when |p| has grown past 2^256.
+// START_DEG degrees multiply |p| by at most 2^37 at lmax 1000, 2^45 at 4096 and 2^57 at
+// 32766 for small spins, and by 2^109 at spin 20000; a block starts with |p| < 2^(inx + 512)
+// at ex = -512 and with |p| < 2^256 at smaller ex, so |p| stays below 2^(412 + 109).
+__device__ inline void rescale_channel(double &p0, double &p1, int &ex, int inx)
 {
     if (ex == 0)
         return;
-    if (fabs(p1) >= ldexp(1.0, ex < -1024 ? 1023 : START_EXP - ex)) {
+    if (fabs(p1) >= ldexp(1.0, ex < -1024 ? 1023 : inx - ex)) {
         p0 = ldexp(p0, ex);
         p1 = ldexp(p1, ex);
         ex = 0;
@@ -73,8 +78,8 @@ __device__ inline void rescale_channel(double &p0, double &p1, int &ex)
 // done once per plan (or in each Legendre launch), 2 ms at lmax 4096.
 template <bool SPIN>
 __global__ __launch_bounds__(64) void leg_starts_kernel(
-    const double *__restrict__ ab, const StartInfo *__restrict__ st, int lmax, int m0, int ntheta,
-    int npairs, int np, double2 *__restrict__ sta, double2 *__restrict__ stb,
+    const double *__restrict__ ab, const StartInfo *__restrict__ st, int lmax, int inx, int m0,
+    int ntheta, int npairs, int np, double2 *__restrict__ sta, double2 *__restrict__ stb,
     int32_t *__restrict__ stk)
 {
     const int m = m0 + blockIdx.y, e = blockIdx.x * 64 + threadIdx.x;
@@ -86,9 +91,9 @@ __global__ __launch_bounds__(64) void leg_starts_kernel(
     double a0 = 0.0, a1 = 0.0, b0 = 0.0, b1 = 0.0;
     int ea = -512, eb = -512;
     if (valid) {
-        to_scaled(start_value(si.mant_p, si.ex_p, si.a_p, si.b_p, sh, ch), a1, ea);
+        to_scaled(start_value(si.mant_p, si.ex_p, si.a_p, si.b_p, sh, ch), inx, a1, ea);
         if (SPIN)
-            to_scaled(start_value(si.mant_m, si.ex_m, si.a_m, si.b_m, sh, ch), b1, eb);
+            to_scaled(start_value(si.mant_m, si.ex_m, si.a_m, si.b_m, sh, ch), inx, b1, eb);
     }
     const size_t idx = (size_t)blockIdx.y * np + e;
     int ka = START_NEVER, kb = START_NEVER;
@@ -121,9 +126,9 @@ __global__ __launch_bounds__(64) void leg_starts_kernel(
             }
         }
         if (wa)
-            rescale_channel(a0, a1, ea);
+            rescale_channel(a0, a1, ea, inx);
         if (SPIN && wb)
-            rescale_channel(b0, b1, eb);
+            rescale_channel(b0, b1, eb, inx);
     }
     if (e >= np)
         return;
@@ -143,10 +148,10 @@ hipError_t launch_leg_starts(const gsht_plan &p, int m0, int nm, hipStream_t s)
     dim3 blk(64), grd((p.leg.np + 63) / 64, nm);
     if (p.spin)
         hipLaunchKernelGGL(leg_starts_kernel<true>, grd, blk, 0, s, p.leg.ab, p.leg.start, p.lmax,
-                           m0, p.ntheta, p.npairs, p.leg.np, p.leg.sta, p.leg.stb, p.leg.stk);
+                           p.start_exp, m0, p.ntheta, p.npairs, p.leg.np, p.leg.sta, p.leg.stb, p.leg.stk);
     else
         hipLaunchKernelGGL(leg_starts_kernel<false>, grd, blk, 0, s, p.leg.ab, p.leg.start, p.lmax,
-                           m0, p.ntheta, p.npairs, p.leg.np, p.leg.sta, p.leg.stb, p.leg.stk);
+                           p.start_exp, m0, p.ntheta, p.npairs, p.leg.np, p.leg.sta, p.leg.stb, p.leg.stk);
     return hipGetLastError();
 }
 
