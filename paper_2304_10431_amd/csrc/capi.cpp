@@ -795,8 +795,8 @@ int setup_columns(gsht_plan *p, hipStream_t s)
 }
 
 // Opt-in timing of the plan-creation phases (GSHT_PLAN_TRACE=1: one line per phase on
-// stderr, and how the spreading flushes its patches; the stream is synchronised at each
-// mark, so traced creation is slower).
+// stderr, the shape of the column kernels and how the spreading flushes its patches; the
+// stream is synchronised at each mark, so traced creation is slower).
 struct PlanTrace {
     bool on;
     hipStream_t s;
@@ -815,6 +815,15 @@ struct PlanTrace {
         fprintf(stderr, "gsht plan: %-18s %9.3f ms\n", what,
                 std::chrono::duration<double, std::milli>(now - t).count());
         t = now;
+    }
+    void columns(const gsht_plan &p) const
+    {
+        if (!on)
+            return;
+        int nt, fwd, adj;
+        column_shape(p, nt, fwd, adj);
+        fprintf(stderr, "gsht plan: column mode %d, %d threads, %d forward and %d adjoint slots\n",
+                p.colmode, nt, fwd, adj);
     }
     void spreading(const gsht_plan &p) const
     {
@@ -902,6 +911,7 @@ int plan_create_impl(gsht_plan **out, int lmax, int mmax, int spin, const double
     if ((rc = setup_columns(p, s)) != GSHT_OK) { free_plan(p); return rc; }
     p->workspace_bytes = ws - (int64_t)p->ncol * (p->nd - p->ds) * (int64_t)cs;
     tr.mark("column setup");
+    tr.columns(*p);
     if ((rc = dev_alloc(p, &p->D, (size_t)p->ncol * p->ds * cs)) != GSHT_OK) { free_plan(p); return rc; }
     if ((rc = dev_alloc(p, &p->E, (size_t)p->ncol * p->n1 * cs)) != GSHT_OK) { free_plan(p); return rc; }
     if ((rc = dev_alloc(p, &p->G, (size_t)p->nrows * gcols * cs)) != GSHT_OK) { free_plan(p); return rc; }

@@ -730,35 +730,40 @@ size_t col_lds(const gsht_plan &p)
 // transform has n / 8 butterflies, so large workgroups leave most of their waves idle on
 // short columns; but while all pairs fit the chip at once (1024 / NT workgroups per CU),
 // more threads shorten each of them.  So: the most threads with which every pair is
-// resident, and enough for 12 (FP32) or 9 (FP64) values per thread.  Forward + adjoint,
-// spin 2: FP64 lmax 512 (513 pairs) 256 threads 0.061, 512 0.081, 1024 0.106 ms; lmax 255
-// (256 pairs) 0.039, 0.037, 0.039; FP32 lmax 700 256 threads 0.064, 512 0.081 ms; lmax
-// 1024 128 threads 0.115, 256 0.107, 512 0.130 ms.
+// resident, and enough for 12 (FP32) or 9 (FP64) values per thread.  That is 256 to 1024
+// threads (FP32: 512): more than 1024 pairs have columns too long for fewer than 256.
+// Forward + adjoint, spin 2: FP64 lmax 512 (513 pairs) 256 threads 0.061, 512 0.081, 1024
+// 0.106 ms; lmax 255 (256 pairs) 0.039, 0.037, 0.039; FP32 lmax 700 256 threads 0.064, 512
+// 0.081 ms; lmax 1024 256 threads 0.107, 512 0.130 ms.
 template <typename T>
 int half_threads(const gsht_plan &p)
 {
     constexpr int top = col_half_threads<T>(), per = sizeof(T) == 4 ? 12 : 9;
     const int nh = p.n1 / 2, n = p.nd > nh ? p.nd : nh, pairs = (p.ncol + 1) / 2;
     int nt = top;
-    while (nt > 64 && pairs > 256 * (1024 / nt) && n <= per * (nt / 2))
+    while (nt > 256 && pairs > 256 * (1024 / nt) && n <= per * (nt / 2))
         nt /= 2;
     return nt;
 }
 
-// Calls f(kernel, threads) with the mode-2 instance for this plan, forward or adjoint.
-// MAXV register slots per thread hold the forward's n1 / 2 or the adjoint's max(nd,
-// n1 / 2) values; slots beyond that cost registers (FP64 with the most, 10, spills 36 to
-// scratch: at lmax 4096 the forward took 1.70 instead of 1.61 ms, single columns).
+// Calls f(kernel, threads, slots) with the mode-2 instance for this plan, forward or
+// adjoint.  MAXV register slots per thread hold the forward's n1 / 2 or the adjoint's
+// max(nd, n1 / 2) values; slots beyond that cost registers (FP64 with the most, 10, spills
+// 36 to scratch: at lmax 4096 the forward took 1.70 instead of 1.61 ms, single columns).
+// The lists below hold the counts that accepted plans come to (n1 / 2 is 1, 3 or 5 times a
+// power of two, so the forward skips some; its 10 needs columns without LDS padding).
 template <typename T, bool ADJ, int NT, int MAXV, int... MORE, typename F>
 hipError_t with_slots(int v, F &&f)
 {
     if constexpr (sizeof...(MORE) > 0)
         if (v > MAXV)
             return with_slots<T, ADJ, NT, MORE...>(v, f);
+    if (v > MAXV)
+        return hipErrorInvalidValue;
     if constexpr (ADJ)
-        return f(column_adj_half_kernel<T, NT, MAXV>, NT);
+        return f(column_adj_half_kernel<T, NT, MAXV>, NT, MAXV);
     else
-        return f(column_fwd_half_kernel<T, NT, MAXV>, NT);
+        return f(column_fwd_half_kernel<T, NT, MAXV>, NT, MAXV);
 }
 
 template <typename T, bool ADJ, typename F>
@@ -767,19 +772,20 @@ hipError_t with_half(const gsht_plan &p, F &&f)
     const int nt = half_threads<T>(p), nh = p.n1 / 2;
     const int v = ((ADJ && p.nd > nh ? p.nd : nh) + nt - 1) / nt;
     if constexpr (sizeof(T) == 4) {
+        if (nt == 256)
+            return with_slots<T, ADJ, 256, 9, 12>(v, f);
+        return with_slots<T, ADJ, 512, 9, 12, 17>(v, f);
+    } else if constexpr (ADJ) {
         switch (nt) {
-        case 64: return with_slots<T, ADJ, 64, 9, 12>(v, f);
-        case 128: return with_slots<T, ADJ, 128, 9, 12>(v, f);
-        case 256: return with_slots<T, ADJ, 256, 9, 12>(v, f);
-        default: return with_slots<T, ADJ, 512, 9, 12, 17>(v, f);
-        }
-    } else {
-        switch (nt) {
-        case 64: return with_slots<T, ADJ, 64, 6, 9>(v, f);
-        case 128: return with_slots<T, ADJ, 128, 6, 9>(v, f);
         case 256: return with_slots<T, ADJ, 256, 6, 8, 9>(v, f);
         case 512: return with_slots<T, ADJ, 512, 6, 8, 9>(v, f);
         default: return with_slots<T, ADJ, 1024, 4, 5, 6, 7, 8, 9, 10>(v, f);
+        }
+    } else {
+        switch (nt) {
+        case 256: return with_slots<T, ADJ, 256, 6, 8>(v, f);
+        case 512: return with_slots<T, ADJ, 512, 6, 8>(v, f);
+        default: return with_slots<T, ADJ, 1024, 4, 5, 6, 8, 10>(v, f);
         }
     }
 }
@@ -790,7 +796,7 @@ hipError_t set_lds(const gsht_plan &p)
     const int b = (int)col_lds<T>(p);
     hipError_t e;
     if (p.colmode == 2) {
-        auto attr = [&](auto kern, int) {
+        auto attr = [&](auto kern, int, int) {
             return hipFuncSetAttribute((const void *)kern,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, b);
         };
@@ -814,7 +820,7 @@ void launch_fwd(const gsht_plan &p, hipStream_t s)
     const ColArgs a = col_args(p);
     const size_t b = col_lds<T>(p);
     if (p.colmode == 2) {
-        (void)with_half<T, false>(p, [&](auto kern, int nt) {
+        (void)with_half<T, false>(p, [&](auto kern, int nt, int) {
             hipLaunchKernelGGL(kern, dim3((p.ncol + 1) / 2), dim3(nt), b, s, (const C *)p.D, (C *)p.E, a,
                                p.cf_d, p.cf_h, (const C *)p.twist);
             return hipSuccess;
@@ -832,7 +838,7 @@ void launch_adj(const gsht_plan &p, hipStream_t s)
     const ColArgs a = col_args(p);
     const size_t b = col_lds<T>(p);
     if (p.colmode == 2) {
-        (void)with_half<T, true>(p, [&](auto kern, int nt) {
+        (void)with_half<T, true>(p, [&](auto kern, int nt, int) {
             hipLaunchKernelGGL(kern, dim3((p.ncol + 1) / 2), dim3(nt), b, s, (const C *)p.E, (C *)p.D, a,
                                p.cf_d, p.cf_h, (const C *)p.twist);
             return hipSuccess;
@@ -853,6 +859,27 @@ hipError_t column_set_lds(const gsht_plan &p)
 int column_half_maxn(int prec) { return prec == GSHT_F64 ? col_half_maxn<double>() : col_half_maxn<float>(); }
 
 int column_max_radix(int) { return COL_MAXR; }
+
+void column_shape(const gsht_plan &p, int &threads, int &fwd, int &adj)
+{
+    auto get = [&](int &slots) {
+        return [&](auto, int nt, int v) {
+            threads = nt;
+            slots = v;
+            return hipSuccess;
+        };
+    };
+    threads = fwd = adj = 0;
+    if (p.colmode != 2)
+        return;
+    if (p.prec == GSHT_F64) {
+        (void)with_half<double, false>(p, get(fwd));
+        (void)with_half<double, true>(p, get(adj));
+    } else {
+        (void)with_half<float, false>(p, get(fwd));
+        (void)with_half<float, true>(p, get(adj));
+    }
+}
 
 size_t column_lds_bytes(const gsht_plan &p)
 {

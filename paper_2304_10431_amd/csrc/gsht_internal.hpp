@@ -269,6 +269,8 @@ hipError_t column_set_lds(const gsht_plan &p);                    // once per pl
 int column_half_maxn(int prec);  // largest nd or n1 / 2 of mode 2
 int column_max_radix(int prec);  // largest radix the in-LDS transforms are built with
 size_t column_lds_bytes(const gsht_plan &p);  // LDS per workgroup of the plan's mode
+// mode 2: threads and register slots of the plan's two kernels (other modes: 0)
+void column_shape(const gsht_plan &p, int &threads, int &fwd, int &adj);
 hipError_t launch_column_fwd(const gsht_plan &p, hipStream_t s);  // D -> E
 hipError_t launch_column_adj(const gsht_plan &p, hipStream_t s);  // E -> D
 
