@@ -32,6 +32,7 @@ Usage: python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload NAME]
 from __future__ import annotations
 
 import argparse
+import functools
 import hashlib
 import json
 import math
@@ -90,19 +91,68 @@ def measured_traffic(workload, form, stage, w=None):
     return rec.get("bytes_per_call")
 
 
+@functools.lru_cache(maxsize=None)
+def entered_share(lmax, mmax, spin, exponent=-100, nm=48, nring=256):
+    """Share of the (l, m, ring pair, channel) volume, max(m, s) <= l <= lmax, that the
+    Legendre kernels sum: from the first multiple of 8 degrees above max(m, s) at which the
+    normalised harmonic has reached 2^exponent.  The kernels' recurrence (its magnitudes
+    kept by exponent), run at nm values of m and nring rings of the northern half."""
+    theta = np.pi * (np.arange(nring) + 0.5) / (2 * nring)
+    x, lsh, lch = np.cos(theta), np.log2(np.sin(theta / 2)), np.log2(np.cos(theta / 2))
+    done = total = 0.0
+    for m in np.unique(np.linspace(0, mmax, min(nm, mmax + 1)).astype(int)):
+        m = int(m)
+        l0 = max(m, spin)
+        if l0 > lmax:
+            continue
+        l = np.arange(l0, lmax + 1, dtype=np.float64)
+        inv = 1.0 / np.sqrt(((l + 1) ** 2 - m * m) * ((l + 1) ** 2 - spin * spin))
+        alpha = np.sqrt((2 * l + 3) / (2 * l + 1)) * (l + 1) * (2 * l + 1) * inv
+        norm = np.ones(l.size + 1)  # N_l: the recurrence's factor of p_{l-1} is 1
+        for k in range(1, l.size):
+            lk = l[k]
+            norm[k + 1] = norm[k - 1] * (
+                math.sqrt((2 * lk + 3) / (2 * lk - 1)) * (lk + 1) / lk * inv[k]
+                * math.sqrt((lk * lk - m * m) * (lk * lk - spin * spin)))
+        a = alpha * norm[:-1] / norm[1:]
+        b = a * m * spin / np.maximum(l * (l + 1), 1.0)
+        logbinom = (math.lgamma(2 * l0 + 1) - math.lgamma(abs(m - spin) + 1)
+                    - math.lgamma(2 * l0 - abs(m - spin) + 1)) / math.log(2.0)
+        start = 0.5 * (math.log2((2 * l0 + 1) / (4 * math.pi)) + logbinom)
+        for sg in ((spin, -spin) if spin else (0,)):
+            hc = 2 * max(m - sg, 0) + sg - m  # exponent of cos(theta / 2)
+            ex = start + (2 * l0 - hc) * lsh + hc * lch
+            p0, p1 = np.zeros(nring), np.ones(nring)
+            entry = np.where(ex >= exponent, l0, lmax + 1)
+            sign = 1.0 if sg >= 0 else -1.0
+            for k in range(0, l.size - 8, 8):
+                if not np.any(entry > lmax):
+                    break
+                for d in range(k, k + 8):
+                    p0, p1 = p1, (a[d] * x + sign * b[d]) * p1 - p0
+                p1, e = np.frexp(p1)
+                p0 = np.ldexp(p0, -e)
+                ex = ex + e
+                entry = np.where((entry > lmax) & (ex - 1 >= exponent), l0 + k + 8, entry)
+            done += np.sum(lmax + 1 - entry)
+            total += nring * (lmax + 1 - l0)
+    return done / total if total else 1.0
+
+
 def legendre_flops(lmax, mmax, spin):
-    """Algorithmic FP64 flops of one Legendre launch: per (l, m, ring pair) unit,
-    8 flop for spin 0 (2 FMA recurrence + 2 FMA accumulation) and 24 flop for
-    spin > 0 (2 recurrences + 4 complex-by-real accumulations), over
-    max(m, s) <= l <= lmax, 0 <= m <= mmax and the (lmax + 2) / 2 ring pairs of the
-    smallest ring grid that is exact (lmax + 2 rings)."""
+    """FP64 flops that one Legendre launch has to do: per (l, m, ring pair) unit, 8 flop
+    for spin 0 (2 FMA recurrence + 2 FMA accumulation) and 24 flop for spin > 0 (2
+    recurrences + 4 complex-by-real accumulations), over max(m, s) <= l <= lmax,
+    0 <= m <= mmax and the (lmax + 2) / 2 ring pairs of the smallest ring grid that is
+    exact (lmax + 2 rings), times the share of these units in which the harmonic is not
+    negligible (entered_share)."""
     units = 0
     for m in range(mmax + 1):
         l0 = max(m, spin)
         if l0 <= lmax:
             units += lmax - l0 + 1
     per = 8 if spin == 0 else 24
-    return per * units * ((lmax + 3) // 2)
+    return per * units * ((lmax + 3) // 2) * entered_share(lmax, mmax, spin)
 
 
 def stage_bytes(stage, info, npts, ncomp, prec):
@@ -110,9 +160,9 @@ def stage_bytes(stage, info, npts, ncomp, prec):
     spread: per point its sorted FP64 (theta, phi) (16 B), 4 B permutation entry and
     ncomp map values, plus one read and one write of every kept grid cell, times the
     patch halo factor ((T + w - 1) / T)^2.  interp: the same with one read of the grid.
-    column_fwd: the doubled columns read once (ncol x nd complex) and the kept rows of
-    the oversampled columns written once (ncol x nrows complex); column_adj: the
-    reverse."""
+    column_fwd: the columns read once (ncol x ntheta complex where the stage takes the
+    rings alone, column mode 2, otherwise the doubled nd) and the kept rows of the
+    oversampled columns written once (ncol x nrows complex); column_adj: the reverse."""
     rs = 8 if prec == "f64" else 4
     cs = 2 * rs
     w, t1, t2 = info["w"], info["tile1"], info["tile2"]
@@ -125,7 +175,8 @@ def stage_bytes(stage, info, npts, ncomp, prec):
     if stage == "interp":
         return pts + grid * halo
     if stage in ("column_fwd", "column_adj"):
-        return ncol * (info["ndouble"] + info["nrows"]) * cs
+        length = info["ntheta"] if info["column_mode"] == 2 else info["ndouble"]
+        return ncol * (length + info["nrows"]) * cs
     return None
 
 
