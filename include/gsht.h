@@ -481,13 +481,14 @@ int gsht_legendre_rings_adjoint(const void *F, int lmax, int mmax, int spin, int
  * Allocation-free form of gsht_legendre_rings_adjoint, for callers that cannot
  * allocate device memory (code under HIP graph capture, tight serving loops,
  * harnesses that forbid allocation).  Same arguments, layouts and results; it calls
- * no hipMalloc, hipFree or other allocating routine and does not synchronise.  The
- * Legendre tables, start data and accumulators live in one fixed 64 MiB scratch
- * array per device, held by the library until the process ends; sizes whose tables
- * need more (about 56 nalm bytes for spin > 0, 40 nalm for spin 0) are refused with
- * GSHT_EINVAL before any device work.  Each call rewrites every part of the scratch
- * it reads (start data copied from the host, tables and live-chunk table recomputed,
- * accumulators cleared by a fill kernel).  All calls on one device share its
+ * no hipMalloc, hipFree or other allocating routine and does not synchronise.  It
+ * works in one fixed 128 MiB scratch array per device, held by the library until the
+ * process ends.  Half of it holds the Legendre tables, start data and accumulators;
+ * sizes that need more there (about 56 nalm bytes for spin > 0, 40 nalm for spin 0) are
+ * refused with GSHT_EINVAL before any device work.  The other half holds the
+ * recurrence starts of all rings, in bands of m where they need more.  Each call
+ * rewrites every part of the scratch it reads (start data copied from the host, tables
+ * and starts recomputed, accumulators cleared by a fill kernel).  All calls on one device share its
  * scratch: calls that overlap on one device (other host threads, or other streams
  * still running an earlier call) race and must be serialised by the caller.
  */

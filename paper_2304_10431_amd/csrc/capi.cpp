@@ -1093,7 +1093,7 @@ int plan_synth_grid(gsht_plan *p, const void *alm, double mscale, hipStream_t s,
     return plan_synth_from_D(p, s);
 }
 
-// Doubled columns D -> oversampled grid.
+// Columns D -> oversampled grid.
 int plan_synth_from_D(gsht_plan *p, hipStream_t s)
 {
     if (p->colmode == 0) {
@@ -1140,7 +1140,7 @@ int plan_deriv_impl(gsht_plan *p, const void *alm, void *map, void *dth, void *d
     return ok();
 }
 
-// Adjoint from the map down to the doubled columns D (before the Legendre step).
+// Adjoint from the map down to the columns D (before the Legendre step).
 int plan_adjoint_to_D(gsht_plan *p, const void *map, hipStream_t s)
 {
     const int rc = need_points(p);
@@ -1459,7 +1459,7 @@ static bool use_mfma(const gsht_plan *p)
 }
 
 // Buffers of the matrix-core step, sized for 16 maps: tile offsets per m (16 degrees
-// per block from l0 = max(m, s)), tiles, scales, doubled columns.
+// per block from l0 = max(m, s)), tiles, scales, columns.
 static int setup_mfma(gsht_plan *p, hipStream_t s)
 {
     if (p->mfma_tiles)
@@ -1490,7 +1490,7 @@ static int setup_mfma(gsht_plan *p, hipStream_t s)
 }
 
 // Buffers of the matrix-core adjoint (16 maps): ring-input tiles per (m, slice, 32-ring
-// step), scales, sums; the doubled columns are shared with the matrix-core synthesis.
+// step), scales, sums; the columns are shared with the matrix-core synthesis.
 static int setup_mfma_adj(gsht_plan *p, hipStream_t s)
 {
     int rc;
@@ -1513,13 +1513,6 @@ static int setup_mfma_adj(gsht_plan *p, hipStream_t s)
     return GSHT_OK;
 }
 
-static bool use_mfma_adj(const gsht_plan *p)
-{
-    int S, W;
-    adj_mfma_shape(*p, S, W);
-    return use_mfma(p) && W > 0;
-}
-
 int gsht_plan_adjoint_many(gsht_plan *p, int nmaps, const void *map, void *alm, void *hip_stream)
 {
     if (!p)
@@ -1537,7 +1530,7 @@ int gsht_plan_adjoint_many(gsht_plan *p, int nmaps, const void *map, void *alm, 
     const size_t dstride = (size_t)p->ncol * p->ds;
     const size_t nr = (size_t)2 * p->ncomp;
     int rc;
-    const bool mfma = use_mfma_adj(p);
+    const bool mfma = use_mfma(p);
     for (int k = 0; k < nmaps;) {
         const char *mk = (const char *)map + (map ? k * mstride : 0);
         char *ak = (char *)alm + k * astride;

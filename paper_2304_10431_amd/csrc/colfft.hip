@@ -373,6 +373,10 @@ __device__ inline void load_rows(const C *ec, int i, C &ev, C &od, const ColArgs
 // m + 1 one is even and one odd, and so are their transforms (the deconvolution in theta
 // is even in k): the two run as one complex transform z = f_m + f_{m+1} and separate at
 // the end by f_m[a] = (z[a] + sigma_m z[-a]) / 2, f_{m+1}[a] = (z[a] - sigma_m z[-a]) / 2.
+// The two thereby share the transforms' rounding, relative to the larger of them (an empty
+// column next to a full one is no longer exactly zero); the phi transform, which follows or
+// precedes, mixes all columns at the same level, and the errors of whole calls against 64
+// bits did not move.
 // D then holds the ntheta rings alone, not the doubled meridian.  Half the transforms and half the traffic of D; at lmax
 // 4096, sigma 2: FP64 1.90 -> 1.12 ms forward, 1.80 -> 1.18 ms adjoint (sigma 1.5, FP32:
 // 0.90 -> 0.48 and 0.96 -> 0.59 ms).

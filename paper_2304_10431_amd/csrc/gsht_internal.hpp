@@ -242,9 +242,9 @@ hipError_t launch_prep_mfma(const gsht_plan &p, const void *alm, int nm, const i
 hipError_t launch_leg_synth_mfma(const gsht_plan &p, int nm, const void *tiles,
                                  const float *oscale, const int64_t *boff, void *Dout,
                                  size_t dstride, hipStream_t s);
-// matrix-core adjoint of nm <= 16 maps (FP32 plans) from their doubled columns
+// matrix-core adjoint of nm <= 16 maps (FP32 plans) from their columns
 // (map k at Din + k dstride): ring-input tiles, then the sums into accm [nm][nalm][NR]
-void adj_mfma_shape(const gsht_plan &p, int &S, int &W);  // W = 0: not possible
+void adj_mfma_shape(const gsht_plan &p, int &S, int &W);
 size_t adj_mfma_state_bytes(const gsht_plan &p);          // recurrence state buffer
 hipError_t launch_prep_adj_mfma(const gsht_plan &p, int nm, const void *Din, size_t dstride,
                                 void *tiles, float *oscale, hipStream_t s);

@@ -405,7 +405,7 @@ hipError_t launch_leg_synth(const gsht_plan &p, void *Dout, bool grad, hipStream
 // NM maps at once: the recurrence (both channels) runs once per ring pair and
 // degree and feeds the sums of every map; coefficients are interleaved per degree
 // as u[idx][map][US].  Chunks, starts and blocks are the single-map kernel's.  Map k's
-// doubled columns start at D + k dstride.
+// columns start at D + k dstride.
 template <typename T, bool SPIN, int R, int NM>
 __global__ __launch_bounds__(64) void leg_synth_multi_kernel(
     const double *__restrict__ ab, const double *__restrict__ u, const StartInfo *__restrict__ st,

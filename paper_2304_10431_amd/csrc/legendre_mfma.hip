@@ -317,7 +317,7 @@ __device__ inline unsigned halves(unsigned x, unsigned y)
     return SEL == 0 ? __builtin_amdgcn_perm(y, x, 0x05040100u) : __builtin_amdgcn_perm(y, x, 0x07060302u);
 }
 
-// The eight per-ring adjoint inputs of ring pair q from one map's doubled columns.
+// The eight per-ring adjoint inputs of ring pair q from one map's columns.
 __device__ inline void adj_inputs(const float2 *__restrict__ D, int m, int mmax, int spin, int q,
                                   int ntheta, int nd, int dbl, int npairs, float (&v)[8])
 {
@@ -639,8 +639,7 @@ __global__ __launch_bounds__(64 * adj_wmax<NB>()) void leg_adjoint_mfma_kernel(
 
 // Launch shape of the adjoint kernel: NB sub-blocks of 16 degrees per block (the F
 // tiles of a slice serve all of them), W waves per workgroup within the LDS (slabs of
-// 2 x 16 NB x 68 words each), at most 32 slices per wave (the live mask); W = 0 if
-// the plan has more ring slices than that.  GSHT_ADJ_NB (1, 2 or 4) selects NB.
+// 2 x 16 NB x 68 words each), S ring slices per wave.  GSHT_ADJ_NB (1, 2 or 4) selects NB.
 static int adj_nb()
 {
     const char *e = getenv("GSHT_ADJ_NB");
@@ -657,8 +656,6 @@ void adj_mfma_shape(const gsht_plan &p, int &S, int &W)
     const int wmax = nb == 1 ? adj_wmax<1>() : nb == 2 ? adj_wmax<2>() : adj_wmax<4>();
     S = (nslice + wmax - 1) / wmax;
     W = (nslice + S - 1) / S;
-    if (S > 32)
-        S = W = 0;
 }
 
 size_t adj_mfma_state_bytes(const gsht_plan &p)
@@ -718,7 +715,7 @@ hipError_t launch_leg_adjoint_mfma(const gsht_plan &p, int nm, const void *tiles
 {
     int S, W;
     adj_mfma_shape(p, S, W);
-    if (p.prec != GSHT_F32 || nm < 1 || nm > 16 || W == 0)
+    if (p.prec != GSHT_F32 || nm < 1 || nm > 16)
         return hipErrorInvalidValue;
     if (p.spin)
         return nm > 8 ? adj_mfma_nb<true, 4>(p, nm, W, tiles, oscale, rstate, accm, s)
