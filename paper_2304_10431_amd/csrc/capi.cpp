@@ -477,8 +477,9 @@ int stage_starts(gsht_plan *p, hipStream_t s)
 // their own where `room` bytes of the workspace cap and the device's memory hold all of
 // them.  Otherwise each Legendre launch rebuilds them in E (e_bytes), whose contents are
 // always dead then: a synthesis writes E after its Legendre step, an adjoint reads it for
-// the last time before.  E holds the starts of every m at nearly all sizes (20 or 36
-// bytes per m and ring pair against at least 5 lmax complex values per m).  Rebuilding
+// the last time before.  E holds the starts of every m at all sizes but a few with mmax = 0
+// (20 or 36 bytes per m and ring pair, half as many pairs as lmax, against 2.5 lmax complex
+// values or more per column), which get their few hundred bytes anyway.  Rebuilding
 // takes 2 ms at lmax 4096, spin 2, where the Legendre steps with masks that needed no
 // starts took 2.3 ms more.
 int plan_starts(gsht_plan *p, size_t room, size_t e_bytes, hipStream_t s)
